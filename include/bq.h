@@ -320,10 +320,12 @@ bq_status_t bq_heev(bq_handle_t h, const bq_matrix_t* A, double* w, double* V, i
  * algorithmic work of the launch: 2 m n k per real product for a GEMM,
  * the bytes read plus written for a pre-combination or zero fill. */
 typedef BQ_ENUM(bq_kernel_e) {
-  BQ_KERNEL_GEMM_GAUSS = 0, /* complex x complex, 3 real products    */
+  BQ_KERNEL_GEMM_GAUSS = 0, /* complex x complex, 3 real products; config -1:
+                               one launch of all eight products (24 real) */
   BQ_KERNEL_GEMM_RC = 1,    /* real x complex, 2 real products       */
   BQ_KERNEL_GEMM_CR = 2,    /* complex x real, 2 real products       */
-  BQ_KERNEL_GEMM_RR = 3,    /* real x real, 1 real product           */
+  BQ_KERNEL_GEMM_RR = 3,    /* real x real, 1 real product; config -1: one
+                               launch of all eight products (8 real)   */
   BQ_KERNEL_COMBINE = 10,   /* Hadamard pre-combination              */
   BQ_KERNEL_FILL = 11,      /* zero fill of a structurally zero block */
   BQ_KERNEL_SPLIT = 12,     /* exponents + digit slices of one operand */

@@ -622,6 +622,52 @@ struct CrtRecord {
   int rounds = 0;
 };
 
+// Arguments of the fused kernel for a plan that is the whole bilinear form:
+// eight products of one kind, complex x complex (every component of A and B
+// present) or real x real (the real-quaternion components alone).
+bool fused_args(const Plan& pl, const bq_matrix_t* A, const bq_matrix_t* B, const bq_matrix_t* C, unsigned out_mask,
+                bq::FusedArgs* out) {
+  if (!pl.bilinear || pl.prods.size() != 8) return false;
+  bq::FusedArgs g{};
+  const bool im = A->comp[4] != nullptr;
+  for (int c = 0; c < 8; ++c) {
+    const bool want = c < 4 || im;
+    if ((A->comp[c] != nullptr) != want || (B->comp[c] != nullptr) != want) return false;
+    g.a[c] = A->comp[c];
+    g.b[c] = B->comp[c];
+    g.c[c] = (want && (out_mask >> c & 1)) ? C->comp[c] : nullptr;
+  }
+  g.lda = A->ld;
+  g.ldb = B->ld;
+  g.ldc = C->ld;
+  g.m = pl.m;
+  g.n = pl.n;
+  g.k = pl.k;
+  g.ta = pl.ta;
+  g.tb = pl.tb;
+  g.sL = pl.prods[0].L.s;
+  g.sR = pl.prods[0].R.s;
+  for (int q = 0; q < 8; ++q) {
+    const Prod& p = pl.prods[q];
+    if (p.L.combo != (q < 4 ? -1 : q - 4)) return false;
+    for (const Tgt& t : p.tgts) {
+      if (q < 4) g.cd[t.w] = t.coef.re;
+      else g.ch[t.w][q - 4] = t.coef.re;
+    }
+  }
+  for (int u = 0; u < 4; ++u) {
+    g.sa[u] = pl.wA[0][u];  // the first Hadamard row is (1, 1, 1, 1)
+    g.sb[u] = pl.wB[0][u];
+    g.pair_a[u] = kPairs[u][0];
+    g.pair_b[u] = kPairs[u][1];
+  }
+  auto al16 = [](const double* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
+  g.vec = g.lda % 2 == 0 && g.ldb % 2 == 0;
+  for (int c = 0; c < 8; ++c) g.vec = g.vec && al16(g.a[c]) && al16(g.b[c]);
+  *out = g;
+  return true;
+}
+
 // Enqueue the plan.  Validation has passed.  With rec (CRT form only) the
 // launches are recorded, not made, and every real product of a complex
 // product keeps its own digit buffers.
@@ -819,14 +865,32 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
     return e;
   };
 
-  if (k > 0 && pl.bilinear && !streamed) {
+  // Sizes that leave the per-product launches short of blocks run all eight
+  // products in one launch, which forms the pre-combinations itself.
+  bool fused = false;
+  if (bq::FusedArgs fa; pr.et < 0 && k > 0 && fused_args(pl, A, B, C, out_mask, &fa)) {
+    const int im = fa.a[4] != nullptr;
+    // A forced tile configuration of the real products keeps their launches.
+    const int tile = !im && cfg_override >= 0 ? 0 : bq::fused_tile(im, m, n, k, fa.ta, fa.tb, fa.lda, fa.ldb);
+    if (tile > 0) {
+      Tracer tr(h, s, im ? BQ_KERNEL_GEMM_GAUSS : BQ_KERNEL_GEMM_RR, -1, m, n, k,
+                double(pl.real_gemms) * 2.0 * double(m) * double(n) * double(k), 0.0);
+      hipError_t e = bq::launch_fused(fa, im, tile, s);
+      tr.done();
+      if (e != hipSuccess) return hip_fail(e, "fused product launch");
+      for (int c = 0; c < (im ? 8 : 4); ++c) touched[c] = true;
+      fused = true;
+    }
+  }
+
+  if (k > 0 && pl.bilinear && !streamed && !fused) {
     hipError_t e = combine(true, 0, 4, 0);
     if (e == hipSuccess) e = combine(false, 0, 4, 0);
     if (e != hipSuccess) return hip_fail(e, "pre-combination launch");
   }
 
   for (const Prod& p : pl.prods) {
-    if (k == 0) break;
+    if (k == 0 || fused) break;
     if (&p != &pl.prods.front()) ++round;
     if (rec) rec->rounds = std::max(rec->rounds, round + 1);  // the longest plan of the batch
     Operand L = p.L, R = p.R;

@@ -56,6 +56,23 @@ struct GemmArgs {
   int64_t ldadd;  // leading dimension of the targets' addend blocks
 };
 
+// All eight products of eq. bilinearH on one tile per block (bq_fused.hip).
+// C_w (+ i C_{w+4}) = cd[w] P_{1+w} + sum_q ch[w][q] P_{5+q}, the coefficients
+// real; direct product q pairs units pair_a[q], pair_b[q] of A and B.
+struct FusedArgs {
+  const double* a[8];
+  const double* b[8];
+  double* c[8];  // null: not written
+  int64_t lda, ldb, ldc;
+  int64_t m, n, k;
+  double sa[4], sb[4];  // sign of each unit of op(A), op(B) (sa[0] = sb[0] = 1)
+  double sL, sR;        // conjugation signs of the imaginary parts
+  double cd[4], ch[4][4];
+  int pair_a[4], pair_b[4];
+  int ta, tb;  // A stored k x m, B stored n x k
+  int vec;     // 1: lda, ldb even and operand bases 16-byte aligned
+};
+
 // Linear combinations of quaternion components (the Hadamard rows of
 // eq. bilinearH, with operand signs folded in):
 //   dst_r[q] = sum_u w[q][u] src[u],  dst_i[q] = sum_u w[q][u] src[u + 4].
@@ -191,6 +208,11 @@ hipError_t noalloc_scratch(int device, void** ptr, size_t* bytes);
 hipError_t launch_cgemm(int kind, const GemmArgs& g, int cfg, hipStream_t s);
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 hipError_t launch_fill_zero(double* p, int64_t rows, int64_t cols, int64_t ld, hipStream_t s);
+// The fused kernel (bq_fused.hip); im: 1 with imaginary components (24 real
+// products), 0 for real quaternions (8); tile: 16 or 32.
+hipError_t launch_fused(const FusedArgs& g, int im, int tile, hipStream_t s);
+// Tile edge of the fused kernel for this product, 0: the per-product path.
+int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb);
 int num_tile_configs();
 TileConfig tile_config(int cfg);
 int default_tile_config(int kind, int64_t m, int64_t n, int64_t k);

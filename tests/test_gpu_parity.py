@@ -510,3 +510,31 @@ def test_tuning_switches_same_products(bq, monkeypatch, env, value):
     print(f"{env}={value}", flush=True)
     assert np.array_equal(run(bq, A, B), oracle.gemm(A, B))
     assert np.array_equal(run(bq, Ar, Br, mask_a=R, mask_b=R), oracle.gemm(Ar, Br))
+
+
+@pytest.mark.parametrize("mask", [0xFF, 0x0F])
+@pytest.mark.parametrize("m,k,n,pad", [(1, 1, 1, 0), (16, 16, 16, 0), (17, 31, 33, 1), (31, 33, 15, 0), (48, 7, 100, 1),
+                                       (513, 8, 511, 0), (640, 24, 640, 0), (650, 41, 642, 1)])
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("H", "T")])
+def test_one_launch_products(bq, mask, m, k, n, pad, opA, opB):
+    """Small products run in one launch of 16 x 16 or 32 x 32 tiles (k-steps
+    of 8, 16 or 32): one element, whole tiles, ragged m, n and k, odd and even
+    leading dimensions, both tile sizes.  Integer inputs: every product, sum
+    and Hadamard combination is exact, so the result equals the oracle's; the
+    row padding holds NaN and the padding of C is left alone."""
+    import torch
+
+    A, B = stored_pair(m, k, n, opA, opB, "int", seed=m + k + n, bound=512, mask=mask)
+
+    def padded(X):
+        P = torch.full((8, X.shape[1], X.shape[2] + pad), float("nan"), dtype=torch.float64, device="cuda")
+        P[:, :, :X.shape[2]] = dev(X)
+        return P[:, :, :X.shape[2]]
+
+    Cbuf = torch.full((8, m, n + pad), 12345.0, dtype=torch.float64, device="cuda")
+    print(f"one launch {m}x{k}x{n} pad {pad} {opA}{opB} mask {mask:#x}", flush=True)
+    bq.bq_gemm(padded(A), padded(B), Cbuf[:, :, :n], opA=opA, opB=opB, mask_a=mask, mask_b=mask)
+    torch.cuda.synchronize()
+    got = Cbuf.cpu().numpy()
+    assert np.array_equal(got[:, :, :n], oracle.gemm(OP_FN[opA](A), OP_FN[opB](B)))
+    assert np.all(got[:, :, n:] == 12345.0)
