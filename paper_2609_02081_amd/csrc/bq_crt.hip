@@ -169,6 +169,32 @@ __device__ __forceinline__ void crt_exp_block(const SplitArgs& a, int* exps, int
 // four LDS stages filled straight from global memory three k-steps ahead,
 // every wave moving 4 of the stage's 16 KB.  The int32 result is reduced to
 // its symmetric residue and stored as a byte plane R[i][row][col].
+// Modulus and tile of block b of the blocks [p0, p0 + N T) that run the N
+// residue GEMMs of one product (T tiles each).  Small planes: each XCD takes
+// a contiguous run over (modulus, tile), so it reads one or two moduli's
+// planes once into its 4 MB L2 (a modulus spread over all XCDs is read eight
+// times from beyond them).  Traced launches: n = 1024 30.8 -> 24.2 us, n =
+// 1536 (4.7 MB per modulus) 82.6 -> 79.2, n = 2048 (8.4 MB) 139 -> 131; at
+// n = 3072 (19 MB) no difference.  Larger planes: every modulus is spread over
+// the XCDs, a run of tiles each, so that the planes in use at a time stay in
+// the 256 MB cache behind the L2s.
+constexpr int64_t kCrtXcdPlane = 9 << 20;
+
+__device__ __forceinline__ void crt_gemm_tile_of(const CrtGemmArgs& g, int64_t b, int64_t p0, int nmod, int tiles_m,
+                                                 int tiles_n, int& mod, int& tm, int& tn) {
+  const int64_t T = (int64_t)tiles_m * tiles_n;
+  int t;
+  if (g.plane_a + g.plane_b <= kCrtXcdPlane) {
+    const int64_t pos = xcd_position(b, p0, p0 + T * nmod);
+    mod = (int)(pos / T);
+    t = (int)(pos % T);
+  } else {
+    mod = (int)((b - p0) / T);
+    t = (int)xcd_position(b, p0 + mod * T, p0 + (mod + 1) * T);
+  }
+  grouped_tile(t, tiles_m, tiles_n, tm, tn);
+}
+
 constexpr int kCrtGemmLds = 4 * 4 * 64 * 64;  // four stages of two A and two B 4 KB tiles
 
 __device__ __forceinline__ void crt_gemm_block(const CrtGemmArgs& g, int tm, int tn, int mod, unsigned char* lds) {
@@ -264,13 +290,11 @@ __device__ __forceinline__ void crt_gemm_block(const CrtGemmArgs& g, int tm, int
 }
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-crt_gemm(const CrtGemmArgs g) {
+crt_gemm(const CrtGemmArgs g, int nmod) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kCrtGemmLds];
-  const int tiles_m = (int)((g.m + 127) / 128);
-  const int tiles_n = (int)((g.n + 127) / 128);
-  int tm, tn;
-  slice_tile_coords(tiles_m, tiles_n, tm, tn);
-  crt_gemm_block(g, tm, tn, blockIdx.y, lds);
+  int mod, tm, tn;
+  crt_gemm_tile_of(g, blockIdx.x, 0, nmod, (int)((g.m + 127) / 128), (int)((g.n + 127) / 128), mod, tm, tn);
+  crt_gemm_block(g, tm, tn, mod, lds);
 }
 
 // The same GEMM for large products: a 256 x 256 block of 4 waves (128 x 128
@@ -284,7 +308,7 @@ crt_gemm(const CrtGemmArgs g) {
 // tile in LDS and stored as 16-byte rows.
 template <int NST>  // LDS stages; 4 measured faster than 5
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-crt_gemm_256(const CrtGemmArgs g) {
+crt_gemm_256(const CrtGemmArgs g, int nmod) {
   constexpr int BM = 256, BN = 256, ROWB = 64, TILE = 64 * ROWB;  // 4 KB per 64-row tile
   constexpr int STAGE = 8 * TILE;                                  // four A tiles, four B tiles
   constexpr int NPW = 8;
@@ -292,13 +316,9 @@ crt_gemm_256(const CrtGemmArgs g) {
   constexpr int OUT_LD = BN + 16;
   static_assert(BM * OUT_LD <= NST * STAGE, "the residue tile fits the stages");
   __shared__ __attribute__((aligned(16))) unsigned char lds[NST * STAGE];
-  const int mod = blockIdx.y;
+  int mod, tm, tn;
+  crt_gemm_tile_of(g, blockIdx.x, 0, nmod, (int)((g.m + BM - 1) / BM), (int)((g.n + BN - 1) / BN), mod, tm, tn);
   const int p = kCrtModuli[mod];
-
-  const int tiles_m = (int)((g.m + BM - 1) / BM);
-  const int tiles_n = (int)((g.n + BN - 1) / BN);
-  int tm, tn;
-  slice_tile_coords(tiles_m, tiles_n, tm, tn);
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -605,18 +625,15 @@ __global__ void __launch_bounds__(256) crt_split_grouped(const CrtSplitItem* ite
   }
 }
 
-// Item blocks run modulus by modulus, tiles row by row within a modulus.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kCrtGemmLds];
   const int64_t b = blockIdx.x;
   const int i = crt_find_item(prefix, count, b);
   const CrtGemmArgs& g = items[i].g;
-  const int tiles_n = (int)((g.n + 127) / 128);
-  const int64_t tiles = ((g.m + 127) / 128) * tiles_n;
-  const int64_t local = b - prefix[i];
-  const int t = (int)(local % tiles);
-  crt_gemm_block(g, t / tiles_n, t % tiles_n, (int)(local / tiles), lds);
+  int mod, tm, tn;
+  crt_gemm_tile_of(g, b, prefix[i], items[i].nmod, (int)((g.m + 127) / 128), (int)((g.n + 127) / 128), mod, tm, tn);
+  crt_gemm_block(g, tm, tn, mod, lds);
 }
 
 template <int N>
@@ -750,12 +767,12 @@ hipError_t launch_crt_gemm(int N, const CrtGemmArgs& g, hipStream_t st) {
   if (crt_gemm_tile(N, g.m, g.n) == 256) {
     if (g.kp % 128 != 0) return hipErrorInvalidValue;  // the loop takes k-steps in pairs
     const int64_t tiles = ((g.m + 255) / 256) * ((g.n + 255) / 256);
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(crt_gemm_256<4>, dim3((unsigned)tiles, (unsigned)N), dim3(256), 0, st, g);
+    if (tiles * N > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(crt_gemm_256<4>, dim3((unsigned)(tiles * N)), dim3(256), 0, st, g, N);
   } else {
     const int64_t tiles = ((g.m + 127) / 128) * ((g.n + 127) / 128);
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(crt_gemm, dim3((unsigned)tiles, (unsigned)N), dim3(256), 0, st, g);
+    if (tiles * N > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(crt_gemm, dim3((unsigned)(tiles * N)), dim3(256), 0, st, g, N);
   }
   return hipGetLastError();
 }

@@ -73,17 +73,28 @@ __device__ __forceinline__ int64_t digit_offset(int64_t r, int64_t byte_in_row, 
   return ((r >> 6) * nk + kt) * (64 * RB) + rr * RB + swz_chunk<16>(rr, b >> 4) * 16 + (b & 15);
 }
 
-// Block -> output tile, XCD-aware and grouped by 8 tile rows (as in the
-// FP64 GEMM): consecutive block ids land on different XCDs, so each XCD
-// gets a contiguous run of tiles.
-__device__ __forceinline__ void slice_tile_coords(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int T = tiles_m * tiles_n, w = blockIdx.x;
-  const int x = w % 8, slot = w / 8, base = T / 8, rem = T % 8;
-  const int t = x * base + (x < rem ? x : rem) + slot;
+// Blocks are dealt to the 8 XCDs in turn (b % 8).  Position of block b among
+// the blocks [p0, p1) of a launch when each XCD takes a contiguous run of
+// positions.
+__device__ __forceinline__ int64_t xcd_position(int64_t b, int64_t p0, int64_t p1) {
+  const int64_t x = b & 7;
+  // Blocks below p whose XCD precedes x; blocks of XCD x below p0.
+  auto before = [&](int64_t p) { return (p >> 3) * x + ((p & 7) < x ? (p & 7) : x); };
+  return before(p1) - before(p0) + (b >> 3) - ((p0 + 7 - x) >> 3);
+}
+
+// Tile t of an output, in groups of 8 tile rows (as in the FP64 GEMM).
+__device__ __forceinline__ void grouped_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8;
   const int gm = min(tiles_m - first_m, 8), in_g = t - group * per_group;
   tm = first_m + in_g % gm;
   tn = in_g / gm;
+}
+
+// Block -> output tile of a one-output launch: each XCD gets a contiguous run
+// of tiles.
+__device__ __forceinline__ void slice_tile_coords(int tiles_m, int tiles_n, int& tm, int& tn) {
+  grouped_tile((int)xcd_position(blockIdx.x, 0, (int64_t)tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
 }
 
 // LDS destination of the direct global -> LDS buffer loads.

@@ -265,3 +265,18 @@ def test_n24576_hermitian_sampled(bq):
     err = oracle.rel_frobenius(Cs, oracle.gemm(As, Bs))
     print(f"crt n={n}: sampled rel err {err:.3e}", flush=True)
     assert err <= TOL
+
+
+@pytest.mark.parametrize("m,k,n,tile", [(130, 70, 900, "128"), (385, 100, 129, "128"), (1290, 40, 520, "256"),
+                                        (2600, 2400, 1500, "128")])
+def test_residue_gemm_tile_order(bq, monkeypatch, m, k, n, tile):
+    """Tile counts that are no multiple of 8, small planes (an XCD takes runs
+    over moduli and tiles) and planes above 9 MiB (runs within each modulus):
+    every tile of every modulus is formed once, so an integer product is the
+    oracle's, checked on sampled rows and columns for the largest."""
+    monkeypatch.setenv("BQ_CRT_TILE", tile)
+    print(f"residue GEMM tile order {m}x{k}x{n} tile {tile}", flush=True)
+    A, B = inputs.pair(m, k, n, "int", seed=91, bound=512)
+    got = run(bq, A, B)
+    rows = np.arange(0, m, max(1, m // 150))
+    assert np.array_equal(got[:, rows], oracle.gemm(A[:, rows], B))
