@@ -28,30 +28,34 @@ namespace bq {
 constexpr int kCrtModuli[kMaxCrtModuli] = {255, 253, 251, 247, 241, 239, 233, 229, 227, 223,
                                            211, 199, 197, 193, 191, 181, 179, 173, 167, 163};
 
-// 2^18 and 2^36 modulo each p_i: the weights of the 18-bit limbs of X'.
-struct CrtTables {
-  int w18[kMaxCrtModuli];
-  int w36[kMaxCrtModuli];
+// Per modulus p: the symmetric residues of 256^j, j = 0..3 and 4..6, as four
+// signed bytes each, and p and 1 / p in FP32.
+struct CrtModulus {
+  int wlo, whi;
+  float p, inv;
 };
-constexpr CrtTables make_crt_tables() {
-  CrtTables t{};
+struct CrtModuli {
+  CrtModulus m[kMaxCrtModuli];
+};
+constexpr CrtModuli make_crt_weights() {
+  CrtModuli t{};
   for (int i = 0; i < kMaxCrtModuli; ++i) {
-    t.w18[i] = (int)((1ll << 18) % kCrtModuli[i]);
-    t.w36[i] = (int)((1ll << 36) % kCrtModuli[i]);
+    const int p = kCrtModuli[i];
+    unsigned w[2] = {0, 0};
+    int r = 1;
+    for (int j = 0; j < 7; ++j) {
+      const int s = r > (p - 1) / 2 ? r - p : r;
+      w[j / 4] |= (unsigned)(s & 255) << (8 * (j % 4));
+      r = r * 256 % p;
+    }
+    t.m[i] = {(int)w[0], (int)w[1], (float)p, 1.0f / (float)p};
   }
   return t;
 }
-constexpr CrtTables kCrtW = make_crt_tables();
+__constant__ constexpr CrtModuli kCrtW = make_crt_weights();
 
-// Symmetric residue of t (|t| < 2^31) modulo an odd p: [-(p-1)/2, (p-1)/2].
-// For a p known at compile time (the division becomes a multiplication).
-__device__ __forceinline__ int sym_mod(int t, int p) {
-  t %= p;
-  const int h = (p - 1) >> 1;
-  return t > h ? t - p : (t < -h ? t + p : t);
-}
-
-// The same for a p known at run time: q = rint(t / p) in FP64 is exact (t / p
+// Symmetric residue of t (|t| < 2^31) modulo an odd p, in [-(p-1)/2, (p-1)/2]:
+// q = rint(t / p) in FP64 is exact (t / p
 // is never within 1 / (2 p) of a half-integer for odd p, far above the
 // rounding error), and t - q p is formed exactly by one fma.
 __device__ __forceinline__ int sym_mod_rt(int t, double p, double inv_p) {
@@ -59,108 +63,237 @@ __device__ __forceinline__ int sym_mod_rt(int t, double p, double inv_p) {
   return (int)__builtin_fma(-rint(td * inv_p), p, td);
 }
 
-// Residues of one element: X' = rint(x 2^(b - e)) (|X'| <= 2^53) as 18-bit
-// limbs a2 2^36 + a1 2^18 + a0 (a0, a1 in [0, 2^18), |a2| <= 2^17), so
-// a2 (2^36 mod p) + a1 (2^18 mod p) + a0 stays below 2^27 and one reduction
-// per modulus is left; p and the weights are constants once unrolled.
-template <int N>
-__device__ __forceinline__ void crt_residues(double x, int e, int b, signed char* r) {
+// X' = rint(x 2^(b - e)) (|X'| <= 2^53) as seven signed bytes d_j with X' =
+// sum_j d_j 256^j: adding 128 in each of the seven places makes every digit
+// of the sum d_j + 128, and the top bit of each byte turns it back.
+__device__ __forceinline__ void crt_digits(double x, int e, int b, int& lo, int& hi) {
   const double y = exp_special(e) ? 0.0 : rint(ldexp(x, b - e));
-  const int64_t xi = (int64_t)y;
-  const int a0 = (int)(xi & 0x3ffff);
-  const int a1 = (int)((xi >> 18) & 0x3ffff);
-  const int a2 = (int)(xi >> 36);
-#pragma unroll
-  for (int i = 0; i < N; ++i) r[i] = (signed char)sym_mod(a2 * kCrtW.w36[i] + a1 * kCrtW.w18[i] + a0, kCrtModuli[i]);
+  const uint64_t u = (uint64_t)(int64_t)y + 0x0080808080808080ull;
+  lo = (int)((uint32_t)u ^ 0x80808080u);
+  hi = (int)((uint32_t)(u >> 32) ^ 0x00808080u);
 }
 
-// Left factor: residue planes R[i][row][kk] in the tiled 64-byte layout.
-// Thread: 2 consecutive kk of one row, so a wave reads 1 KB of the row and
-// writes 128 contiguous bytes of each plane.  grid.x = rows_pad,
-// grid.y = kp / 512.
-template <int N>
-__device__ __forceinline__ void crt_split_left_at(const SplitArgs& a, const int* exps, void* out, int64_t r,
-                                                  int64_t kk) {
-  if (kk >= a.kp) return;
-  const int e = (r < a.rows) ? exps[r] : INT_MIN;
-  signed char q[2][N];
+// Symmetric residue modulo m.p in the low byte of the result: t = sum_j d_j
+// (256^j mod p) by two four-byte dot products (|t| < 2^17, summed onto the
+// bits of 1.5 2^23, which makes the sum the FP32 number 1.5 2^23 + t), then t
+// - p rint(t / p).  rint is exact: t / p is at least 1 / (2 p) from a
+// half-integer and its FP32 error below 1e-4.  8 instructions against 25 for
+// 18-bit limbs and an integer division by a constant.
+__device__ __forceinline__ int crt_residue(int lo, int hi, const CrtModulus& m) {
+  constexpr float kMagic = 12582912.0f;  // 1.5 2^23 = 0x4b400000
+  int t = __builtin_amdgcn_sdot4(lo, m.wlo, 0x4b400000, false);
+  t = __builtin_amdgcn_sdot4(hi, m.whi, t, false);
+  const float tm = __builtin_bit_cast(float, t);
+  const float q = __builtin_fmaf(tm - kMagic, m.inv, kMagic) - kMagic;
+  return __builtin_bit_cast(int, __builtin_fmaf(-q, m.p, tm));
+}
+
+// Low bytes of four words, packed.
+__device__ __forceinline__ int pack_bytes(int a, int b, int c, int d) {
+  const unsigned ab = __builtin_amdgcn_perm((unsigned)b, (unsigned)a, 0x0c0c0400u);
+  const unsigned cd = __builtin_amdgcn_perm((unsigned)d, (unsigned)c, 0x04000c0cu);
+  return (int)(ab | cd);
+}
+
+// Residues of one 64 x 64 tile (64 rows of the left factor, or columns of the
+// right one, by 64 of the inner dimension) of the wanted values of an operand
+// in the tiled 64-byte layout.  Thread: 16 consecutive inner elements (one
+// 16-byte chunk of each plane) of one row or column; r and i are read once
+// for all their values.  Where the inner dimension is contiguous four lanes
+// share a row (512 bytes), else 64 lanes a row of the stored matrix.  The
+// moduli run in a loop with their constants in scalar registers.  Traffic
+// bound (8 or 16 bytes read and N written per element and value): at n = 4096
+// all exponents and residues of a product take 6.8 ms (28 GB, 4.1 TB/s)
+// against 9.6 with a launch and an atomic pass per operand; at n = 1024 0.59
+// ms against 1.35 (32 launches against 144).
+__device__ __forceinline__ void crt_split_block(const CrtOperand& a, int64_t b) {
+  const int64_t nkt = a.kp / 64;
+  const int64_t rt = b / nkt, kt = b % nkt;
+  const int t = threadIdx.x;
+  const int64_t v = rt * 64 + (a.along ? t >> 2 : t & 63);
+  const int64_t k0 = kt * 64 + (a.along ? t & 3 : t >> 6) * 16;
+  const int64_t K = a.along ? a.cols : a.rows;
+  const bool in = v < a.dim;
+  const bool want_i = a.out[1] != nullptr || a.out[2] != nullptr;
+  double r[16], im[16];
+  auto load = [&](const double* p, double (&x)[16]) {
+    if (a.along) {
+      const double* q = p + v * a.ld + k0;
+      if (a.vec && in && k0 + 16 <= K) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int64_t c = kk + t;
-    const double x = (r < a.rows && c < a.cols) ? operand_value(a, r * a.ld + c) : 0.0;
-    crt_residues<N>(x, e, a.beta, q[t]);
+        for (int j = 0; j < 8; ++j) {
+          const double2 d = *reinterpret_cast<const double2*>(q + 2 * j);
+          x[2 * j] = d.x;
+          x[2 * j + 1] = d.y;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = in && k0 + j < K ? q[j] : 0.0;
+      }
+    } else {
+      const double* q = p + k0 * a.ld + v;
+      if (in && k0 + 16 <= K) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = q[j * a.ld];
+      } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = in && k0 + j < K ? q[j * a.ld] : 0.0;
+      }
+    }
+  };
+  load(a.r, r);
+  if (want_i) load(a.i, im);
+  const int64_t o = digit_offset(v, k0, a.kp);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    if (!a.out[s]) continue;
+    const int e = in ? a.e[s][v] : INT_MIN;
+    int lo[16], hi[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const double x = s == 0 ? r[j] : (s == 1 ? im[j] : __builtin_fma(a.w2, im[j], r[j]));
+      crt_digits(x, e, a.bits, lo[j], hi[j]);
+    }
+    unsigned char* out = static_cast<unsigned char*>(a.out[s]) + o;
+    for (int i = 0; i < a.nmod; ++i) {
+      const CrtModulus m = kCrtW.m[i];
+      i4v q;
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        q[g] = pack_bytes(crt_residue(lo[4 * g], hi[4 * g], m), crt_residue(lo[4 * g + 1], hi[4 * g + 1], m),
+                          crt_residue(lo[4 * g + 2], hi[4 * g + 2], m), crt_residue(lo[4 * g + 3], hi[4 * g + 3], m));
+      *reinterpret_cast<i4v*>(out) = q;
+      out += a.plane;
+    }
   }
-  const int64_t o = digit_offset(r, kk, a.kp);
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    *reinterpret_cast<unsigned short*>(static_cast<unsigned char*>(out) + (int64_t)i * a.slice_stride + o) =
-        (unsigned short)((unsigned char)q[0][i] | ((unsigned)(unsigned char)q[1][i] << 8));
 }
 
-template <int N>
-__global__ void __launch_bounds__(256) crt_split_left(const SplitArgs a, const int* exps, void* out) {
-  crt_split_left_at<N>(a, exps, out, blockIdx.x, (int64_t)blockIdx.y * 512 + threadIdx.x * 2);
-}
-
-// Right factor (k x n): residues stored transposed, R[i][col][kk].  Thread:
-// one column and 16 consecutive kk (one 16-byte chunk of each plane),
-// consecutive lanes on consecutive columns, so every row read is coalesced
-// and no LDS transpose is needed.  grid.x = cols_pad / 64, grid.y = kp / 64.
-template <int N>
-__device__ __forceinline__ void crt_split_right_block(const SplitArgs& a, const int* exps, void* out, int64_t bx,
-                                                      int64_t by) {
-  const int64_t c = bx * 64 + (threadIdx.x & 63);
-  const int64_t k0 = by * 64 + (threadIdx.x >> 6) * 16;
-  const int e = (c < a.cols) ? exps[c] : INT_MIN;
-  i4v q[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) q[i] = i4v{0, 0, 0, 0};
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    const int64_t kk = k0 + t;
-    const double x = (c < a.cols && kk < a.rows) ? operand_value(a, kk * a.ld + c) : 0.0;
-    signed char d[N];
-    crt_residues<N>(x, e, a.beta, d);
-#pragma unroll
-    for (int i = 0; i < N; ++i) q[i][t >> 2] |= (int)(unsigned char)d[i] << (8 * (t & 3));
+// Largest magnitude of a set of doubles, kept as the high words of |x| and
+// the low words (which count only where every high word is zero): three
+// integer operations an element, and exact exponents down to denormals.
+struct CrtMax {
+  unsigned hi = 0, lo = 0;
+  __device__ __forceinline__ void add(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    hi = max(hi, (unsigned)(u >> 32) & 0x7fffffffu);
+    lo = max(lo, (unsigned)u);
   }
-  const int64_t o = digit_offset(c, k0, a.kp);
+  __device__ __forceinline__ void merge(unsigned h, unsigned l) {
+    hi = max(hi, h);
+    lo = max(lo, l);
+  }
+  // The frexp exponent, or one of the markers.
+  __device__ __forceinline__ int exponent() const {
+    if (hi >= 0x7ff00000u) return kExpNonFinite;
+    if (hi >= 0x00100000u) return (int)(hi >> 20) - 1022;
+    if (hi != 0) return 32 - 1073 + 31 - __builtin_clz(hi);
+    return lo != 0 ? 31 - __builtin_clz(lo) - 1073 : INT_MIN;
+  }
+};
+
+// Exponents of 16 rows or columns of the wanted values of an operand, 1024
+// threads: where the inner dimension is contiguous a wave per row, else 16
+// columns (128 bytes of a stored row) by 64 row lanes.  Indices past the end
+// are clamped to the last one (a repeated element leaves the maximum), so the
+// loads of four steps are in flight together.  One launch per complex product
+// reads r and i once for three exponents; no initialisation and no atomics.
+constexpr int kCrtExpThreads = 1024;
+struct CrtExpLds {
+  unsigned hi[3][16][16], lo[3][16][16];  // value, wave, column
+};
+__device__ __forceinline__ void crt_exp_block(const CrtOperand& a, int64_t b, CrtExpLds& red) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t K = a.along ? a.cols : a.rows;
+  const bool want_i = a.e[1] != nullptr || a.e[2] != nullptr;
+  CrtMax mx[3];
+  auto add = [&](double r, double i) {
+    if (a.e[0]) mx[0].add(r);
+    if (a.e[1]) mx[1].add(i);
+    if (a.e[2]) mx[2].add(__builtin_fma(a.w2, i, r));
+  };
+  if (a.along) {
+    const int64_t v = min(b * 16 + wave, a.dim - 1);
+    const double* pr = a.r + v * a.ld;
+    const double* pi = want_i ? a.i + v * a.ld : pr;
+    if (a.vec && (K & 1) == 0) {
+      for (int64_t c = 2 * lane; c < K + 2 * lane; c += 512) {
+        double2 x[4], y[4];
 #pragma unroll
-  for (int i = 0; i < N; ++i)
-    *reinterpret_cast<i4v*>(static_cast<unsigned char*>(out) + (int64_t)i * a.slice_stride + o) = q[i];
-}
-
-template <int N>
-__global__ void __launch_bounds__(256) crt_split_right(const SplitArgs a, const int* exps, void* out) {
-  crt_split_right_block<N>(a, exps, out, blockIdx.x, blockIdx.y);
-}
-
-// Exponents of one operand without atomics (grouped launches): a row-kernel
-// operand takes one block per row, a column-kernel operand one block per 64
-// columns over all its rows; every block writes its exponents once.
-__device__ __forceinline__ void crt_exp_block(const SplitArgs& a, int* exps, int64_t b, int* red) {
-  int e = INT_MIN;
-  if (a.left) {
-    const int64_t r = b;
-    for (int64_t c = threadIdx.x; c < a.cols; c += 256) e = max(e, exp_of(operand_value(a, r * a.ld + c)));
-    for (int o = 32; o > 0; o >>= 1) e = max(e, __shfl_xor(e, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      e = max(max(red[0], red[1]), max(red[2], red[3]));
-      exps[r] = exp_special(e) ? e : e + a.head;
+        for (int u = 0; u < 4; ++u) {
+          const int64_t q = min(c + 128 * u, K - 2);
+          x[u] = *reinterpret_cast<const double2*>(pr + q);
+          y[u] = want_i ? *reinterpret_cast<const double2*>(pi + q) : x[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          add(x[u].x, y[u].x);
+          add(x[u].y, y[u].y);
+        }
+      }
+    } else {
+      for (int64_t c = lane; c < K + lane; c += 256) {
+        double x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int64_t q = min(c + 64 * u, K - 1);
+          x[u] = pr[q];
+          y[u] = want_i ? pi[q] : x[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) add(x[u], y[u]);
+      }
     }
   } else {
-    const int64_t c = b * 64 + (threadIdx.x & 63);
-    if (c < a.cols)
-      for (int64_t r = threadIdx.x >> 6; r < a.rows; r += 4) e = max(e, exp_of(operand_value(a, r * a.ld + c)));
-    red[threadIdx.x] = e;
-    __syncthreads();
-    if (threadIdx.x < 64 && c < a.cols) {
-      e = max(max(red[threadIdx.x], red[threadIdx.x + 64]), max(red[threadIdx.x + 128], red[threadIdx.x + 192]));
-      exps[c] = exp_special(e) ? e : e + a.head;
+    const int64_t v = min(b * 16 + (t & 15), a.dim - 1);
+    const int rl = t >> 4;
+    for (int64_t c = rl; c < K + rl; c += 256) {
+      double x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t q = min(c + 64 * u, K - 1) * a.ld + v;
+        x[u] = a.r[q];
+        y[u] = want_i ? a.i[q] : x[u];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) add(x[u], y[u]);
     }
   }
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    if (!a.e[s]) continue;
+    for (int o = 32; o >= (a.along ? 1 : 16); o >>= 1)
+      mx[s].merge(__shfl_xor(mx[s].hi, o), __shfl_xor(mx[s].lo, o));
+    if (a.along) {
+      const int64_t v = b * 16 + wave;
+      if (lane == 0 && v < a.dim) a.e[s][v] = mx[s].exponent();
+    } else if (lane < 16) {
+      red.hi[s][wave][lane] = mx[s].hi;
+      red.lo[s][wave][lane] = mx[s].lo;
+    }
+  }
+  if (!a.along) {
+    __syncthreads();
+    const int s = t >> 4, c = t & 15;
+    if (s < 3 && a.e[s] && b * 16 + c < a.dim) {
+      CrtMax m;
+      for (int w = 0; w < 16; ++w) m.merge(red.hi[s][w][c], red.lo[s][w][c]);
+      a.e[s][b * 16 + c] = m.exponent();
+    }
+  }
+}
+
+// Both operands of a product in one launch: the blocks of x, then those of y.
+__global__ void __launch_bounds__(kCrtExpThreads) crt_exp(const CrtOperand x, const CrtOperand y, int64_t xblocks) {
+  __shared__ CrtExpLds red;
+  const int64_t b = blockIdx.x;
+  if (b < xblocks) crt_exp_block(x, b, red);
+  else crt_exp_block(y, b - xblocks, red);
+}
+
+__global__ void __launch_bounds__(256) crt_split(const CrtOperand x, const CrtOperand y, int64_t xblocks) {
+  const int64_t b = blockIdx.x;
+  if (b < xblocks) crt_split_block(x, b);
+  else crt_split_block(y, b - xblocks);
 }
 
 // One INT8 GEMM per modulus (blockIdx.y): residue planes of X (rows padded
@@ -597,32 +730,20 @@ __device__ __forceinline__ int crt_find_item(const int64_t* prefix, int count, i
   return lo;
 }
 
-__global__ void __launch_bounds__(256) crt_exp_grouped(const CrtSplitItem* items, const int64_t* prefix, int count) {
-  __shared__ int red[256];
+__global__ void __launch_bounds__(kCrtExpThreads) crt_exp_grouped(const CrtOperand* items, const int64_t* prefix,
+                                                                int count) {
+  __shared__ CrtExpLds red;
   const int64_t b = blockIdx.x;
   const int i = crt_find_item(prefix, count, b);
-  crt_exp_block(items[i].a, items[i].exps, b - prefix[i], red);
+  const CrtOperand a = items[i];
+  crt_exp_block(a, b - prefix[i], red);
 }
 
-template <int N>
-__global__ void __launch_bounds__(256) crt_split_grouped(const CrtSplitItem* items, const int64_t* prefix, int count) {
+__global__ void __launch_bounds__(256) crt_split_grouped(const CrtOperand* items, const int64_t* prefix, int count) {
   const int64_t b = blockIdx.x;
   const int i = crt_find_item(prefix, count, b);
-  const CrtSplitItem& it = items[i];
-  const int64_t local = b - prefix[i];
-  if (it.a.left) {
-    // thread: one pair of kk of one row, pairs of consecutive rows packed
-    // into the block (padding rows are left alone: their GEMM rows are
-    // never stored)
-    const int64_t pairs = it.a.kp / 2;
-    const int64_t q = local * 256 + threadIdx.x;
-    const int64_t r = q / pairs;
-    if (r >= it.a.rows) return;
-    crt_split_left_at<N>(it.a, it.exps, it.out, r, (q % pairs) * 2);
-  } else {
-    const int64_t nky = it.a.kp / 64;
-    crt_split_right_block<N>(it.a, it.exps, it.out, local / nky, local % nky);
-  }
+  const CrtOperand a = items[i];
+  crt_split_block(a, b - prefix[i]);
 }
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -654,18 +775,6 @@ __global__ void __launch_bounds__(256) crt_combine_grouped(const CrtCombineArgs*
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-template <int N>
-static hipError_t launch_crt_split_n(const SplitArgs& a, int* exps, void* out, hipStream_t st) {
-  if (hipError_t e = launch_split_exponents(a, exps, st); e != hipSuccess) return e;
-  if (a.left)
-    hipLaunchKernelGGL((crt_split_left<N>), dim3((unsigned)a.rows_pad, (unsigned)((a.kp + 511) / 512)),
-                       dim3(256), 0, st, a, exps, out);
-  else
-    hipLaunchKernelGGL((crt_split_right<N>), dim3((unsigned)(a.cols_pad / 64), (unsigned)(a.kp / 64)), dim3(256), 0,
-                       st, a, exps, out);
-  return hipGetLastError();
-}
-
 // Chinese remainder constants of the first N moduli, exact (base-2^32
 // big integers): c_i = M_i (M_i^-1 mod p_i) with M_i = M / p_i and M, kept
 // modulo 2^128 as four 32-bit parts (exact in FP64), and c_i / M in FP64.
@@ -742,12 +851,20 @@ static hipError_t launch_crt_combine_n(CrtCombineArgs g, hipStream_t st) {
 #define BQ_CRT_CASES(X) \
   X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)
 
-hipError_t launch_crt_split(int N, const SplitArgs& a, int* exps, void* out, hipStream_t st) {
-#define X(NN) \
-  if (N == NN) return launch_crt_split_n<NN>(a, exps, out, st);
-  BQ_CRT_CASES(X)
-#undef X
-  return hipErrorInvalidValue;
+hipError_t launch_crt_exp(const CrtOperand& x, const CrtOperand& y, hipStream_t st) {
+  const int64_t xb = crt_exp_blocks(x), blocks = xb + crt_exp_blocks(y);
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(crt_exp, dim3((unsigned)blocks), dim3(kCrtExpThreads), 0, st, x, y, xb);
+  return hipGetLastError();
+}
+
+hipError_t launch_crt_split(const CrtOperand& x, const CrtOperand& y, hipStream_t st) {
+  const int64_t xb = crt_split_blocks(x), blocks = xb + crt_split_blocks(y);
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff || x.nmod > kMaxCrtModuli || y.nmod > kMaxCrtModuli) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(crt_split, dim3((unsigned)blocks), dim3(256), 0, st, x, y, xb);
+  return hipGetLastError();
 }
 
 // Block shape of the residue GEMMs: 256 x 256 once the grid holds two
@@ -791,30 +908,20 @@ int64_t crt_combine_blocks(const CrtCombineArgs& c) {
   return (c.m * ((c.n + kGroupedCombineCols - 1) / kGroupedCombineCols) + 255) / 256;
 }
 
-hipError_t launch_crt_exp_grouped(const CrtSplitItem* items, const int64_t* prefix, int count, int64_t blocks,
+hipError_t launch_crt_exp_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
                                   hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_exp_grouped, dim3((unsigned)blocks), dim3(256), 0, st, items, prefix, count);
+  hipLaunchKernelGGL(crt_exp_grouped, dim3((unsigned)blocks), dim3(kCrtExpThreads), 0, st, items, prefix, count);
   return hipGetLastError();
 }
 
-template <int N>
-static hipError_t launch_crt_split_grouped_n(const CrtSplitItem* items, const int64_t* prefix, int count,
-                                             int64_t blocks, hipStream_t st) {
-  hipLaunchKernelGGL((crt_split_grouped<N>), dim3((unsigned)blocks), dim3(256), 0, st, items, prefix, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_crt_split_grouped(int N, const CrtSplitItem* items, const int64_t* prefix, int count,
-                                    int64_t blocks, hipStream_t st) {
+hipError_t launch_crt_split_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
+                                    hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-#define X(NN) \
-  if (N == NN) return launch_crt_split_grouped_n<NN>(items, prefix, count, blocks, st);
-  BQ_CRT_CASES(X)
-#undef X
-  return hipErrorInvalidValue;
+  hipLaunchKernelGGL(crt_split_grouped, dim3((unsigned)blocks), dim3(256), 0, st, items, prefix, count);
+  return hipGetLastError();
 }
 
 hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t blocks,

@@ -610,7 +610,7 @@ struct Tracer {
 // launched (grouped CRT plans run each stage of every problem in one
 // launch).  round: index of the complex product in the plan.
 struct CrtRecord {
-  struct Split { bq::CrtSplitItem it; int N, round; };
+  struct Split { bq::CrtOperand it; int round; };
   struct Gemm { bq::CrtGemmItem it; int round; };
   struct Comb { bq::CrtCombineArgs c; int N, round; };
   struct Fill { double* p; int64_t rows, cols, ld; };
@@ -791,50 +791,90 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
     return e;
   };
 
-  // CRT form: one real product T = X Y into residue set q (exponents and
-  // residue planes of its INT8 GEMMs); crt_combine reconstructs it.
+  // CRT form: one operand side of a complex product, nothing wanted yet.
   const int64_t ldr = crt_ldr(n);
   int round = 0;  // complex product being enqueued (recorded launches carry it)
-  auto crt_product = [&](const double* x1, const double* x2, double xw2, int64_t ldx, const double* y1,
-                         const double* y2, double yw2, int64_t ldy, int q) -> hipError_t {
-    bq::SplitArgs xa = pl.ta ? bq::SplitArgs{x1, x2, 1.0, xw2, ldx, k, m, 0, sl.rows_pad, sl.kp,
-                                             sl.rows_pad * sl.kp, beta, 0, 0}
-                             : bq::SplitArgs{x1, x2, 1.0, xw2, ldx, m, k, sl.rows_pad, 0, sl.kp,
-                                             sl.rows_pad * sl.kp, beta, 0, 1};
-    bq::SplitArgs ya = pl.tb ? bq::SplitArgs{y1, y2, 1.0, yw2, ldy, n, k, sl.cols_pad, 0, sl.kp,
-                                             sl.cols_pad * sl.kp, beta, 0, 1}
-                             : bq::SplitArgs{y1, y2, 1.0, yw2, ldy, k, n, 0, sl.cols_pad, sl.kp,
-                                             sl.cols_pad * sl.kp, beta, 0, 0};
+  auto crt_operand = [&](const Operand& O, bool left) {
+    bq::CrtOperand a{};
+    a.r = O.r;
+    a.i = O.i;
+    a.w2 = O.s;
+    a.ld = O.ld;
+    const bool t = left ? pl.ta : pl.tb;
+    // One exponent per row of op(A), per column of op(B): along the stored
+    // rows for A in N and C and for B in T and H.
+    a.along = left ? !t : t;
+    a.dim = left ? m : n;
+    a.rows = a.along ? a.dim : k;
+    a.cols = a.along ? k : a.dim;
+    auto al16 = [](const double* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
+    a.vec = a.ld % 2 == 0 && al16(a.r) && al16(a.i);
+    a.kp = sl.kp;
+    a.plane = (left ? sl.rows_pad : sl.cols_pad) * sl.kp;
+    a.nmod = S;
+    a.bits = beta;
+    return a;
+  };
+  // A complex product's real products (value xs[q] of X times value ys[q] of
+  // Y) into residue sets 0..np-1, for crt_combine to reconstruct.  The
+  // exponents of every value go into the set of the first product that has it
+  // (cc points at them).
+  auto crt_products = [&](const Operand& L, const Operand& R, int np, const int* xs, const int* ys,
+                          bq::CrtCombineArgs* cc) -> hipError_t {
+    bq::CrtOperand x = crt_operand(L, true), y = crt_operand(R, false);
+    int xf[3] = {-1, -1, -1}, yf[3] = {-1, -1, -1};  // first product of each value
+    for (int q = 0; q < np; ++q) {
+      if (xf[xs[q]] < 0) xf[xs[q]] = q;
+      if (yf[ys[q]] < 0) yf[ys[q]] = q;
+      x.e[xs[q]] = crt_ea[xf[xs[q]]];
+      y.e[ys[q]] = crt_eb[yf[ys[q]]];
+      cc->res[q] = crt_res[q];
+      cc->ea[q] = x.e[xs[q]];
+      cc->eb[q] = y.e[ys[q]];
+    }
+    auto gemm_args = [&](int q) {
+      const int dx = rec ? xf[xs[q]] : 0, dy = rec ? yf[ys[q]] : 0;
+      return bq::CrtGemmArgs{crt_da[dx], crt_db[dy], x.plane, y.plane, sl.kp, m, n, crt_res[q], m * ldr, ldr};
+    };
     if (rec) {
-      const int dq = sl.digit_sets > 1 ? q : 0;
-      rec->splits.push_back({{xa, crt_ea[q], crt_da[dq]}, S, round});
-      rec->splits.push_back({{ya, crt_eb[q], crt_db[dq]}, S, round});
-      rec->gemms.push_back({{{crt_da[dq], crt_db[dq], sl.rows_pad * sl.kp, sl.cols_pad * sl.kp, sl.kp, m, n,
-                              crt_res[q], m * ldr, ldr},
-                             S},
-                            round});
+      for (int q = 0; q < np; ++q) {
+        x.out[xs[q]] = crt_da[xf[xs[q]]];
+        y.out[ys[q]] = crt_db[yf[ys[q]]];
+        rec->gemms.push_back({{gemm_args(q), S}, round});
+      }
+      rec->splits.push_back({x, round});
+      rec->splits.push_back({y, round});
       return hipSuccess;
     }
+    const double ex = double(m) * double(k) * 8.0, ey = double(k) * double(n) * 8.0;
     {
-      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, k, 0, 0.0,
-                double(m) * double(k) * 8.0 * (x2 ? 2 : 1) * 2.0 + double(sl.rows_pad) * double(sl.kp) * S);
-      hipError_t e = bq::launch_crt_split(S, xa, crt_ea[q], dig_a, s);
+      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, n, k, 0.0, ex * (x.i ? 2 : 1) + ey * (y.i ? 2 : 1));
+      hipError_t e = bq::launch_crt_exp(x, y, s);
       tr.done();
       if (e != hipSuccess) return e;
     }
-    {
-      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, k, n, 0, 0.0,
-                double(k) * double(n) * 8.0 * (y2 ? 2 : 1) * 2.0 + double(sl.cols_pad) * double(sl.kp) * S);
-      hipError_t e = bq::launch_crt_split(S, ya, crt_eb[q], dig_b, s);
+    // One set of residue planes: every real product's operands in turn, an
+    // operand that the product before had left as it is.
+    for (int q = 0; q < np; ++q) {
+      bq::CrtOperand xq = x, yq = y;
+      if (q == 0 || xs[q] != xs[q - 1]) xq.out[xs[q]] = dig_a;
+      else xq.dim = 0;
+      if (q == 0 || ys[q] != ys[q - 1]) yq.out[ys[q]] = dig_b;
+      else yq.dim = 0;
+      {
+        Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, n, k, 0.0,
+                  (xq.dim ? ex * (xs[q] == 2 ? 2 : 1) + double(m) * double(sl.kp) * S : 0.0) +
+                      (yq.dim ? ey * (ys[q] == 2 ? 2 : 1) + double(n) * double(sl.kp) * S : 0.0));
+        hipError_t e = bq::launch_crt_split(xq, yq, s);
+        tr.done();
+        if (e != hipSuccess) return e;
+      }
+      Tracer tr(h, s, BQ_KERNEL_CRT_GEMM, S, m, n, k, double(S) * 2.0 * double(m) * double(n) * double(k), 0.0);
+      hipError_t e = bq::launch_crt_gemm(S, gemm_args(q), s);
       tr.done();
       if (e != hipSuccess) return e;
     }
-    const bq::CrtGemmArgs cg{dig_a, dig_b, sl.rows_pad * sl.kp, sl.cols_pad * sl.kp, sl.kp, m, n,
-                             crt_res[q], m * ldr, ldr};
-    Tracer tr(h, s, BQ_KERNEL_CRT_GEMM, S, m, n, k, double(S) * 2.0 * double(m) * double(n) * double(k), 0.0);
-    hipError_t e = bq::launch_crt_gemm(S, cg, s);
-    tr.done();
-    return e;
+    return hipSuccess;
   };
 
   auto combine = [&](bool left, int q0, int nq, int slot0) -> hipError_t {
@@ -973,15 +1013,15 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
           if (any) used.push_back((int)pi);
         }
         if (cc.ntgt == 0) continue;
+        int xs[bq::kCrtProducts], ys[bq::kCrtProducts];  // values: 0 real part, 1 imaginary part, 2 Gauss sum
         for (size_t q = 0; q < used.size(); ++q) {
           const RealProd& rp = rps[used[q]];
-          hipError_t e = crt_product(rp.x1, rp.x2, rp.xw2, L.ld, rp.y1, rp.y2, rp.yw2, R.ld, (int)q);
-          if (e != hipSuccess) return hip_fail(e, "split-precision launch");
-          cc.res[q] = crt_res[q];
-          cc.ea[q] = crt_ea[q];
-          cc.eb[q] = crt_eb[q];
+          xs[q] = rp.x2 ? 2 : (rp.x1 == L.r ? 0 : 1);
+          ys[q] = rp.y2 ? 2 : (rp.y1 == R.r ? 0 : 1);
         }
         cc.np = (int)used.size();
+        if (hipError_t e = crt_products(L, R, cc.np, xs, ys, &cc); e != hipSuccess)
+          return hip_fail(e, "split-precision launch");
         for (int w = 0; w < 8; ++w) {
           if (slot_of[w] < 0) continue;
           cc.mode[slot_of[w]] = touched[w] ? bq::TGT_ACCUM : bq::TGT_WRITE;
@@ -1367,9 +1407,8 @@ void tune_cache_store(const std::string& key, int cfg, int dyn) {
 // Grouped CRT plans: every problem's CRT sequence recorded against its own
 // workspace region (base + offset), then laid out as item tables of the
 // grouped launches: the Hadamard pre-combinations of all problems, then per
-// complex product (round) the exponents of every operand, the residues (one
-// launch per modulus count), the residue GEMMs and the reconstructions (one
-// launch per modulus count).
+// complex product (round) the exponents of every operand, the residues, the
+// residue GEMMs and the reconstructions (one launch per modulus count).
 struct CrtLaunch {
   enum Type { PRE, EXP, SPLIT, GEMM, COMBINE } type;
   int N;
@@ -1416,17 +1455,10 @@ void crt_tables(const CrtRecord& rec, std::vector<char>* bytes, std::vector<CrtL
     std::vector<CrtRecord::Split> sp;
     for (const auto& x : rec.splits)
       if (x.round == r) sp.push_back(x);
-    std::stable_sort(sp.begin(), sp.end(), [](const auto& a, const auto& b) { return a.N < b.N; });
-    std::vector<bq::CrtSplitItem> all;
-    for (const auto& x : sp) all.push_back(x.it);
-    add(CrtLaunch::EXP, 0, all, [](const bq::CrtSplitItem& it) { return bq::crt_exp_blocks(it.a); });
-    for (size_t i = 0; i < sp.size();) {
-      size_t j = i;
-      std::vector<bq::CrtSplitItem> part;
-      while (j < sp.size() && sp[j].N == sp[i].N) part.push_back(sp[j++].it);
-      add(CrtLaunch::SPLIT, sp[i].N, part, [](const bq::CrtSplitItem& it) { return bq::crt_split_blocks(it.a); });
-      i = j;
-    }
+    std::vector<bq::CrtOperand> ops;
+    for (const auto& x : sp) ops.push_back(x.it);
+    add(CrtLaunch::EXP, 0, ops, [](const bq::CrtOperand& a) { return bq::crt_exp_blocks(a); });
+    add(CrtLaunch::SPLIT, 0, ops, [](const bq::CrtOperand& a) { return bq::crt_split_blocks(a); });
     std::vector<bq::CrtGemmItem> gm;
     for (const auto& x : rec.gemms)
       if (x.round == r) gm.push_back(x.it);
@@ -1453,11 +1485,11 @@ hipError_t crt_launch(const CrtLaunch& L, const char* d, hipStream_t s) {
       return bq::launch_grouped_combine(reinterpret_cast<const bq::CombineArgs*>(d + L.items), prefix, L.count,
                                         L.blocks, s);
     case CrtLaunch::EXP:
-      return bq::launch_crt_exp_grouped(reinterpret_cast<const bq::CrtSplitItem*>(d + L.items), prefix, L.count,
+      return bq::launch_crt_exp_grouped(reinterpret_cast<const bq::CrtOperand*>(d + L.items), prefix, L.count,
                                         L.blocks, s);
     case CrtLaunch::SPLIT:
-      return bq::launch_crt_split_grouped(L.N, reinterpret_cast<const bq::CrtSplitItem*>(d + L.items), prefix,
-                                          L.count, L.blocks, s);
+      return bq::launch_crt_split_grouped(reinterpret_cast<const bq::CrtOperand*>(d + L.items), prefix, L.count,
+                                          L.blocks, s);
     case CrtLaunch::GEMM:
       return bq::launch_crt_gemm_grouped(reinterpret_cast<const bq::CrtGemmItem*>(d + L.items), prefix, L.count,
                                          L.blocks, s);

@@ -248,7 +248,29 @@ int slice_kstep(int et);              // k per MFMA step (32 or 64)
 int slice_beta(int et);
 int slice_head(int et);
 int slice_flush_steps(int et, int S);  // k-steps per exact level accumulation
-hipError_t launch_crt_split(int N, const SplitArgs& a, int* exps, void* out, hipStream_t s);  // a.beta = bits
+// One operand side of a complex product in the CRT form: its values 0: r, 1: i,
+// 2: r + w2 i (the Gauss sum), those wanted with their exponents (one per row
+// of the left factor, per column of the right one) and residue planes.
+struct CrtOperand {
+  const double* r;
+  const double* i;  // null when only r is wanted
+  double w2;
+  int64_t ld, rows, cols;  // as stored
+  int64_t dim;             // exponents: the stored rows (along = 1) or columns
+  int along;               // 1: the inner dimension is contiguous
+  int vec;                 // 1: rows are 16-byte aligned
+  int64_t kp, plane;       // inner dimension padded to 128; bytes between modulus planes
+  int nmod, bits;
+  int* e[3];     // null: exponent not wanted
+  void* out[3];  // null: residues not wanted
+};
+inline int64_t crt_exp_blocks(const CrtOperand& a) { return (a.dim + 15) / 16; }
+// Tiles of the rows (columns) an operand has; the padding tiles only feed
+// GEMM results that are never stored.
+inline int64_t crt_split_blocks(const CrtOperand& a) { return ((a.dim + 63) / 64) * (a.kp / 64); }
+// Exponents, then residues, of the wanted values of both operands.
+hipError_t launch_crt_exp(const CrtOperand& x, const CrtOperand& y, hipStream_t s);
+hipError_t launch_crt_split(const CrtOperand& x, const CrtOperand& y, hipStream_t s);
 hipError_t launch_crt_gemm(int N, const CrtGemmArgs& g, hipStream_t s);
 hipError_t launch_crt_combine(int N, const CrtCombineArgs& g, hipStream_t s);
 int crt_modulus(int i);
@@ -256,33 +278,22 @@ int crt_modulus(int i);
 // Grouped CRT launches (batched plans): every launch covers a list of items
 // of many problems; item i owns blocks [prefix[i], prefix[i + 1]) of a 1-D
 // grid, and a block finds its item by binary search in prefix.
-//   exponents: one operand per item (CrtSplitItem), crt_exp_blocks blocks;
-//   residues:  the same items, crt_split_blocks blocks (all items one N);
+//   exponents: one operand side of a complex product per item, crt_exp_blocks;
+//   residues:  the same items, crt_split_blocks;
 //   GEMM:      one real product per item, 128 x 128 tiles x moduli;
 //   combine:   one complex product per item (all items one N).
-struct CrtSplitItem {
-  SplitArgs a;
-  int* exps;
-  void* out;
-};
 struct CrtGemmItem {
   CrtGemmArgs g;
   int nmod;
 };
-inline int64_t crt_exp_blocks(const SplitArgs& a) { return a.left ? a.rows : (a.cols + 63) / 64; }
-// Residues of the rows (columns) an operand has; the padding rows (columns)
-// only feed GEMM results that are never stored.
-inline int64_t crt_split_blocks(const SplitArgs& a) {
-  return a.left ? (a.rows * (a.kp / 2) + 255) / 256 : ((a.cols + 63) / 64) * (a.kp / 64);
-}
 inline int64_t crt_gemm_blocks(const CrtGemmItem& it) {
   return ((it.g.m + 127) / 128) * ((it.g.n + 127) / 128) * it.nmod;
 }
 int64_t crt_combine_blocks(const CrtCombineArgs& c);
-hipError_t launch_crt_exp_grouped(const CrtSplitItem* items, const int64_t* prefix, int count, int64_t blocks,
+hipError_t launch_crt_exp_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
                                   hipStream_t s);
-hipError_t launch_crt_split_grouped(int N, const CrtSplitItem* items, const int64_t* prefix, int count,
-                                    int64_t blocks, hipStream_t s);
+hipError_t launch_crt_split_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
+                                    hipStream_t s);
 hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t blocks,
                                    hipStream_t s);
 hipError_t launch_crt_combine_grouped(int N, const CrtCombineArgs* items, const int64_t* prefix, int count,
