@@ -16,10 +16,7 @@
 // carry b bits.
 #include <limits.h>
 
-#include <algorithm>
-#include <cmath>
 #include <cstdlib>
-#include <vector>
 
 #include "bq_split_common.h"
 
@@ -273,8 +270,10 @@ __device__ __forceinline__ void crt_exp_block(const CrtOperand& a, int64_t b, Cr
   }
   if (!a.along) {
     __syncthreads();
-    const int s = t >> 4, c = t & 15;
-    if (s < 3 && a.e[s] && b * 16 + c < a.dim) {
+    const int c = t & 15;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      if (t >> 4 != s || !a.e[s] || b * 16 + c >= a.dim) continue;
       CrtMax m;
       for (int w = 0; w < 16; ++w) m.merge(red.hi[s][w][c], red.lo[s][w][c]);
       a.e[s][b * 16 + c] = m.exponent();
@@ -549,176 +548,267 @@ crt_gemm_256(const CrtGemmArgs g, int nmod) {
   }
 }
 
-// |P| rounded to FP64 once (round to nearest even): the leading 64 bits
-// with every lower bit folded into a sticky bit, converted as two exact
-// 32-bit halves joined by one fma.
-__device__ __forceinline__ double u128_to_double(unsigned __int128 u) {
-  const uint64_t hi = (uint64_t)(u >> 64);
-  int sh = 0;
-  uint64_t top = (uint64_t)u;
-  if (hi != 0) {
-    sh = 64 - __builtin_clzll(hi);
-    const unsigned __int128 rest = u & ((((unsigned __int128)1) << sh) - 1);
-    top = (uint64_t)(u >> sh) | (uint64_t)(rest != 0);
+// Reconstruction constants of one modulus count: with M = p_1 ... p_N and c_i
+// = M_i (M_i^-1 mod p_i), M_i = M / p_i, taken symmetric (|c_i| < M / 2): c_i
+// modulo 2^128 as 16 signed bytes, c[j][i / 4] holding byte j of four moduli;
+// rint(2^23 c_i / M) as 3 signed bytes the same way; M modulo 2^128 as eight
+// 16-bit limbs.  Moduli past the count have zeros.  Everything is formed
+// modulo 2^128, so no wider integer is needed.
+constexpr int kCrtGroups = kMaxCrtModuli / 4;
+struct alignas(16) CrtConsts {
+  int c[16][8];  // kCrtGroups used, rows of 32 bytes
+  int f[3][8];
+  int m16[8];
+};
+struct CrtConstTable {
+  CrtConsts n[kMaxCrtModuli + 1];
+};
+constexpr CrtConsts make_crt_consts(int N) {
+  CrtConsts t{};
+  unsigned __int128 M = 1, each = 0;  // each: 0x80 in every byte
+  for (int i = 0; i < N; ++i) M *= (unsigned)kCrtModuli[i];
+  for (int j = 0; j < 16; ++j) each |= (unsigned __int128)0x80 << (8 * j);
+  for (int h = 0; h < 8; ++h) t.m16[h] = (int)((unsigned)(M >> (16 * h)) & 0xffffu);
+  for (int i = 0; i < N; ++i) {
+    const int p = kCrtModuli[i];
+    unsigned __int128 Mi = 1;
+    int a = 1, inv = 1;  // M_i modulo p, and its inverse by search
+    for (int j = 0; j < N; ++j)
+      if (j != i) {
+        Mi *= (unsigned)kCrtModuli[j];
+        a = a * kCrtModuli[j] % p;
+      }
+    while (a * inv % p != 1) ++inv;
+    // c_i / M = inv / p, symmetric: inv - p where inv / p > 1 / 2.
+    const int num = inv > (p - 1) / 2 ? inv - p : inv;
+    unsigned __int128 c = Mi * (unsigned)inv;
+    if (num < 0) c -= M;
+    c += each;  // bytes d_j + 128 of the signed digits d_j
+    for (int j = 0; j < 16; ++j)
+      t.c[j][i / 4] |= (int)((((unsigned)(c >> (8 * j)) & 255u) ^ 0x80u) << (8 * (i % 4)));
+    const int64_t twice = 2 * (int64_t)num * 8388608 + p;  // rint: floor((2 num 2^23 + p) / (2 p))
+    const int64_t q = twice >= 0 ? twice / (2 * p) : -((-twice + 2 * p - 1) / (2 * p));
+    const unsigned f = (unsigned)(int)q + 0x808080u;
+    for (int j = 0; j < 3; ++j) t.f[j][i / 4] |= (int)((((f >> (8 * j)) & 255u) ^ 0x80u) << (8 * (i % 4)));
   }
+  return t;
+}
+constexpr CrtConstTable make_crt_const_table() {
+  CrtConstTable t{};
+  for (int N = 1; N <= kMaxCrtModuli; ++N) t.n[N] = make_crt_consts(N);
+  return t;
+}
+__constant__ constexpr CrtConstTable kCrtC = make_crt_const_table();
+
+// The same pointer, opaque to the compiler: constants read through it are
+// loaded where they are used rather than all at once (more than the scalar
+// registers hold, which would spill them).
+typedef const __attribute__((address_space(4))) CrtConsts* crt_consts_ptr;
+typedef const __attribute__((address_space(4))) int* const_ints;
+__device__ __forceinline__ crt_consts_ptr reload(crt_consts_ptr p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// |P| 2^shift rounded to FP64 once (to nearest even): the leading 64 bits with
+// every lower bit folded into a sticky bit, converted as two exact 32-bit
+// halves joined by one fma.
+__device__ __forceinline__ double u128_to_double(uint64_t hi, uint64_t lo, int shift) {
+  const int nlz = hi ? __builtin_clzll(hi) : 0;
+  uint64_t top = (hi << nlz) | ((lo >> 1) >> (63 - nlz));
+  const uint64_t rest = lo << nlz;
+  top |= (uint64_t)(rest != 0);
+  top = hi ? top : lo;
   const double d = __builtin_fma((double)(uint32_t)(top >> 32), 4294967296.0, (double)(uint32_t)top);
-  return ldexp(d, sh);
+  return ldexp(d, hi ? 64 - nlz + shift : shift);
 }
 
 // P_p from its residues, T_p = P_p 2^(e + f - 2b) for the np real
 // products, sum_p coef[q][p] T_p into every target.  Thread: 4 consecutive
-// columns of one row (one 32-bit load per residue plane); grid.x = rows *
-// ceil(cols / 1024).  The 128-bit sum runs in FP64 over 32-bit parts of c_i
-// and M: x_j = sum_i r_i c_ij - q M_j stays an integer below 2^45, so every
-// fma is exact; the carries are then moved up (floor and fma, exact) until
-// each part lies in [0, 2^32), the carry out of the top part being the
-// reduction modulo 2^128.  The parts and c_i / M are staged in LDS and read
-// as broadcasts.
+// columns of one row (one 32-bit load per residue plane).  P = sum_i r_i c_i -
+// q M modulo 2^128 in integers: the residues of four moduli of an element sit
+// in one register (a byte transpose of four planes' words), so a four-byte dot
+// product adds four terms to one byte place of P; two places share a 32-bit
+// sum (|sum| < 2^28 with q M taken off), and one pass of carries leaves the
+// 16-bit limbs.  q is rint(s), s = sum_i r_i c_i / M from 23-bit fractions the
+// same way (error below 2^-12): for at most 16 moduli P may come near M / 2,
+// so a fraction of s within 2^-11 of 1/2 is settled by comparing P with M / 2
+// (M < 2^125: an estimate one off leaves P - M or P + M, both in range); with
+// more moduli |P| < 2^-6 M.  About 200 instructions an element and product;
+// FP64 sums over 32-bit parts of c_i with a conversion per residue took 330:
+// n = 4096, 16 moduli, 481 against 761 us per complex product (of which the
+// 48 planes and the targets take 220-610 at the copy rate).
 constexpr int kCombineCols = 4;
-constexpr int kGroupedCombineCols = 2;  // fewer registers per thread, more waves for small products
 
-struct CrtLds {
-  double cpart[kMaxCrtModuli][4];
-  double frac[kMaxCrtModuli];
-  double mpart[4];
-};
-
-template <int N, int CC>
-__device__ __forceinline__ void crt_values(const CrtCombineArgs& g, const CrtLds& K, const signed char* res,
-                                           int64_t off, double (&out)[CC]) {
-  double x[CC][4];
-  double s[CC];
+template <int NG, typename Args>
+__device__ __forceinline__ void crt_values(const Args& g, int nmod, const signed char* res, int64_t off,
+                                           const int (&shift)[4], double (&out)[4]) {
+  // R[e][G]: residues 4 G .. 4 G + 3 of element e.
+  int R[4][NG];
 #pragma unroll
-  for (int e = 0; e < CC; ++e) {
-    s[e] = 0.0;
+  for (int G = 0; G < NG; ++G) {
+    unsigned w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) x[e][j] = 0.0;
+    for (int i = 0; i < 4; ++i)
+      w[i] = 4 * G + i < nmod
+                 ? *reinterpret_cast<const uint32_t*>(res + (int64_t)(4 * G + i) * g.plane_r + off)
+                 : 0u;
+    const unsigned ab0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), ab1 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+    const unsigned cd0 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u), cd1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    R[0][G] = (int)__builtin_amdgcn_perm(cd0, ab0, 0x05040100u);
+    R[1][G] = (int)__builtin_amdgcn_perm(cd0, ab0, 0x07060302u);
+    R[2][G] = (int)__builtin_amdgcn_perm(cd1, ab1, 0x05040100u);
+    R[3][G] = (int)__builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
   }
+  auto dots = [&](int e, const_ints k, int acc) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    static_assert(CC == 2 || CC == 4, "one 16- or 32-bit load per plane");
-    const signed char* src = res + (int64_t)i * g.plane_r + off;
-    const uint32_t w = CC == 4 ? *reinterpret_cast<const uint32_t*>(src) : *reinterpret_cast<const uint16_t*>(src);
-    const double fr = K.frac[i];
+    for (int G = 0; G < NG; ++G) acc = __builtin_amdgcn_sdot4(R[e][G], k[G], acc, false);
+    return acc;
+  };
+  crt_consts_ptr K = reload((crt_consts_ptr)&kCrtC.n[nmod]);
+  int v[4], y[4][8];
 #pragma unroll
-    for (int e = 0; e < CC; ++e) {
-      const double v = (double)(int)(signed char)(w >> (8 * e));
-      s[e] = __builtin_fma(v, fr, s[e]);
+  for (int e = 0; e < 4; ++e) v[e] = dots(e, K->f[1], dots(e, K->f[2], 0) << 8) + (dots(e, K->f[0], 0) >> 8);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) x[e][j] = __builtin_fma(v, K.cpart[i][j], x[e][j]);
-    }
+  for (int h = 0; h < 8; ++h) {
+    if (h % 2 == 0) K = reload(K);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e][h] = dots(e, K->c[2 * h], dots(e, K->c[2 * h + 1], 0) << 8);
   }
-  unsigned __int128 Mu = 0;
+  K = reload(K);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) Mu |= (unsigned __int128)(uint32_t)K.mpart[j] << (32 * j);
-  const __int128 M = (__int128)Mu;
-  constexpr double two32 = 4294967296.0, inv32 = 1.0 / 4294967296.0;
+  for (int e = 0; e < 4; ++e) {
+    const int q = (v[e] + (1 << 14)) >> 15;  // s 2^15 in v
 #pragma unroll
-  for (int e = 0; e < CC; ++e) {
-    const double q = rint(s[e]);
-    uint32_t limb[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      double y = __builtin_fma(-q, K.mpart[j], x[e][j]);
-      const double f = floor(y * inv32);
-      y = __builtin_fma(-f, two32, y);
-      if (j < 3) x[e][j + 1] += f;
-      limb[j] = (uint32_t)y;
+    for (int h = 0; h < 8; ++h) {
+      y[e][h] += __mul24(-q, K->m16[h]);
+      if (h > 0) y[e][h] += y[e][h - 1] >> 16;
     }
-    const unsigned __int128 P = ((unsigned __int128)(((uint64_t)limb[3] << 32) | limb[2]) << 64) |
-                                (((uint64_t)limb[1] << 32) | limb[0]);
-    __int128 Ps = (__int128)P;
-    if (N <= 16) {
-      // M < 2^125: an estimate of q one off leaves P - M or P + M, both in range.
-      const __int128 half = (M - 1) >> 1;
-      if (Ps > half) Ps -= M;
-      else if (Ps < -half) Ps += M;
+    auto limb = [&](int j) {
+      return __builtin_amdgcn_perm((unsigned)y[e][2 * j + 1], (unsigned)y[e][2 * j], 0x05040100u);
+    };
+    uint64_t lo = ((uint64_t)limb(1) << 32) | limb(0), hi = ((uint64_t)limb(3) << 32) | limb(2);
+    if constexpr (NG <= 4) {
+      if (((unsigned)(v[e] + (1 << 14) + 16) & 0x7fffu) < 32u) {
+        unsigned __int128 Mu = 0;
+#pragma unroll
+        for (int h = 0; h < 8; ++h) Mu |= (unsigned __int128)(unsigned)K->m16[h] << (16 * h);
+        const __int128 M = (__int128)Mu, half = (M - 1) >> 1;
+        __int128 P = (__int128)(((unsigned __int128)hi << 64) | lo);
+        if (P > half) P -= M;
+        else if (P < -half) P += M;
+        lo = (uint64_t)P;
+        hi = (uint64_t)((unsigned __int128)P >> 64);
+      }
     }
-    const bool neg = Ps < 0;
-    const double a = u128_to_double((unsigned __int128)(neg ? -Ps : Ps));
+    const bool neg = (int64_t)hi < 0;
+    if (neg) {
+      hi = ~hi + (uint64_t)(lo == 0);
+      lo = 0 - lo;
+    }
+    const double a = u128_to_double(hi, lo, shift[e]);
     out[e] = neg ? -a : a;
   }
 }
 
-// Constants of the first N moduli into LDS (every thread calls it).
-template <int N>
-__device__ __forceinline__ void crt_stage_consts(CrtLds& K, const double (&cpart)[kMaxCrtModuli][4],
-                                                 const double (&frac)[kMaxCrtModuli], const double (&mpart)[4]) {
-  for (int t = threadIdx.x; t < N * 4; t += 256) K.cpart[t / 4][t % 4] = cpart[t / 4][t % 4];
-  for (int t = threadIdx.x; t < N; t += 256) K.frac[t] = frac[t];
-  if (threadIdx.x < 4) K.mpart[threadIdx.x] = mpart[threadIdx.x];
-  __syncthreads();
-}
-
-// Columns c0 .. c0 + CC - 1 of row r of the reconstruction of one complex
-// product.
-template <int N, int CC = kCombineCols>
-__device__ __forceinline__ void crt_combine_at(const CrtCombineArgs& g, const CrtLds& K, int64_t r, int64_t c0) {
+// Columns c0 .. c0 + 3 of row r of the reconstruction of one complex product.
+// Args: CrtCombineArgs as kernel arguments, or in a device table read as
+// constant memory (a private copy would sit in scratch, as the loop over the
+// targets indexes it dynamically).
+template <int NG, typename Args>
+__device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t r, int64_t c0) {
+  constexpr int CC = kCombineCols;
   if (r >= g.m || c0 >= g.n) return;
+  const int np = g.np;
+  const int64_t n = g.n;
   double t[kCrtProducts][CC];
 #pragma unroll
   for (int p = 0; p < kCrtProducts; ++p) {
 #pragma unroll
     for (int e = 0; e < CC; ++e) t[p][e] = 0.0;
-    if (p < g.np) {
-      crt_values<N, CC>(g, K, g.res[p], r * g.ldr + c0, t[p]);
+    if (p < np) {
       const int ea = g.ea[p][r];
+      int eb[CC], shift[CC];
 #pragma unroll
       for (int e = 0; e < CC; ++e) {
-        const int eb = (c0 + e < g.n) ? g.eb[p][c0 + e] : INT_MIN;
-        t[p][e] = exp_special(ea) || exp_special(eb) ? exp_scaled(0.0, ea, eb, 0)
-                                                      : ldexp(t[p][e], ea + eb - 2 * g.bits);
+        eb[e] = (c0 + e < n) ? g.eb[p][c0 + e] : INT_MIN;
+        shift[e] = exp_special(ea) || exp_special(eb[e]) ? 0 : ea + eb[e] - 2 * g.bits;
       }
+      crt_values<NG>(g, nmod, g.res[p], r * g.ldr + c0, shift, t[p]);
+#pragma unroll
+      for (int e = 0; e < CC; ++e)
+        if (exp_special(ea) || exp_special(eb[e])) t[p][e] = exp_scaled(0.0, ea, eb[e], 0);
     }
   }
-  // Per target, its pointer, coefficients and mode go to registers before
-  // any store (the arguments may sit in a device table the compiler cannot
-  // tell apart from C).
-  const int ntgt = g.ntgt, np = g.np;
-  const int64_t n = g.n;
-  for (int q = 0; q < ntgt; ++q) {
-    double* cq = g.c[q] + r * g.ldc;
-    double w[kCrtProducts];
+  // Targets in fours: their old values are loaded together before the first
+  // store (the blocks of C do not overlap, which the compiler cannot know).
+  // The loop stays a loop, so that the targets' arguments are read as needed.
+  const int ntgt = g.ntgt;
+  const bool pairs = g.vec && c0 + CC <= n;
+#pragma unroll 1
+  for (int q0 = 0; q0 < ntgt; q0 += 4) {
+    double old[4][CC];
 #pragma unroll
-    for (int p = 0; p < kCrtProducts; ++p) w[p] = g.coef[q][p];
-    const bool accum = g.mode[q] == TGT_ACCUM;
+    for (int u = 0; u < 4; ++u) {
 #pragma unroll
-    for (int e = 0; e < CC; ++e) {
-      if (c0 + e >= n) continue;
-      // zero coefficients are skipped, as the products they would scale
-      double val = 0.0;
-      bool any = false;
+      for (int e = 0; e < CC; ++e) old[u][e] = 0.0;
+      if (q0 + u < ntgt && g.mode[q0 + u] == TGT_ACCUM) {
+        const double* cq = g.c[q0 + u] + r * g.ldc + c0;
+        if (pairs) {
 #pragma unroll
-      for (int p = 0; p < kCrtProducts; ++p) {
-        if (p < np && w[p] != 0.0) {
-          val = any ? __builtin_fma(w[p], t[p][e], val) : w[p] * t[p][e];
-          any = true;
+          for (int e = 0; e < CC; e += 2) {
+            const double2 d = *reinterpret_cast<const double2*>(cq + e);
+            old[u][e] = d.x;
+            old[u][e + 1] = d.y;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < CC; ++e)
+            if (c0 + e < n) old[u][e] = cq[e];
         }
       }
-      if (accum) val += cq[c0 + e];
-      cq[c0 + e] = val;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (q0 + u >= ntgt) continue;
+      double* cq = g.c[q0 + u] + r * g.ldc + c0;
+      // Zero coefficients are skipped, as the products they would scale; the
+      // first product is added to -0, which leaves every value as it is.
+      double val[CC];
+#pragma unroll
+      for (int e = 0; e < CC; ++e) val[e] = -0.0;
+#pragma unroll
+      for (int p = 0; p < kCrtProducts; ++p)
+        if (g.nz[q0 + u] >> p & 1) {
+          const double w = g.coef[q0 + u][p];
+#pragma unroll
+          for (int e = 0; e < CC; ++e) val[e] = __builtin_fma(w, t[p][e], val[e]);
+        }
+      if (g.mode[q0 + u] == TGT_ACCUM) {
+#pragma unroll
+        for (int e = 0; e < CC; ++e) val[e] += old[u][e];
+      }
+      if (pairs) {
+#pragma unroll
+        for (int e = 0; e < CC; e += 2) *reinterpret_cast<double2*>(cq + e) = double2{val[e], val[e + 1]};
+      } else {
+#pragma unroll
+        for (int e = 0; e < CC; ++e)
+          if (c0 + e < n) cq[e] = val[e];
+      }
     }
   }
 }
 
-template <int N>
-__global__ void __launch_bounds__(256) crt_combine(const CrtCombineArgs g) {
-  __shared__ CrtLds K;
-  crt_stage_consts<N>(K, g.cpart, g.frac, g.mpart);
+template <int NG>
+__global__ void __launch_bounds__(256) crt_combine(const CrtCombineArgs g, int nmod) {
   const int64_t bpr = (g.n + 256 * kCombineCols - 1) / (256 * kCombineCols);
-  crt_combine_at<N>(g, K, blockIdx.x / bpr, (blockIdx.x % bpr) * (256 * kCombineCols) + threadIdx.x * kCombineCols);
+  crt_combine_at<NG>(g, nmod, blockIdx.x / bpr, (blockIdx.x % bpr) * (256 * kCombineCols) + threadIdx.x * kCombineCols);
 }
 
 // ---------------------------------------------------------------------------
 // Grouped forms: one launch over the items of many problems.
 // ---------------------------------------------------------------------------
-// The Chinese remainder constants of one modulus count (filled on the host).
-struct CrtConsts {
-  double cpart[kMaxCrtModuli][4];
-  double frac[kMaxCrtModuli];
-  double mpart[4];
-};
-
 // Last item whose first block is at or before block b.
 __device__ __forceinline__ int crt_find_item(const int64_t* prefix, int count, int64_t b) {
   int lo = 0, hi = count - 1;
@@ -757,100 +847,22 @@ crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count) {
   crt_gemm_block(g, tm, tn, mod, lds);
 }
 
-template <int N>
+template <int NG>
 __global__ void __launch_bounds__(256) crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix,
-                                                           int count, const CrtConsts k) {
-  __shared__ CrtLds K;
-  crt_stage_consts<N>(K, k.cpart, k.frac, k.mpart);
+                                                           int count, int nmod) {
   const int64_t b = blockIdx.x;
   const int i = crt_find_item(prefix, count, b);
-  // thread: one pair of columns; the pairs of consecutive rows packed into
-  // the block
-  const CrtCombineArgs& g = items[i];
-  const int64_t qpr = (g.n + kGroupedCombineCols - 1) / kGroupedCombineCols;
+  // thread: four columns; the quads of consecutive rows packed into the block
+  typedef const __attribute__((address_space(4))) CrtCombineArgs table_args;
+  table_args& g = *(table_args*)(items + __builtin_amdgcn_readfirstlane(i));
+  const int64_t qpr = (g.n + kCombineCols - 1) / kCombineCols;
   const int64_t q = (b - prefix[i]) * 256 + threadIdx.x;
-  crt_combine_at<N, kGroupedCombineCols>(g, K, q / qpr, (q % qpr) * kGroupedCombineCols);
+  crt_combine_at<NG>(g, nmod, q / qpr, (q % qpr) * kCombineCols);
 }
 
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-// Chinese remainder constants of the first N moduli, exact (base-2^32
-// big integers): c_i = M_i (M_i^-1 mod p_i) with M_i = M / p_i and M, kept
-// modulo 2^128 as four 32-bit parts (exact in FP64), and c_i / M in FP64.
-
-static std::vector<uint32_t> big_mul(std::vector<uint32_t> v, uint32_t x) {
-  uint64_t carry = 0;
-  for (uint32_t& l : v) {
-    const uint64_t t = uint64_t(l) * x + carry;
-    l = uint32_t(t);
-    carry = t >> 32;
-  }
-  if (carry) v.push_back(uint32_t(carry));
-  return v;
-}
-
-static std::vector<uint32_t> big_div(const std::vector<uint32_t>& v, uint32_t x) {  // exact division
-  std::vector<uint32_t> q(v.size());
-  uint64_t rem = 0;
-  for (size_t i = v.size(); i-- > 0;) {
-    const uint64_t cur = (rem << 32) | v[i];
-    q[i] = uint32_t(cur / x);
-    rem = cur % x;
-  }
-  return q;
-}
-
-static uint32_t big_mod(const std::vector<uint32_t>& v, uint32_t x) {
-  uint64_t rem = 0;
-  for (size_t i = v.size(); i-- > 0;) rem = ((rem << 32) | v[i]) % x;
-  return uint32_t(rem);
-}
-
-static long double big_value(const std::vector<uint32_t>& v) {
-  long double d = 0.0L;
-  for (size_t i = v.size(); i-- > 0;) d = d * 4294967296.0L + (long double)v[i];
-  return d;
-}
-
-static CrtConsts make_crt_consts(int N) {
-  CrtConsts t{};
-  std::vector<uint32_t> M{1};
-  for (int i = 0; i < N; ++i) M = big_mul(M, uint32_t(kCrtModuli[i]));
-  const long double Md = big_value(M);
-  auto part = [](const std::vector<uint32_t>& v, int j) -> double {
-    return size_t(j) < v.size() ? double(v[size_t(j)]) : 0.0;
-  };
-  for (int j = 0; j < 4; ++j) t.mpart[j] = part(M, j);
-  for (int i = 0; i < N; ++i) {
-    const uint32_t p = uint32_t(kCrtModuli[i]);
-    const std::vector<uint32_t> Mi = big_div(M, p);
-    const uint32_t a = big_mod(Mi, p);
-    uint32_t inv = 1;  // a^-1 mod p by search (p < 256)
-    while ((uint64_t(a) * inv) % p != 1) ++inv;
-    const std::vector<uint32_t> ci = big_mul(Mi, inv);
-    for (int j = 0; j < 4; ++j) t.cpart[i][j] = part(ci, j);
-    t.frac[i] = (double)(big_value(ci) / Md);
-  }
-  return t;
-}
-
-template <int N>
-static hipError_t launch_crt_combine_n(CrtCombineArgs g, hipStream_t st) {
-  const int64_t blocks = g.m * ((g.n + 256 * kCombineCols - 1) / (256 * kCombineCols));
-  if (blocks <= 0) return hipSuccess;
-  if (blocks > 0x7fffffff || (g.ldr % kCombineCols) != 0) return hipErrorInvalidValue;
-  static const CrtConsts k = make_crt_consts(N);
-  std::copy(&k.cpart[0][0], &k.cpart[0][0] + kMaxCrtModuli * 4, &g.cpart[0][0]);
-  std::copy(k.frac, k.frac + kMaxCrtModuli, g.frac);
-  std::copy(k.mpart, k.mpart + 4, g.mpart);
-  hipLaunchKernelGGL((crt_combine<N>), dim3((unsigned)blocks), dim3(256), 0, st, g);
-  return hipGetLastError();
-}
-
-#define BQ_CRT_CASES(X) \
-  X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)
-
 hipError_t launch_crt_exp(const CrtOperand& x, const CrtOperand& y, hipStream_t st) {
   const int64_t xb = crt_exp_blocks(x), blocks = xb + crt_exp_blocks(y);
   if (blocks <= 0) return hipSuccess;
@@ -895,17 +907,24 @@ hipError_t launch_crt_gemm(int N, const CrtGemmArgs& g, hipStream_t st) {
 }
 
 hipError_t launch_crt_combine(int N, const CrtCombineArgs& g, hipStream_t st) {
-#define X(NN) \
-  if (N == NN) return launch_crt_combine_n<NN>(g, st);
-  BQ_CRT_CASES(X)
-#undef X
-  return hipErrorInvalidValue;
+  const int64_t blocks = g.m * ((g.n + 256 * kCombineCols - 1) / (256 * kCombineCols));
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff || (g.ldr % kCombineCols) != 0 || N < 1 || N > kMaxCrtModuli) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(256);
+  switch ((N + 3) / 4) {
+    case 1: hipLaunchKernelGGL(crt_combine<1>, grid, block, 0, st, g, N); break;
+    case 2: hipLaunchKernelGGL(crt_combine<2>, grid, block, 0, st, g, N); break;
+    case 3: hipLaunchKernelGGL(crt_combine<3>, grid, block, 0, st, g, N); break;
+    case 4: hipLaunchKernelGGL(crt_combine<4>, grid, block, 0, st, g, N); break;
+    default: hipLaunchKernelGGL(crt_combine<5>, grid, block, 0, st, g, N); break;
+  }
+  return hipGetLastError();
 }
 
 int crt_modulus(int i) { return (i >= 0 && i < kMaxCrtModuli) ? kCrtModuli[i] : 0; }
 
 int64_t crt_combine_blocks(const CrtCombineArgs& c) {
-  return (c.m * ((c.n + kGroupedCombineCols - 1) / kGroupedCombineCols) + 255) / 256;
+  return (c.m * ((c.n + kCombineCols - 1) / kCombineCols) + 255) / 256;
 }
 
 hipError_t launch_crt_exp_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
@@ -932,23 +951,19 @@ hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* pref
   return hipGetLastError();
 }
 
-template <int N>
-static hipError_t launch_crt_combine_grouped_n(const CrtCombineArgs* items, const int64_t* prefix, int count,
-                                               int64_t blocks, hipStream_t st) {
-  static const CrtConsts k = make_crt_consts(N);
-  hipLaunchKernelGGL((crt_combine_grouped<N>), dim3((unsigned)blocks), dim3(256), 0, st, items, prefix, count, k);
-  return hipGetLastError();
-}
-
 hipError_t launch_crt_combine_grouped(int N, const CrtCombineArgs* items, const int64_t* prefix, int count,
                                       int64_t blocks, hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-#define X(NN) \
-  if (N == NN) return launch_crt_combine_grouped_n<NN>(items, prefix, count, blocks, st);
-  BQ_CRT_CASES(X)
-#undef X
-  return hipErrorInvalidValue;
+  if (blocks > 0x7fffffff || N < 1 || N > kMaxCrtModuli) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(256);
+  switch ((N + 3) / 4) {
+    case 1: hipLaunchKernelGGL(crt_combine_grouped<1>, grid, block, 0, st, items, prefix, count, N); break;
+    case 2: hipLaunchKernelGGL(crt_combine_grouped<2>, grid, block, 0, st, items, prefix, count, N); break;
+    case 3: hipLaunchKernelGGL(crt_combine_grouped<3>, grid, block, 0, st, items, prefix, count, N); break;
+    case 4: hipLaunchKernelGGL(crt_combine_grouped<4>, grid, block, 0, st, items, prefix, count, N); break;
+    default: hipLaunchKernelGGL(crt_combine_grouped<5>, grid, block, 0, st, items, prefix, count, N); break;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace bq

@@ -1033,6 +1033,11 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
         cc.n = n;
         cc.bits = beta;
         cc.ldc = C->ld;
+        cc.vec = cc.ldc % 2 == 0;
+        for (int q = 0; q < cc.ntgt; ++q) {
+          cc.vec = cc.vec && (reinterpret_cast<uintptr_t>(cc.c[q]) & 15u) == 0;
+          for (int p2 = 0; p2 < cc.np; ++p2) cc.nz[q] |= (cc.coef[q][p2] != 0.0) << p2;
+        }
         if (rec) {
           rec->combs.push_back({cc, S, round});
           continue;

@@ -162,12 +162,10 @@ struct CrtCombineArgs {
   int ntgt;
   double* c[kMaxSliceTargets];
   double coef[kMaxSliceTargets][kCrtProducts];
+  int nz[kMaxSliceTargets];  // bit p: coef[q][p] is not zero, one at least
   int mode[kMaxSliceTargets];
   int64_t ldc;
-  // Filled by the launcher: Chinese remainder constants of the N moduli.
-  double cpart[kMaxCrtModuli][4];  // c_i modulo 2^128 as four 32-bit parts, low first
-  double frac[kMaxCrtModuli];      // c_i / M
-  double mpart[4];                 // M modulo 2^128, the same way
+  int vec;  // 1: ldc even and every target 16-byte aligned
 };
 
 // Complex linear map of the 8 components into an R x R complex buffer

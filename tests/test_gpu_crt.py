@@ -280,3 +280,24 @@ def test_residue_gemm_tile_order(bq, monkeypatch, m, k, n, tile):
     got = run(bq, A, B)
     rows = np.arange(0, m, max(1, m // 150))
     assert np.array_equal(got[:, rows], oracle.gemm(A[:, rows], B))
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 8, 12, 13, 16, 17])
+@pytest.mark.parametrize("m,k,n", [(5, 3, 7), (66, 130, 33), (17, 64, 18)])
+def test_modulus_groups_and_edges(bq, N, m, k, n):
+    """Residues are combined four moduli and four columns at a time, split in
+    64 x 64 tiles and scaled in groups of 16 rows or columns: counts on and
+    beside each edge, odd and even rows (8- and 16-byte accesses), columns
+    and rows that are zero, tiny and huge.  Every element
+    equals the oracle's."""
+    R = inputs.MASKS["real"]
+    A, B = inputs.pair(m, k, n, "logspread", seed=92 + N, mask_a=R, mask_b=R)
+    A[0, m // 2] = 0.0
+    A[0, m - 1] *= 2.0 ** -500
+    B[0, :, n // 2] = 0.0
+    B[0, :, 0] *= 2.0 ** 300
+    print(f"crt edges {m}x{k}x{n} N={N}", flush=True)
+    if ozaki2.bits_for(N, k) < 1:
+        pytest.skip("too few moduli for this inner dimension")
+    got = run(bq, A, B, N, mask_a=R, mask_b=R)
+    assert np.array_equal(got[0], ozaki2.product(A[0], B[0], N))
