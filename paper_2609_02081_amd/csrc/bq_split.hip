@@ -224,28 +224,26 @@ constexpr double pow2neg(int e) {
 }
 
 // Output of one wave tile (16 MI x 16 NI at rows r0.., columns c0..):
-// exponent scaling, then coef * T into every target block.
+// exponent scaling, then coef * T into every target block (store_targets).
 template <int MI, int NI>
 __device__ __forceinline__ void store_tile(const SliceGemmArgs& g, const d4s (&acc)[MI][NI], int64_t r0, int64_t c0,
                                            int fr, int fg) {
+  double t[MI * NI * 4];
+  int64_t off[MI * NI * 4];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
+        const int e = (i * NI + j) * 4 + v;
         const int64_t r = r0 + i * 16 + 4 * fg + v;
         const int64_t c = c0 + j * 16 + fr;
-        if (r >= g.m || c >= g.n) continue;
-        const int ea = g.ea[r], eb = g.eb[c];
-        const double t = exp_scaled(acc[i][j][v], ea, eb, 0);
-        const int64_t off = r * g.ldc + c;
-        for (int q = 0; q < g.ntgt; ++q) {
-          double val = g.coef[q] * t;
-          if (g.mode[q] == TGT_ACCUM) val += g.c[q][off];
-          g.c[q][off] = val;
-        }
+        const bool in = r < g.m && c < g.n;
+        off[e] = in ? r * g.ldc + c : -1;
+        t[e] = in ? exp_scaled(acc[i][j][v], g.ea[r], g.eb[c], 0) : 0.0;
       }
+  store_targets(g, t, off);
 }
 
 // ---------------------------------------------------------------------------

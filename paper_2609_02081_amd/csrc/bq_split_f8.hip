@@ -51,19 +51,17 @@ __device__ __forceinline__ f16x mfma_f8(i8x a, i8x b, f16x c) {
 // lane l, element v holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
 __device__ __forceinline__ void store_tile_f8(const SliceGemmArgs& g, const double (&acc)[16], int64_t r0,
                                               int64_t c0, int lane) {
+  double t[16];
+  int64_t off[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int64_t r = r0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int64_t c = c0 + (lane & 31);
-    if (r >= g.m || c >= g.n) continue;
-    const double t = exp_scaled(acc[v], g.ea[r], g.eb[c], 0);
-    const int64_t off = r * g.ldc + c;
-    for (int q = 0; q < g.ntgt; ++q) {
-      double val = g.coef[q] * t;
-      if (g.mode[q] == TGT_ACCUM) val += g.c[q][off];
-      g.c[q][off] = val;
-    }
+    const bool in = r < g.m && c < g.n;
+    off[v] = in ? r * g.ldc + c : -1;
+    t[v] = in ? exp_scaled(acc[v], g.ea[r], g.eb[c], 0) : 0.0;
   }
+  store_targets(g, t, off);
 }
 
 template <int S>
