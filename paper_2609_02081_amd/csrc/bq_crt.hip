@@ -85,13 +85,6 @@ __device__ __forceinline__ int crt_residue(int lo, int hi, const CrtModulus& m) 
   return __builtin_bit_cast(int, __builtin_fmaf(-q, m.p, tm));
 }
 
-// Low bytes of four words, packed.
-__device__ __forceinline__ int pack_bytes(int a, int b, int c, int d) {
-  const unsigned ab = __builtin_amdgcn_perm((unsigned)b, (unsigned)a, 0x0c0c0400u);
-  const unsigned cd = __builtin_amdgcn_perm((unsigned)d, (unsigned)c, 0x04000c0cu);
-  return (int)(ab | cd);
-}
-
 // Residues of one 64 x 64 tile (64 rows of the left factor, or columns of the
 // right one, by 64 of the inner dimension) of the wanted values of an operand
 // in the tiled 64-byte layout.  Thread: 16 consecutive inner elements (one
@@ -103,7 +96,7 @@ __device__ __forceinline__ int pack_bytes(int a, int b, int c, int d) {
 // all exponents and residues of a product take 6.8 ms (28 GB, 4.1 TB/s)
 // against 9.6 with a launch and an atomic pass per operand; at n = 1024 0.59
 // ms against 1.35 (32 launches against 144).
-__device__ __forceinline__ void crt_split_block(const CrtOperand& a, int64_t b) {
+__device__ __forceinline__ void crt_split_block(const SplitOperand& a, int64_t b) {
   const int64_t nkt = a.kp / 64;
   const int64_t rt = b / nkt, kt = b % nkt;
   const int t = threadIdx.x;
@@ -113,33 +106,8 @@ __device__ __forceinline__ void crt_split_block(const CrtOperand& a, int64_t b) 
   const bool in = v < a.dim;
   const bool want_i = a.out[1] != nullptr || a.out[2] != nullptr;
   double r[16], im[16];
-  auto load = [&](const double* p, double (&x)[16]) {
-    if (a.along) {
-      const double* q = p + v * a.ld + k0;
-      if (a.vec && in && k0 + 16 <= K) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const double2 d = *reinterpret_cast<const double2*>(q + 2 * j);
-          x[2 * j] = d.x;
-          x[2 * j + 1] = d.y;
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = in && k0 + j < K ? q[j] : 0.0;
-      }
-    } else {
-      const double* q = p + k0 * a.ld + v;
-      if (in && k0 + 16 <= K) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = q[j * a.ld];
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = in && k0 + j < K ? q[j * a.ld] : 0.0;
-      }
-    }
-  };
-  load(a.r, r);
-  if (want_i) load(a.i, im);
+  load_inner16(a, a.r, v, k0, K, in, r);
+  if (want_i) load_inner16(a, a.i, v, k0, K, in, im);
   const int64_t o = digit_offset(v, k0, a.kp);
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
@@ -152,7 +120,7 @@ __device__ __forceinline__ void crt_split_block(const CrtOperand& a, int64_t b) 
       crt_digits(x, e, a.bits, lo[j], hi[j]);
     }
     unsigned char* out = static_cast<unsigned char*>(a.out[s]) + o;
-    for (int i = 0; i < a.nmod; ++i) {
+    for (int i = 0; i < a.count; ++i) {
       const CrtModulus m = kCrtW.m[i];
       i4v q;
 #pragma unroll
@@ -165,131 +133,8 @@ __device__ __forceinline__ void crt_split_block(const CrtOperand& a, int64_t b) 
   }
 }
 
-// Largest magnitude of a set of doubles, kept as the high words of |x| and
-// the low words (which count only where every high word is zero): three
-// integer operations an element, and exact exponents down to denormals.
-struct CrtMax {
-  unsigned hi = 0, lo = 0;
-  __device__ __forceinline__ void add(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    hi = max(hi, (unsigned)(u >> 32) & 0x7fffffffu);
-    lo = max(lo, (unsigned)u);
-  }
-  __device__ __forceinline__ void merge(unsigned h, unsigned l) {
-    hi = max(hi, h);
-    lo = max(lo, l);
-  }
-  // The frexp exponent, or one of the markers.
-  __device__ __forceinline__ int exponent() const {
-    if (hi >= 0x7ff00000u) return kExpNonFinite;
-    if (hi >= 0x00100000u) return (int)(hi >> 20) - 1022;
-    if (hi != 0) return 32 - 1073 + 31 - __builtin_clz(hi);
-    return lo != 0 ? 31 - __builtin_clz(lo) - 1073 : INT_MIN;
-  }
-};
-
-// Exponents of 16 rows or columns of the wanted values of an operand, 1024
-// threads: where the inner dimension is contiguous a wave per row, else 16
-// columns (128 bytes of a stored row) by 64 row lanes.  Indices past the end
-// are clamped to the last one (a repeated element leaves the maximum), so the
-// loads of four steps are in flight together.  One launch per complex product
-// reads r and i once for three exponents; no initialisation and no atomics.
-constexpr int kCrtExpThreads = 1024;
-struct CrtExpLds {
-  unsigned hi[3][16][16], lo[3][16][16];  // value, wave, column
-};
-__device__ __forceinline__ void crt_exp_block(const CrtOperand& a, int64_t b, CrtExpLds& red) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t K = a.along ? a.cols : a.rows;
-  const bool want_i = a.e[1] != nullptr || a.e[2] != nullptr;
-  CrtMax mx[3];
-  auto add = [&](double r, double i) {
-    if (a.e[0]) mx[0].add(r);
-    if (a.e[1]) mx[1].add(i);
-    if (a.e[2]) mx[2].add(__builtin_fma(a.w2, i, r));
-  };
-  if (a.along) {
-    const int64_t v = min(b * 16 + wave, a.dim - 1);
-    const double* pr = a.r + v * a.ld;
-    const double* pi = want_i ? a.i + v * a.ld : pr;
-    if (a.vec && (K & 1) == 0) {
-      for (int64_t c = 2 * lane; c < K + 2 * lane; c += 512) {
-        double2 x[4], y[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t q = min(c + 128 * u, K - 2);
-          x[u] = *reinterpret_cast<const double2*>(pr + q);
-          y[u] = want_i ? *reinterpret_cast<const double2*>(pi + q) : x[u];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          add(x[u].x, y[u].x);
-          add(x[u].y, y[u].y);
-        }
-      }
-    } else {
-      for (int64_t c = lane; c < K + lane; c += 256) {
-        double x[4], y[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t q = min(c + 64 * u, K - 1);
-          x[u] = pr[q];
-          y[u] = want_i ? pi[q] : x[u];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) add(x[u], y[u]);
-      }
-    }
-  } else {
-    const int64_t v = min(b * 16 + (t & 15), a.dim - 1);
-    const int rl = t >> 4;
-    for (int64_t c = rl; c < K + rl; c += 256) {
-      double x[4], y[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t q = min(c + 64 * u, K - 1) * a.ld + v;
-        x[u] = a.r[q];
-        y[u] = want_i ? a.i[q] : x[u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) add(x[u], y[u]);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    if (!a.e[s]) continue;
-    for (int o = 32; o >= (a.along ? 1 : 16); o >>= 1)
-      mx[s].merge(__shfl_xor(mx[s].hi, o), __shfl_xor(mx[s].lo, o));
-    if (a.along) {
-      const int64_t v = b * 16 + wave;
-      if (lane == 0 && v < a.dim) a.e[s][v] = mx[s].exponent();
-    } else if (lane < 16) {
-      red.hi[s][wave][lane] = mx[s].hi;
-      red.lo[s][wave][lane] = mx[s].lo;
-    }
-  }
-  if (!a.along) {
-    __syncthreads();
-    const int c = t & 15;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      if (t >> 4 != s || !a.e[s] || b * 16 + c >= a.dim) continue;
-      CrtMax m;
-      for (int w = 0; w < 16; ++w) m.merge(red.hi[s][w][c], red.lo[s][w][c]);
-      a.e[s][b * 16 + c] = m.exponent();
-    }
-  }
-}
-
 // Both operands of a product in one launch: the blocks of x, then those of y.
-__global__ void __launch_bounds__(kCrtExpThreads) crt_exp(const CrtOperand x, const CrtOperand y, int64_t xblocks) {
-  __shared__ CrtExpLds red;
-  const int64_t b = blockIdx.x;
-  if (b < xblocks) crt_exp_block(x, b, red);
-  else crt_exp_block(y, b - xblocks, red);
-}
-
-__global__ void __launch_bounds__(256) crt_split(const CrtOperand x, const CrtOperand y, int64_t xblocks) {
+__global__ void __launch_bounds__(256) crt_split(const SplitOperand x, const SplitOperand y, int64_t xblocks) {
   const int64_t b = blockIdx.x;
   if (b < xblocks) crt_split_block(x, b);
   else crt_split_block(y, b - xblocks);
@@ -809,30 +654,10 @@ __global__ void __launch_bounds__(256) crt_combine(const CrtCombineArgs g, int n
 // ---------------------------------------------------------------------------
 // Grouped forms: one launch over the items of many problems.
 // ---------------------------------------------------------------------------
-// Last item whose first block is at or before block b.
-__device__ __forceinline__ int crt_find_item(const int64_t* prefix, int count, int64_t b) {
-  int lo = 0, hi = count - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (prefix[mid] <= b) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-__global__ void __launch_bounds__(kCrtExpThreads) crt_exp_grouped(const CrtOperand* items, const int64_t* prefix,
-                                                                int count) {
-  __shared__ CrtExpLds red;
+__global__ void __launch_bounds__(256) crt_split_grouped(const SplitOperand* items, const int64_t* prefix, int count) {
   const int64_t b = blockIdx.x;
-  const int i = crt_find_item(prefix, count, b);
-  const CrtOperand a = items[i];
-  crt_exp_block(a, b - prefix[i], red);
-}
-
-__global__ void __launch_bounds__(256) crt_split_grouped(const CrtOperand* items, const int64_t* prefix, int count) {
-  const int64_t b = blockIdx.x;
-  const int i = crt_find_item(prefix, count, b);
-  const CrtOperand a = items[i];
+  const int i = find_item(prefix, count, b);
+  const SplitOperand a = items[i];
   crt_split_block(a, b - prefix[i]);
 }
 
@@ -840,7 +665,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kCrtGemmLds];
   const int64_t b = blockIdx.x;
-  const int i = crt_find_item(prefix, count, b);
+  const int i = find_item(prefix, count, b);
   const CrtGemmArgs& g = items[i].g;
   int mod, tm, tn;
   crt_gemm_tile_of(g, b, prefix[i], items[i].nmod, (int)((g.m + 127) / 128), (int)((g.n + 127) / 128), mod, tm, tn);
@@ -851,7 +676,7 @@ template <int NG>
 __global__ void __launch_bounds__(256) crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix,
                                                            int count, int nmod) {
   const int64_t b = blockIdx.x;
-  const int i = crt_find_item(prefix, count, b);
+  const int i = find_item(prefix, count, b);
   // thread: four columns; the quads of consecutive rows packed into the block
   typedef const __attribute__((address_space(4))) CrtCombineArgs table_args;
   table_args& g = *(table_args*)(items + __builtin_amdgcn_readfirstlane(i));
@@ -863,18 +688,10 @@ __global__ void __launch_bounds__(256) crt_combine_grouped(const CrtCombineArgs*
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_crt_exp(const CrtOperand& x, const CrtOperand& y, hipStream_t st) {
-  const int64_t xb = crt_exp_blocks(x), blocks = xb + crt_exp_blocks(y);
+hipError_t launch_crt_split(const SplitOperand& x, const SplitOperand& y, hipStream_t st) {
+  const int64_t xb = split_blocks(x), blocks = xb + split_blocks(y);
   if (blocks <= 0) return hipSuccess;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_exp, dim3((unsigned)blocks), dim3(kCrtExpThreads), 0, st, x, y, xb);
-  return hipGetLastError();
-}
-
-hipError_t launch_crt_split(const CrtOperand& x, const CrtOperand& y, hipStream_t st) {
-  const int64_t xb = crt_split_blocks(x), blocks = xb + crt_split_blocks(y);
-  if (blocks <= 0) return hipSuccess;
-  if (blocks > 0x7fffffff || x.nmod > kMaxCrtModuli || y.nmod > kMaxCrtModuli) return hipErrorInvalidValue;
+  if (blocks > 0x7fffffff || x.count > kMaxCrtModuli || y.count > kMaxCrtModuli) return hipErrorInvalidValue;
   hipLaunchKernelGGL(crt_split, dim3((unsigned)blocks), dim3(256), 0, st, x, y, xb);
   return hipGetLastError();
 }
@@ -927,15 +744,7 @@ int64_t crt_combine_blocks(const CrtCombineArgs& c) {
   return (c.m * ((c.n + kCombineCols - 1) / kCombineCols) + 255) / 256;
 }
 
-hipError_t launch_crt_exp_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
-                                  hipStream_t st) {
-  if (count <= 0 || blocks <= 0) return hipSuccess;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_exp_grouped, dim3((unsigned)blocks), dim3(kCrtExpThreads), 0, st, items, prefix, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_crt_split_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
+hipError_t launch_crt_split_grouped(const SplitOperand* items, const int64_t* prefix, int count, int64_t blocks,
                                     hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;

@@ -610,7 +610,7 @@ struct Tracer {
 // launched (grouped CRT plans run each stage of every problem in one
 // launch).  round: index of the complex product in the plan.
 struct CrtRecord {
-  struct Split { bq::CrtOperand it; int round; };
+  struct Split { bq::SplitOperand it; int round; };
   struct Gemm { bq::CrtGemmItem it; int round; };
   struct Comb { bq::CrtCombineArgs c; int N, round; };
   struct Fill { double* p; int64_t rows, cols, ld; };
@@ -730,10 +730,34 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
   const int beta = crt ? crt_bits(S, k) : (pr.et >= 0 ? bq::slice_beta(pr.et) : 0);
   const int head = (pr.et >= 0 && !crt) ? bq::slice_head(pr.et) : 0;
 
-  // One real product T = X Y of the split form, X = xw1 x1 + xw2 x2 (m x k),
-  // Y = yw1 y1 + yw2 y2 (k x n); C_w op= cw * T for each (w, cw).
-  auto split_product = [&](const double* x1, double xw1, const double* x2, double xw2, int64_t ldx,
-                           const double* y1, double yw1, const double* y2, double yw2, int64_t ldy,
+  // Split forms: one operand side of a complex product, nothing wanted yet.
+  const int64_t ldr = crt_ldr(n);
+  int round = 0;  // complex product being enqueued (recorded launches carry it)
+  auto split_operand = [&](const Operand& O, bool left) {
+    bq::SplitOperand a{};
+    a.r = O.r;
+    a.i = O.i;
+    a.w2 = O.s;
+    a.ld = O.ld;
+    const bool t = left ? pl.ta : pl.tb;
+    // One exponent per row of op(A), per column of op(B): along the stored
+    // rows for A in N and C and for B in T and H.
+    a.along = left ? !t : t;
+    a.dim = left ? m : n;
+    a.rows = a.along ? a.dim : k;
+    a.cols = a.along ? k : a.dim;
+    auto al16 = [](const double* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
+    a.vec = a.ld % 2 == 0 && al16(a.r) && al16(a.i);
+    a.kp = sl.kp;
+    a.plane = (left ? sl.rows_pad : sl.cols_pad) * sl.kp * es;
+    a.count = S;
+    a.bits = beta;
+    a.head = head;
+    return a;
+  };
+  // Digit forms: one real product T = X Y, X value xv of L (m x k), Y value yv
+  // of R (k x n); C_w op= cw * T for each (w, cw).
+  auto split_product = [&](const Operand& L, int xv, const Operand& R, int yv,
                            const std::vector<std::pair<int, double>>& outs) -> hipError_t {
     bq::SliceGemmArgs sg{};
     for (const auto& o : outs) {
@@ -745,30 +769,22 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
       ++sg.ntgt;
     }
     if (sg.ntgt == 0) return hipSuccess;
-    // The left factor takes one exponent per row of op(A): along the stored
-    // rows (row kernels) for N and C, along the stored columns (column
-    // kernels, which also transpose the digits) for T and H; the right factor
-    // the other way round.
-    bq::SplitArgs xa = pl.ta ? bq::SplitArgs{x1, x2, xw1, xw2, ldx, k, m, 0, sl.rows_pad, sl.kp,
-                                             sl.rows_pad * sl.kp, beta, head, 0}
-                             : bq::SplitArgs{x1, x2, xw1, xw2, ldx, m, k, sl.rows_pad, 0, sl.kp,
-                                             sl.rows_pad * sl.kp, beta, head, 1};
-    bq::SplitArgs ya = pl.tb ? bq::SplitArgs{y1, y2, yw1, yw2, ldy, n, k, sl.cols_pad, 0, sl.kp,
-                                             sl.cols_pad * sl.kp, beta, head, 1}
-                             : bq::SplitArgs{y1, y2, yw1, yw2, ldy, k, n, 0, sl.cols_pad, sl.kp,
-                                             sl.cols_pad * sl.kp, beta, head, 0};
-    const double elems_x = double(m) * double(k), elems_y = double(k) * double(n);
+    bq::SplitOperand x = split_operand(L, true), y = split_operand(R, false);
+    x.e[xv] = exp_a;
+    y.e[yv] = exp_b;
+    const double ex = double(m) * double(k) * 8.0 * (xv == 2 ? 2 : 1), ey = double(k) * double(n) * 8.0 * (yv == 2 ? 2 : 1);
     {
-      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, k, 0, 0.0,
-                elems_x * 8.0 * (x2 ? 2 : 1) * 2.0 + double(sl.rows_pad) * double(sl.kp) * S * es);
-      hipError_t e = bq::launch_split(pr.et, S, xa, exp_a, dig_a, s);
+      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, n, k, 0.0, ex + ey);
+      hipError_t e = bq::launch_exponents(x, y, s);
       tr.done();
       if (e != hipSuccess) return e;
     }
+    x.out[xv] = dig_a;
+    y.out[yv] = dig_b;
     {
-      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, k, n, 0, 0.0,
-                elems_y * 8.0 * (y2 ? 2 : 1) * 2.0 + double(sl.cols_pad) * double(sl.kp) * S * es);
-      hipError_t e = bq::launch_split(pr.et, S, ya, exp_b, dig_b, s);
+      Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, n, k, 0.0,
+                ex + ey + (double(m) + double(n)) * double(sl.kp) * S * es);
+      hipError_t e = bq::launch_digits(pr.et, x, y, s);
       tr.done();
       if (e != hipSuccess) return e;
     }
@@ -791,37 +807,13 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
     return e;
   };
 
-  // CRT form: one operand side of a complex product, nothing wanted yet.
-  const int64_t ldr = crt_ldr(n);
-  int round = 0;  // complex product being enqueued (recorded launches carry it)
-  auto crt_operand = [&](const Operand& O, bool left) {
-    bq::CrtOperand a{};
-    a.r = O.r;
-    a.i = O.i;
-    a.w2 = O.s;
-    a.ld = O.ld;
-    const bool t = left ? pl.ta : pl.tb;
-    // One exponent per row of op(A), per column of op(B): along the stored
-    // rows for A in N and C and for B in T and H.
-    a.along = left ? !t : t;
-    a.dim = left ? m : n;
-    a.rows = a.along ? a.dim : k;
-    a.cols = a.along ? k : a.dim;
-    auto al16 = [](const double* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-    a.vec = a.ld % 2 == 0 && al16(a.r) && al16(a.i);
-    a.kp = sl.kp;
-    a.plane = (left ? sl.rows_pad : sl.cols_pad) * sl.kp;
-    a.nmod = S;
-    a.bits = beta;
-    return a;
-  };
   // A complex product's real products (value xs[q] of X times value ys[q] of
   // Y) into residue sets 0..np-1, for crt_combine to reconstruct.  The
   // exponents of every value go into the set of the first product that has it
   // (cc points at them).
   auto crt_products = [&](const Operand& L, const Operand& R, int np, const int* xs, const int* ys,
                           bq::CrtCombineArgs* cc) -> hipError_t {
-    bq::CrtOperand x = crt_operand(L, true), y = crt_operand(R, false);
+    bq::SplitOperand x = split_operand(L, true), y = split_operand(R, false);
     int xf[3] = {-1, -1, -1}, yf[3] = {-1, -1, -1};  // first product of each value
     for (int q = 0; q < np; ++q) {
       if (xf[xs[q]] < 0) xf[xs[q]] = q;
@@ -849,14 +841,14 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
     const double ex = double(m) * double(k) * 8.0, ey = double(k) * double(n) * 8.0;
     {
       Tracer tr(h, s, BQ_KERNEL_SPLIT, -1, m, n, k, 0.0, ex * (x.i ? 2 : 1) + ey * (y.i ? 2 : 1));
-      hipError_t e = bq::launch_crt_exp(x, y, s);
+      hipError_t e = bq::launch_exponents(x, y, s);
       tr.done();
       if (e != hipSuccess) return e;
     }
     // One set of residue planes: every real product's operands in turn, an
     // operand that the product before had left as it is.
     for (int q = 0; q < np; ++q) {
-      bq::CrtOperand xq = x, yq = y;
+      bq::SplitOperand xq = x, yq = y;
       if (q == 0 || xs[q] != xs[q - 1]) xq.out[xs[q]] = dig_a;
       else xq.dim = 0;
       if (q == 0 || ys[q] != ys[q - 1]) yq.out[ys[q]] = dig_b;
@@ -985,6 +977,10 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
       } else {
         rps.push_back({L.r, nullptr, 0.0, R.r, nullptr, 0.0, 1.0, 0.0});
       }
+      // Which value of its operand side a real product takes: 0 the real part,
+      // 1 the imaginary part, 2 the Gauss sum.
+      auto value_x = [&](const RealProd& rp) { return rp.x2 ? 2 : (rp.x1 == L.r ? 0 : 1); };
+      auto value_y = [&](const RealProd& rp) { return rp.y2 ? 2 : (rp.y1 == R.r ? 0 : 1); };
       if (crt) {
         // The real products of this complex product into residue sets, then
         // one reconstruction pass: target q takes sum_p coef[q][p] T_p.
@@ -1013,11 +1009,11 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
           if (any) used.push_back((int)pi);
         }
         if (cc.ntgt == 0) continue;
-        int xs[bq::kCrtProducts], ys[bq::kCrtProducts];  // values: 0 real part, 1 imaginary part, 2 Gauss sum
+        int xs[bq::kCrtProducts], ys[bq::kCrtProducts];
         for (size_t q = 0; q < used.size(); ++q) {
           const RealProd& rp = rps[used[q]];
-          xs[q] = rp.x2 ? 2 : (rp.x1 == L.r ? 0 : 1);
-          ys[q] = rp.y2 ? 2 : (rp.y1 == R.r ? 0 : 1);
+          xs[q] = value_x(rp);
+          ys[q] = value_y(rp);
         }
         cc.np = (int)used.size();
         if (hipError_t e = crt_products(L, R, cc.np, xs, ys, &cc); e != hipSuccess)
@@ -1058,7 +1054,7 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
           outs.push_back({t.w, c.re * rp.aR - c.im * rp.aI});
           outs.push_back({t.w + 4, c.re * rp.aI + c.im * rp.aR});
         }
-        hipError_t e = split_product(rp.x1, 1.0, rp.x2, rp.xw2, L.ld, rp.y1, 1.0, rp.y2, rp.yw2, R.ld, outs);
+        hipError_t e = split_product(L, value_x(rp), R, value_y(rp), outs);
         if (e != hipSuccess) return hip_fail(e, "split-precision launch");
       }
       continue;
@@ -1460,10 +1456,10 @@ void crt_tables(const CrtRecord& rec, std::vector<char>* bytes, std::vector<CrtL
     std::vector<CrtRecord::Split> sp;
     for (const auto& x : rec.splits)
       if (x.round == r) sp.push_back(x);
-    std::vector<bq::CrtOperand> ops;
+    std::vector<bq::SplitOperand> ops;
     for (const auto& x : sp) ops.push_back(x.it);
-    add(CrtLaunch::EXP, 0, ops, [](const bq::CrtOperand& a) { return bq::crt_exp_blocks(a); });
-    add(CrtLaunch::SPLIT, 0, ops, [](const bq::CrtOperand& a) { return bq::crt_split_blocks(a); });
+    add(CrtLaunch::EXP, 0, ops, [](const bq::SplitOperand& a) { return bq::exponent_blocks(a); });
+    add(CrtLaunch::SPLIT, 0, ops, [](const bq::SplitOperand& a) { return bq::split_blocks(a); });
     std::vector<bq::CrtGemmItem> gm;
     for (const auto& x : rec.gemms)
       if (x.round == r) gm.push_back(x.it);
@@ -1490,10 +1486,10 @@ hipError_t crt_launch(const CrtLaunch& L, const char* d, hipStream_t s) {
       return bq::launch_grouped_combine(reinterpret_cast<const bq::CombineArgs*>(d + L.items), prefix, L.count,
                                         L.blocks, s);
     case CrtLaunch::EXP:
-      return bq::launch_crt_exp_grouped(reinterpret_cast<const bq::CrtOperand*>(d + L.items), prefix, L.count,
+      return bq::launch_exponents_grouped(reinterpret_cast<const bq::SplitOperand*>(d + L.items), prefix, L.count,
                                         L.blocks, s);
     case CrtLaunch::SPLIT:
-      return bq::launch_crt_split_grouped(reinterpret_cast<const bq::CrtOperand*>(d + L.items), prefix, L.count,
+      return bq::launch_crt_split_grouped(reinterpret_cast<const bq::SplitOperand*>(d + L.items), prefix, L.count,
                                           L.blocks, s);
     case CrtLaunch::GEMM:
       return bq::launch_crt_gemm_grouped(reinterpret_cast<const bq::CrtGemmItem*>(d + L.items), prefix, L.count,

@@ -89,24 +89,27 @@ struct CombineArgs {
   int64_t rows, cols;
 };
 
-// One real FP64 operand to be split into low-precision digit slices:
-// value = w1 * s1 + w2 * s2 (s2 may be null), row-major with leading
-// dimension ld.  left: the operand is the left factor (m x k, one exponent
-// per row, digits D[s][row][kk]); otherwise the right factor (k x n, one
-// exponent per column, digits stored transposed, D[s][col][kk]).
-struct SplitArgs {
-  const double* s1;
-  const double* s2;
-  double w1, w2;
-  int64_t ld;
-  int64_t rows, cols;          // source shape
-  int64_t rows_pad, cols_pad;  // left: rows padded to 128; right: cols padded to 64
-  int64_t kp;                  // reduced dimension padded to 64 (zero digits)
-  int64_t slice_stride;        // elements between consecutive slices
-  int beta;                    // digit width in bits
-  int head;                    // exponent headroom: row/column exponent = frexp exponent + head
-  int left;
+// One operand side of a complex product in a split form: its values 0: r, 1: i,
+// 2: r + w2 i (the Gauss sum), those wanted with their exponents (one per row
+// of the left factor, per column of the right one) and residue or digit planes.
+struct SplitOperand {
+  const double* r;
+  const double* i;  // null when only r is wanted
+  double w2;
+  int64_t ld, rows, cols;  // as stored
+  int64_t dim;             // exponents: the stored rows (along = 1) or columns
+  int along;               // 1: the inner dimension is contiguous
+  int vec;                 // 1: rows are 16-byte aligned
+  int64_t kp, plane;       // padded inner dimension (elements); bytes between planes
+  int count, bits;         // planes (moduli or slices); integer or digit bits
+  int head;                // added to every exponent (digit forms' headroom)
+  int* e[3];     // null: exponent not wanted
+  void* out[3];  // null: residues not wanted
 };
+inline int64_t exponent_blocks(const SplitOperand& a) { return (a.dim + 15) / 16; }
+// Tiles of the rows (columns) an operand has; the padding tiles only feed
+// GEMM results that are never stored.
+inline int64_t split_blocks(const SplitOperand& a) { return ((a.dim + 63) / 64) * (a.kp / 64); }
 
 constexpr int kMaxSliceTargets = 8;
 
@@ -232,9 +235,7 @@ hipError_t launch_grouped_combine(const CombineArgs* args, const int64_t* row_pr
 // Split-precision kernels (bq_split.hip, bq_split_f8.hip).  et: 0 = BF16
 // digits (beta 7), 1 = OCP FP8 E4M3 digits (beta 5, headroom 1), 2 = INT8
 // digits (beta 7, headroom 1).
-hipError_t launch_split(int et, int S, const SplitArgs& a, int* exps, void* out, hipStream_t s);
-// Row (a.left) or column exponents of a split operand into exps.
-hipError_t launch_split_exponents(const SplitArgs& a, int* exps, hipStream_t s);
+hipError_t launch_digits(int et, const SplitOperand& x, const SplitOperand& y, hipStream_t s);
 hipError_t launch_slice_gemm(int et, int S, const SliceGemmArgs& g, hipStream_t s);
 // FP8 digits (bq_split_f8.hip): beta 5, headroom 1, 1..13 slices.
 hipError_t launch_slice_gemm_f8(int S, const SliceGemmArgs& g, hipStream_t s);
@@ -246,29 +247,9 @@ int slice_kstep(int et);              // k per MFMA step (32 or 64)
 int slice_beta(int et);
 int slice_head(int et);
 int slice_flush_steps(int et, int S);  // k-steps per exact level accumulation
-// One operand side of a complex product in the CRT form: its values 0: r, 1: i,
-// 2: r + w2 i (the Gauss sum), those wanted with their exponents (one per row
-// of the left factor, per column of the right one) and residue planes.
-struct CrtOperand {
-  const double* r;
-  const double* i;  // null when only r is wanted
-  double w2;
-  int64_t ld, rows, cols;  // as stored
-  int64_t dim;             // exponents: the stored rows (along = 1) or columns
-  int along;               // 1: the inner dimension is contiguous
-  int vec;                 // 1: rows are 16-byte aligned
-  int64_t kp, plane;       // inner dimension padded to 128; bytes between modulus planes
-  int nmod, bits;
-  int* e[3];     // null: exponent not wanted
-  void* out[3];  // null: residues not wanted
-};
-inline int64_t crt_exp_blocks(const CrtOperand& a) { return (a.dim + 15) / 16; }
-// Tiles of the rows (columns) an operand has; the padding tiles only feed
-// GEMM results that are never stored.
-inline int64_t crt_split_blocks(const CrtOperand& a) { return ((a.dim + 63) / 64) * (a.kp / 64); }
-// Exponents, then residues, of the wanted values of both operands.
-hipError_t launch_crt_exp(const CrtOperand& x, const CrtOperand& y, hipStream_t s);
-hipError_t launch_crt_split(const CrtOperand& x, const CrtOperand& y, hipStream_t s);
+// Exponents (bq_split.hip), then residues, of the wanted values of both operands.
+hipError_t launch_exponents(const SplitOperand& x, const SplitOperand& y, hipStream_t s);
+hipError_t launch_crt_split(const SplitOperand& x, const SplitOperand& y, hipStream_t s);
 hipError_t launch_crt_gemm(int N, const CrtGemmArgs& g, hipStream_t s);
 hipError_t launch_crt_combine(int N, const CrtCombineArgs& g, hipStream_t s);
 int crt_modulus(int i);
@@ -276,8 +257,8 @@ int crt_modulus(int i);
 // Grouped CRT launches (batched plans): every launch covers a list of items
 // of many problems; item i owns blocks [prefix[i], prefix[i + 1]) of a 1-D
 // grid, and a block finds its item by binary search in prefix.
-//   exponents: one operand side of a complex product per item, crt_exp_blocks;
-//   residues:  the same items, crt_split_blocks;
+//   exponents: one operand side of a complex product per item, exponent_blocks;
+//   residues:  the same items, split_blocks;
 //   GEMM:      one real product per item, 128 x 128 tiles x moduli;
 //   combine:   one complex product per item (all items one N).
 struct CrtGemmItem {
@@ -288,9 +269,9 @@ inline int64_t crt_gemm_blocks(const CrtGemmItem& it) {
   return ((it.g.m + 127) / 128) * ((it.g.n + 127) / 128) * it.nmod;
 }
 int64_t crt_combine_blocks(const CrtCombineArgs& c);
-hipError_t launch_crt_exp_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
+hipError_t launch_exponents_grouped(const SplitOperand* items, const int64_t* prefix, int count, int64_t blocks,
                                   hipStream_t s);
-hipError_t launch_crt_split_grouped(const CrtOperand* items, const int64_t* prefix, int count, int64_t blocks,
+hipError_t launch_crt_split_grouped(const SplitOperand* items, const int64_t* prefix, int count, int64_t blocks,
                                     hipStream_t s);
 hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t blocks,
                                    hipStream_t s);

@@ -28,164 +28,218 @@
 
 namespace bq {
 
-// Exponents: e[r] = max over the reduced dimension of frexp exponents
-// (rows of the left operand, columns of the right one).  exps must hold
-// INT_MIN beforehand.  Block: 256 threads.
-__global__ void __launch_bounds__(256) split_exp_left(const SplitArgs a, int* exps) {
-  // grid.x = rows, grid.y = chunks of 2048 columns
-  const int64_t r = blockIdx.x;
-  const int64_t c0 = (int64_t)blockIdx.y * 2048;
-  int e = INT_MIN;
-  for (int j = threadIdx.x; j < 2048; j += 256) {
-    const int64_t c = c0 + j;
-    if (c < a.cols) e = max(e, exp_of(operand_value(a, r * a.ld + c)));
+// Largest magnitude of a set of doubles, kept as the high words of |x| and
+// the low words (which count only where every high word is zero): three
+// integer operations an element, and exact exponents down to denormals.
+struct MaxMagnitude {
+  unsigned hi = 0, lo = 0;
+  __device__ __forceinline__ void add(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    hi = max(hi, (unsigned)(u >> 32) & 0x7fffffffu);
+    lo = max(lo, (unsigned)u);
   }
-  if (!exp_special(e)) e += a.head;
-  for (int o = 32; o > 0; o >>= 1) e = max(e, __shfl_xor(e, o));
-  __shared__ int red[4];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    e = max(max(red[0], red[1]), max(red[2], red[3]));
-    if (e != INT_MIN) atomicMax(&exps[r], e);
+  __device__ __forceinline__ void merge(unsigned h, unsigned l) {
+    hi = max(hi, h);
+    lo = max(lo, l);
   }
-}
-
-__global__ void __launch_bounds__(256) split_exp_right(const SplitArgs a, int* exps, int64_t chunk) {
-  // grid.x = column blocks of 64, grid.y = row chunks of `chunk` rows;
-  // thread: one column, every 4th row of the chunk.
-  const int64_t c = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-  const int64_t r0 = (int64_t)blockIdx.y * chunk + (threadIdx.x >> 6);
-  int e = INT_MIN;
-  if (c < a.cols)
-    for (int64_t r = r0; r < a.rows && r < (int64_t)(blockIdx.y + 1) * chunk; r += 4)
-      e = max(e, exp_of(operand_value(a, r * a.ld + c)));
-  __shared__ int red[256];
-  red[threadIdx.x] = e;
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    e = max(max(red[threadIdx.x], red[threadIdx.x + 64]), max(red[threadIdx.x + 128], red[threadIdx.x + 192]));
-    if (c < a.cols && e != INT_MIN) atomicMax(&exps[c], exp_special(e) ? e : e + a.head);
+  // The frexp exponent plus head, or one of the markers.
+  __device__ __forceinline__ int exponent(int head) const {
+    if (hi >= 0x7ff00000u) return kExpNonFinite;
+    if (hi >= 0x00100000u) return (int)(hi >> 20) - 1022 + head;
+    if (hi != 0) return 32 - 1073 + 31 - __builtin_clz(hi) + head;
+    return lo != 0 ? 31 - __builtin_clz(lo) - 1073 + head : INT_MIN;
   }
-}
+};
 
-__global__ void __launch_bounds__(256) fill_int(int* p, int64_t n, int v) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-// Digits of one element: q[0..S-1] from x and its row/column exponent.
-template <int S>
-__device__ __forceinline__ void digits(double x, int e, int beta, float* q) {
-  double y = exp_special(e) ? 0.0 : ldexp(x, -e);
+// Exponents of 16 rows or columns of the wanted values of an operand, 1024
+// threads: where the inner dimension is contiguous a wave per row, else 16
+// columns (128 bytes of a stored row) by 64 row lanes.  Indices past the end
+// are clamped to the last one (a repeated element leaves the maximum), so the
+// loads of four steps are in flight together.  One launch per complex product
+// reads r and i once for three exponents; no initialisation and no atomics.
+constexpr int kExpThreads = 1024;
+struct ExpLds {
+  unsigned hi[3][16][16], lo[3][16][16];  // value, wave, column
+};
+__device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b, ExpLds& red) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t K = a.along ? a.cols : a.rows;
+  const bool want_i = a.e[1] != nullptr || a.e[2] != nullptr;
+  MaxMagnitude mx[3];
+  auto add = [&](double r, double i) {
+    if (a.e[0]) mx[0].add(r);
+    if (a.e[1]) mx[1].add(i);
+    if (a.e[2]) mx[2].add(__builtin_fma(a.w2, i, r));
+  };
+  if (a.along) {
+    const int64_t v = min(b * 16 + wave, a.dim - 1);
+    const double* pr = a.r + v * a.ld;
+    const double* pi = want_i ? a.i + v * a.ld : pr;
+    if (a.vec && (K & 1) == 0) {
+      for (int64_t c = 2 * lane; c < K + 2 * lane; c += 512) {
+        double2 x[4], y[4];
 #pragma unroll
-  for (int s = 1; s <= S; ++s) {
-    const double d = rint(ldexp(y, beta * s));
-    q[s - 1] = (float)d;
-    y = y - ldexp(d, -beta * s);
-  }
-}
-
-// Small integer (|q| <= 256) to BF16 bits: exact truncation of the FP32 bits.
-__device__ __forceinline__ unsigned short to_bf16(float q) {
-  return (unsigned short)(__float_as_uint(q) >> 16);
-}
-
-// INT8 digits (beta 7, one bit of headroom) are stored as two's-complement
-// bytes (|q| <= 64).
-// Small integer (|q| <= 16) to OCP FP8 E4M3 bits.
-__device__ __forceinline__ unsigned char to_e4m3(float qf) {
-  int q = (int)qf;
-  const unsigned char s = q < 0 ? 0x80 : 0;
-  q = q < 0 ? -q : q;
-  if (q == 0) return 0;
-  const int E = 31 - __clz(q);
-  const int mant = ((q << 3) >> E) & 7;
-  return (unsigned char)(s | ((E + 7) << 3) | mant);
-}
-
-// Left operand: digits D[s][r][kk] (kk < kp, rows < rows_pad; zero padding).
-// Thread: 8 consecutive kk of one row.  grid.x = rows_pad, grid.y = kp / 2048.
-template <int ET, int S>
-__global__ void __launch_bounds__(256) split_digits_left(const SplitArgs a, const int* exps, void* out) {
-  const int64_t r = blockIdx.x;
-  const int64_t kk0 = (int64_t)blockIdx.y * 2048 + threadIdx.x * 8;
-  if (kk0 >= a.kp) return;
-  const int e = (r < a.rows) ? exps[r] : INT_MIN;
-  float q[8][S];
+        for (int u = 0; u < 4; ++u) {
+          const int64_t q = min(c + 128 * u, K - 2);
+          x[u] = *reinterpret_cast<const double2*>(pr + q);
+          y[u] = want_i ? *reinterpret_cast<const double2*>(pi + q) : x[u];
+        }
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int64_t c = kk0 + t;
-    const double x = (r < a.rows && c < a.cols) ? operand_value(a, r * a.ld + c) : 0.0;
-    digits<S>(x, e, a.beta, q[t]);
-  }
-  constexpr int ES = ET == 0 ? 2 : 1;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const int64_t o = (int64_t)s * a.slice_stride * ES + digit_offset(r, kk0 * ES, a.kp * ES);
-    if constexpr (ET == 0) {
-      i4v v;
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        v[t] = (int)to_bf16(q[2 * t][s]) | ((int)to_bf16(q[2 * t + 1][s]) << 16);
-      *reinterpret_cast<i4v*>(static_cast<unsigned char*>(out) + o) = v;
-    } else if constexpr (ET == 2) {
-      i2v v;
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-        v[t] = (int)(unsigned char)(signed char)q[4 * t][s] | ((int)(unsigned char)(signed char)q[4 * t + 1][s] << 8) |
-               ((int)(unsigned char)(signed char)q[4 * t + 2][s] << 16) |
-               ((int)(unsigned char)(signed char)q[4 * t + 3][s] << 24);
-      *reinterpret_cast<i2v*>(static_cast<unsigned char*>(out) + o) = v;
+        for (int u = 0; u < 4; ++u) {
+          add(x[u].x, y[u].x);
+          add(x[u].y, y[u].y);
+        }
+      }
     } else {
-      i2v v;
+      for (int64_t c = lane; c < K + lane; c += 256) {
+        double x[4], y[4];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        v[t] = (int)to_e4m3(q[4 * t][s]) | ((int)to_e4m3(q[4 * t + 1][s]) << 8) |
-               ((int)to_e4m3(q[4 * t + 2][s]) << 16) | ((int)to_e4m3(q[4 * t + 3][s]) << 24);
-      *reinterpret_cast<i2v*>(static_cast<unsigned char*>(out) + o) = v;
+        for (int u = 0; u < 4; ++u) {
+          const int64_t q = min(c + 64 * u, K - 1);
+          x[u] = pr[q];
+          y[u] = want_i ? pi[q] : x[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) add(x[u], y[u]);
+      }
+    }
+  } else {
+    const int64_t v = min(b * 16 + (t & 15), a.dim - 1);
+    const int rl = t >> 4;
+    for (int64_t c = rl; c < K + rl; c += 256) {
+      double x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t q = min(c + 64 * u, K - 1) * a.ld + v;
+        x[u] = a.r[q];
+        y[u] = want_i ? a.i[q] : x[u];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) add(x[u], y[u]);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    if (!a.e[s]) continue;
+    for (int o = 32; o >= (a.along ? 1 : 16); o >>= 1)
+      mx[s].merge(__shfl_xor(mx[s].hi, o), __shfl_xor(mx[s].lo, o));
+    if (a.along) {
+      const int64_t v = b * 16 + wave;
+      if (lane == 0 && v < a.dim) a.e[s][v] = mx[s].exponent(a.head);
+    } else if (lane < 16) {
+      red.hi[s][wave][lane] = mx[s].hi;
+      red.lo[s][wave][lane] = mx[s].lo;
+    }
+  }
+  if (!a.along) {
+    __syncthreads();
+    const int c = t & 15;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      if (t >> 4 != s || !a.e[s] || b * 16 + c >= a.dim) continue;
+      MaxMagnitude m;
+      for (int w = 0; w < 16; ++w) m.merge(red.hi[s][w][c], red.lo[s][w][c]);
+      a.e[s][b * 16 + c] = m.exponent(a.head);
     }
   }
 }
 
-// Right operand (k x n, row-major): digits stored transposed, D[s][c][kk].
-// Block: a 64 (kk) x 64 (c) tile through LDS.  grid.x = cols_pad / 64,
-// grid.y = kp / 64.
-template <int ET, int S>
-__global__ void __launch_bounds__(256) split_digits_right(const SplitArgs a, const int* exps, void* out) {
-  constexpr int ES = ET == 0 ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) unsigned char tile[S][64][64 * ES + 16];
-  const int64_t c0 = (int64_t)blockIdx.x * 64;
-  const int64_t k0 = (int64_t)blockIdx.y * 64;
-  const int tc = threadIdx.x & 63;
-  const int64_t c = c0 + tc;
-  const int e = (c < a.cols) ? exps[c] : INT_MIN;
-  for (int rr = threadIdx.x >> 6; rr < 64; rr += 4) {
-    const int64_t kk = k0 + rr;
-    const double x = (c < a.cols && kk < a.rows) ? operand_value(a, kk * a.ld + c) : 0.0;
-    float q[S];
-    digits<S>(x, e, a.beta, q);
+// Both operands of a product in one launch: the blocks of x, then those of y.
+__global__ void __launch_bounds__(kExpThreads) operand_exponents(const SplitOperand x, const SplitOperand y, int64_t xblocks) {
+  __shared__ ExpLds red;
+  const int64_t b = blockIdx.x;
+  if (b < xblocks) exponent_block(x, b, red);
+  else exponent_block(y, b - xblocks, red);
+}
+
+// The same over the items of many problems.
+__global__ void __launch_bounds__(kExpThreads) operand_exponents_grouped(const SplitOperand* items, const int64_t* prefix,
+                                                                int count) {
+  __shared__ ExpLds red;
+  const int64_t b = blockIdx.x;
+  const int i = find_item(prefix, count, b);
+  const SplitOperand a = items[i];
+  exponent_block(a, b - prefix[i], red);
+}
+
+// Digits of one 64 x 64 tile (64 rows of the left factor, or columns of the
+// right one, by 64 of the inner dimension) of the wanted value of an operand,
+// in the tiled 64-byte layout.  Thread: 16 consecutive inner elements of one
+// row or column (one 16-byte chunk of each plane, two for BF16).  With z = x
+// 2^(b - e), a digit is rint(z), read off the low bits of z + 1.5 2^52, and
+// the next z is the remainder times 2^b: four full-rate FP64 instructions a
+// digit, all exact.  The slices run in a loop.  Exponents and digits of all
+// operands of a product, n = 2048: INT8 (8 slices) 1.62 ms against 1.96 with
+// three launches per operand, an atomic pass and ldexp per digit, FP8 (12) 1.81
+// against 3.35; n = 256, launch-bound, 0.35 against 0.81.
+template <int ET>
+__device__ __forceinline__ void digits_block(const SplitOperand& a, int64_t b) {
+  constexpr double kMagic = 6755399441055744.0;  // 1.5 2^52
+  const int64_t nkt = a.kp / 64;
+  const int64_t rt = b / nkt, kt = b % nkt;
+  const int t = threadIdx.x;
+  const int64_t v = rt * 64 + (a.along ? t >> 2 : t & 63);
+  const int64_t k0 = kt * 64 + (a.along ? t & 3 : t >> 6) * 16;
+  const int64_t K = a.along ? a.cols : a.rows;
+  const bool in = v < a.dim;
+  const int s = a.out[0] ? 0 : (a.out[1] ? 1 : 2);  // the value wanted
+  double z[16];
+  load_inner16(a, s == 1 ? a.i : a.r, v, k0, K, in, z);
+  if (s == 2) {
+    double im[16];
+    load_inner16(a, a.i, v, k0, K, in, im);
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      if constexpr (ET == 0)
-        *reinterpret_cast<unsigned short*>(&tile[s][tc][rr * 2]) = to_bf16(q[s]);
-      else if constexpr (ET == 2)
-        tile[s][tc][rr] = (unsigned char)(signed char)q[s];
-      else
-        tile[s][tc][rr] = to_e4m3(q[s]);
+    for (int j = 0; j < 16; ++j) z[j] = __builtin_fma(a.w2, im[j], z[j]);
+  }
+  const int e = in ? a.e[s][v] : INT_MIN;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) z[j] = exp_special(e) ? 0.0 : ldexp(z[j], a.bits - e);
+  const double step = (double)(1 << a.bits);
+  constexpr int ES = ET == 0 ? 2 : 1;
+  unsigned char* out = static_cast<unsigned char*>(a.out[s]);
+  const int64_t o0 = digit_offset(v, k0 * ES, a.kp * ES);
+  const int64_t o1 = ET == 0 ? digit_offset(v, k0 * ES + 16, a.kp * ES) : 0;
+  for (int i = 0; i < a.count; ++i) {
+    int d[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const double m = z[j] + kMagic;
+      d[j] = (int)(uint32_t)__builtin_bit_cast(uint64_t, m);
+      z[j] = (z[j] - (m - kMagic)) * step;
     }
+    i4v q;
+    if constexpr (ET == 2) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) q[g] = pack_bytes(d[4 * g], d[4 * g + 1], d[4 * g + 2], d[4 * g + 3]);
+      *reinterpret_cast<i4v*>(out + o0) = q;
+    } else if constexpr (ET == 1) {
+      // |digit| <= 16: exact in E4M3.
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        int w = __builtin_amdgcn_cvt_pk_fp8_f32((float)d[4 * g], (float)d[4 * g + 1], 0, false);
+        q[g] = __builtin_amdgcn_cvt_pk_fp8_f32((float)d[4 * g + 2], (float)d[4 * g + 3], w, true);
+      }
+      *reinterpret_cast<i4v*>(out + o0) = q;
+    } else {
+      // |digit| <= 128: exact in BF16, the upper half of the FP32 number.
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          q[g] = (int)__builtin_amdgcn_perm(__float_as_uint((float)d[8 * h + 2 * g + 1]),
+                                            __float_as_uint((float)d[8 * h + 2 * g]), 0x07060302u);
+        *reinterpret_cast<i4v*>(out + (h ? o1 : o0)) = q;
+      }
+    }
+    out += a.plane;
   }
-  __syncthreads();
-  // Write: row c of slice s gets 64 * ES contiguous bytes; 16-byte pieces.
-  constexpr int PIECES = 64 * ES / 16;  // 8 (bf16) or 4 (fp8)
-  for (int w = threadIdx.x; w < S * 64 * PIECES; w += 256) {
-    const int s = w / (64 * PIECES);
-    const int rem = w % (64 * PIECES);
-    const int cc = rem / PIECES, p = rem % PIECES;
-    const i4v v = *reinterpret_cast<const i4v*>(&tile[s][cc][p * 16]);
-    const int64_t o = digit_offset(c0 + cc, k0 * ES + p * 16, a.kp * ES);
-    *reinterpret_cast<i4v*>(static_cast<unsigned char*>(out) + (int64_t)s * a.slice_stride * ES + o) = v;
-  }
+}
+
+template <int ET>
+__global__ void __launch_bounds__(256) split_digits(const SplitOperand x, const SplitOperand y, int64_t xblocks) {
+  const int64_t b = blockIdx.x;
+  if (b < xblocks) digits_block<ET>(x, b);
+  else digits_block<ET>(y, b - xblocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -385,34 +439,30 @@ slice_gemm_dma(const SliceGemmArgs g) {
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_split_exponents(const SplitArgs& a, int* exps, hipStream_t st) {
-  const int64_t nexp = a.left ? a.rows_pad : a.cols_pad;
-  hipLaunchKernelGGL(fill_int, dim3((unsigned)((nexp + 255) / 256)), dim3(256), 0, st, exps, nexp, INT_MIN);
-  if (a.left)
-    hipLaunchKernelGGL(split_exp_left, dim3((unsigned)a.rows, (unsigned)((a.cols + 2047) / 2048)), dim3(256), 0,
-                       st, a, exps);
-  else {
-    // Row chunks of up to 1024 rows, shorter where the columns alone give
-    // a small grid (about 2048 blocks, chunks of at least 64 rows).
-    const int64_t cb = (a.cols + 63) / 64;
-    const int64_t want = std::min((a.rows + 63) / 64, (2048 + cb - 1) / cb);
-    const int64_t chunks = std::max((a.rows + 1023) / 1024, std::max<int64_t>(want, 1));
-    const int64_t chunk = ((a.rows + chunks - 1) / chunks + 3) / 4 * 4;
-    hipLaunchKernelGGL(split_exp_right, dim3((unsigned)cb, (unsigned)((a.rows + chunk - 1) / chunk)), dim3(256), 0,
-                       st, a, exps, chunk);
-  }
+hipError_t launch_exponents(const SplitOperand& x, const SplitOperand& y, hipStream_t st) {
+  const int64_t xb = exponent_blocks(x), blocks = xb + exponent_blocks(y);
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(operand_exponents, dim3((unsigned)blocks), dim3(kExpThreads), 0, st, x, y, xb);
   return hipGetLastError();
 }
 
-template <int ET, int S>
-static hipError_t launch_split_s(const SplitArgs& a, int* exps, void* out, hipStream_t st) {
-  if (hipError_t e = launch_split_exponents(a, exps, st); e != hipSuccess) return e;
-  if (a.left)
-    hipLaunchKernelGGL((split_digits_left<ET, S>), dim3((unsigned)a.rows_pad, (unsigned)((a.kp + 2047) / 2048)),
-                       dim3(256), 0, st, a, exps, out);
-  else
-    hipLaunchKernelGGL((split_digits_right<ET, S>), dim3((unsigned)(a.cols_pad / 64), (unsigned)(a.kp / 64)),
-                       dim3(256), 0, st, a, exps, out);
+hipError_t launch_exponents_grouped(const SplitOperand* items, const int64_t* prefix, int count, int64_t blocks,
+                                  hipStream_t st) {
+  if (count <= 0 || blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(operand_exponents_grouped, dim3((unsigned)blocks), dim3(kExpThreads), 0, st, items, prefix, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_digits(int et, const SplitOperand& x, const SplitOperand& y, hipStream_t st) {
+  const int64_t xb = split_blocks(x), blocks = xb + split_blocks(y);
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(256);
+  if (et == 0) hipLaunchKernelGGL(split_digits<0>, grid, block, 0, st, x, y, xb);
+  else if (et == 1) hipLaunchKernelGGL(split_digits<1>, grid, block, 0, st, x, y, xb);
+  else hipLaunchKernelGGL(split_digits<2>, grid, block, 0, st, x, y, xb);
   return hipGetLastError();
 }
 
@@ -453,19 +503,6 @@ int slice_flush_steps(int et, int S) {
 
 #define BQ_SPLIT_CASES(ET, X) \
   X(ET, 1) X(ET, 2) X(ET, 3) X(ET, 4) X(ET, 5) X(ET, 6) X(ET, 7) X(ET, 8)
-#define BQ_SPLIT_CASES_MORE(X) \
-  X(1, 9) X(1, 10) X(1, 11) X(1, 12) X(1, 13) X(2, 9)
-
-hipError_t launch_split(int et, int S, const SplitArgs& a, int* exps, void* out, hipStream_t st) {
-#define X(E, SS) \
-  if (et == E && S == SS) return launch_split_s<E, SS>(a, exps, out, st);
-  BQ_SPLIT_CASES(0, X)
-  BQ_SPLIT_CASES(1, X)
-  BQ_SPLIT_CASES(2, X)
-  BQ_SPLIT_CASES_MORE(X)
-#undef X
-  return hipErrorInvalidValue;
-}
 
 hipError_t launch_slice_gemm(int et, int S, const SliceGemmArgs& g, hipStream_t st) {
   if (et == 1) return launch_slice_gemm_f8(S, g, st);

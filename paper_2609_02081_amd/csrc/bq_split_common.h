@@ -16,13 +16,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef int i2v __attribute__((ext_vector_type(2)));
 
-// Value of the split operand: w1 * s1 + w2 * s2 (s2 may be absent).  The
-// FP64 path forms its Gauss sums with the same single rounding.
-__device__ __forceinline__ double operand_value(const SplitArgs& a, int64_t off) {
-  const double x = a.s1[off];
-  return a.s2 ? __builtin_fma(a.w2, a.s2[off], a.w1 * x) : a.w1 * x;
-}
-
 // Row / column exponent markers: INT_MIN for an all-zero row or column (its
 // digits are zero and so is its part of the product), kExpNonFinite for one
 // holding a NaN or an infinity (it wins every max; its digits are zero and
@@ -30,13 +23,6 @@ __device__ __forceinline__ double operand_value(const SplitArgs& a, int64_t off)
 constexpr int kExpNonFinite = INT_MAX;
 
 __device__ __forceinline__ bool exp_special(int e) { return e == INT_MIN || e == kExpNonFinite; }
-
-__device__ __forceinline__ int exp_of(double x) {
-  if (!__builtin_isfinite(x)) return kExpNonFinite;
-  int e;
-  (void)frexp(x, &e);
-  return x == 0.0 ? INT_MIN : e;
-}
 
 // Scale of a product element with row exponent ea and column exponent eb.
 __device__ __forceinline__ double exp_scaled(double v, int ea, int eb, int shift) {
@@ -73,6 +59,53 @@ __device__ __forceinline__ int64_t digit_offset(int64_t r, int64_t byte_in_row, 
   return ((r >> 6) * nk + kt) * (64 * RB) + rr * RB + swz_chunk<16>(rr, b >> 4) * 16 + (b & 15);
 }
 
+// 16 consecutive inner elements from k0 of row or column v of a block (of a
+// SplitOperand; K: the inner dimension, in: v exists), zeros past the end.
+__device__ __forceinline__ void load_inner16(const SplitOperand& a, const double* p, int64_t v, int64_t k0, int64_t K,
+                                             bool in, double (&x)[16]) {
+  if (a.along) {
+    const double* q = p + v * a.ld + k0;
+    if (a.vec && in && k0 + 16 <= K) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const double2 d = *reinterpret_cast<const double2*>(q + 2 * j);
+        x[2 * j] = d.x;
+        x[2 * j + 1] = d.y;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = in && k0 + j < K ? q[j] : 0.0;
+    }
+  } else {
+    const double* q = p + k0 * a.ld + v;
+    if (in && k0 + 16 <= K) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = q[j * a.ld];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = in && k0 + j < K ? q[j * a.ld] : 0.0;
+    }
+  }
+}
+
+// Low bytes of four words, packed.
+__device__ __forceinline__ int pack_bytes(int a, int b, int c, int d) {
+  const unsigned ab = __builtin_amdgcn_perm((unsigned)b, (unsigned)a, 0x0c0c0400u);
+  const unsigned cd = __builtin_amdgcn_perm((unsigned)d, (unsigned)c, 0x04000c0cu);
+  return (int)(ab | cd);
+}
+
+// Last item whose first block is at or before block b.
+__device__ __forceinline__ int find_item(const int64_t* prefix, int count, int64_t b) {
+  int lo = 0, hi = count - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (prefix[mid] <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Blocks are dealt to the 8 XCDs in turn (b % 8).  Position of block b among
 // the blocks [p0, p1) of a launch when each XCD takes a contiguous run of
 // positions.
@@ -106,6 +139,8 @@ __device__ __forceinline__ void slice_tile_coords(int tiles_m, int tiles_n, int&
 // real product of the Hadamard part adds into up to eight blocks).
 template <int NE>
 __device__ __forceinline__ void store_targets(const SliceGemmArgs& g, const double (&t)[NE], const int64_t (&off)[NE]) {
+  // coef * T is rounded before it is added (it is exact but for denormals).
+#pragma clang fp contract(off)
   for (int q = 0; q < g.ntgt; ++q) {
     double* c = g.c[q];
     const double w = g.coef[q];
@@ -115,7 +150,7 @@ __device__ __forceinline__ void store_targets(const SliceGemmArgs& g, const doub
       for (int e = 0; e < NE; ++e) old[e] = off[e] >= 0 ? c[off[e]] : 0.0;
 #pragma unroll
       for (int e = 0; e < NE; ++e)
-        if (off[e] >= 0) c[off[e]] = __builtin_fma(w, t[e], old[e]);
+        if (off[e] >= 0) c[off[e]] = w * t[e] + old[e];
     } else {
 #pragma unroll
       for (int e = 0; e < NE; ++e)

@@ -199,3 +199,18 @@ def test_n16384_default_slices_sampled(bq, kind, dist):
     err = oracle.rel_frobenius(Cs, oracle.gemm(As, Bs))
     print(f"split n=16384 {kind} {dist}: default slices, sampled rel err {err:.3e}", flush=True)
     assert err <= TOL
+
+
+@pytest.mark.parametrize("kind", ["int8", "bf16", "fp8"])
+@pytest.mark.parametrize("m,k,n", [(1, 1, 1), (16, 17, 15), (65, 64, 63), (64, 129, 66)])
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("H", "T")])
+def test_split_tiles_and_edges(bq, kind, m, k, n, opA, opB):
+    """Exponents come from groups of 16 rows or columns and digits from 64 x
+    64 tiles, contiguous or strided in the inner dimension: sizes on and
+    beside each edge, even and odd rows.  Small integers are exact in six
+    slices of any digit type, so the product equals the oracle's."""
+    rng = np.random.default_rng(m + k + n)
+    A = inputs.blocks(rng, *((k, m) if opA in "TH" else (m, k)), "int", bound=100)
+    B = inputs.blocks(rng, *((n, k) if opB in "TH" else (k, n)), "int", bound=100)
+    print(f"split edges {kind} {m}x{k}x{n} {opA}{opB}", flush=True)
+    assert np.array_equal(run(bq, A, B, kind, 6, opA=opA, opB=opB), oracle.gemm(OP_FN[opA](A), OP_FN[opB](B)))
