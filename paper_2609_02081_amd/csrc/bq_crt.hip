@@ -51,13 +51,19 @@ constexpr CrtModuli make_crt_weights() {
 }
 __constant__ constexpr CrtModuli kCrtW = make_crt_weights();
 
-// Symmetric residue of t (|t| < 2^31) modulo an odd p, in [-(p-1)/2, (p-1)/2]:
-// q = rint(t / p) in FP64 is exact (t / p
-// is never within 1 / (2 p) of a half-integer for odd p, far above the
-// rounding error), and t - q p is formed exactly by one fma.
+// Symmetric residue of t (|t| < 2^31) modulo an odd p, in [-(p-1)/2, (p-1)/2],
+// in the low byte of the result: q = rint(t / p) in FP64 is exact (t / p is
+// never within 1 / (2 p) of a half-integer for odd p, far above the rounding
+// error), and t - q p is formed exactly by one fma.  t enters FP64 through the
+// low word of 2^52 + 2^31 + t and the integers leave it through the low word
+// of a sum with 1.5 2^52: six full-rate instructions, no conversions.
 __device__ __forceinline__ int sym_mod_rt(int t, double p, double inv_p) {
-  const double td = (double)t;
-  return (int)__builtin_fma(-rint(td * inv_p), p, td);
+  constexpr double kMagic = 6755399441055744.0;     // 1.5 2^52
+  constexpr double kOffset = 4503601774854144.0;    // 2^52 + 2^31
+  const uint64_t u = 0x4330000000000000ull | ((uint32_t)t ^ 0x80000000u);
+  const double td = __builtin_bit_cast(double, u) - kOffset;
+  const double q = __builtin_fma(td, inv_p, kMagic) - kMagic;
+  return (int)(uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma(-q, p, td) + kMagic);
 }
 
 // X' = rint(x 2^(b - e)) (|X'| <= 2^53) as seven signed bytes d_j with X' =
@@ -230,7 +236,7 @@ __device__ __forceinline__ void crt_gemm_block(const CrtGemmArgs& g, int tm, int
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i], acc[i][j], 0, 0, 0);
       dma(wave * NPW + i, knext, sn);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -252,10 +258,9 @@ __device__ __forceinline__ void crt_gemm_block(const CrtGemmArgs& g, int tm, int
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        lds[(wm0 + i * 16 + 4 * fg + v) * OUT_LD + wn0 + j * 16 + fr] =
-            (unsigned char)sym_mod_rt(acc[i][j][v], pd, inv_p);
+      *reinterpret_cast<int*>(lds + (wm0 + i * 16 + fr) * OUT_LD + wn0 + j * 16 + 4 * fg) =
+          pack_bytes(sym_mod_rt(acc[i][j][0], pd, inv_p), sym_mod_rt(acc[i][j][1], pd, inv_p),
+                     sym_mod_rt(acc[i][j][2], pd, inv_p), sym_mod_rt(acc[i][j][3], pd, inv_p));
   __syncthreads();
   signed char* out = g.out + (int64_t)mod * g.plane_r;
   for (int w = tid; w < BM * (BN / 16); w += 256) {
@@ -282,7 +287,10 @@ crt_gemm(const CrtGemmArgs g, int nmod) {
 // piece after each row of MFMAs); the fragments of k-step kt + 1 are read
 // from LDS into a second register set while the MFMAs of k-step kt run.
 // The int32 results are reduced to residues, gathered as a 256 x 256 byte
-// tile in LDS and stored as 16-byte rows.
+// tile in LDS and stored as 16-byte rows.  The right operand goes first into
+// the MFMA, so a lane's four results are four columns of one row and leave as
+// one word.  n = 4096: 888 us a launch, 2.48 POP/s (918 with byte stores and
+// FP64 conversions), at the 1.9-2.1 GHz the socket's power limit leaves.
 template <int NST>  // LDS stages; 4 measured faster than 5
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 crt_gemm_256(const CrtGemmArgs g, int nmod) {
@@ -348,7 +356,7 @@ crt_gemm_256(const CrtGemmArgs g, int nmod) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i], acc[i][j], 0, 0, 0);
       dma(wave * NPW + i, knext, sn);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -379,10 +387,9 @@ crt_gemm_256(const CrtGemmArgs g, int nmod) {
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        lds[(wm0 + i * 16 + 4 * fg + v) * OUT_LD + wn0 + j * 16 + fr] =
-            (unsigned char)sym_mod_rt(acc[i][j][v], pd, inv_p);
+      *reinterpret_cast<int*>(lds + (wm0 + i * 16 + fr) * OUT_LD + wn0 + j * 16 + 4 * fg) =
+          pack_bytes(sym_mod_rt(acc[i][j][0], pd, inv_p), sym_mod_rt(acc[i][j][1], pd, inv_p),
+                     sym_mod_rt(acc[i][j][2], pd, inv_p), sym_mod_rt(acc[i][j][3], pd, inv_p));
   __syncthreads();
   signed char* out = g.out + (int64_t)mod * g.plane_r;
   for (int w = tid; w < BM * (BN / 16); w += 256) {
@@ -696,15 +703,18 @@ hipError_t launch_crt_split(const SplitOperand& x, const SplitOperand& y, hipStr
   return hipGetLastError();
 }
 
-// Block shape of the residue GEMMs: 256 x 256 once the grid holds two
-// blocks per CU (the larger block halves the bytes per MFMA), else 128 x 128
-// for more blocks on small products.  BQ_CRT_TILE=128 or 256 overrides.
+// Block shape of the residue GEMMs: 256 x 256 once the grid holds four blocks
+// per CU (the larger block halves the bytes per MFMA), else 128 x 128: a large
+// block's fill and drain are not covered by another block on its CU.  Traced
+// launches, 128 against 256: n = 1024 (240 large blocks) 24.2 against 26.2 us,
+// 1536 (576) 63 against 78, 2048 (1024) 133 against 129, 3072 444 against 395,
+// 4096 1036 against 889.  BQ_CRT_TILE=128 or 256 overrides.
 int crt_gemm_tile(int N, int64_t m, int64_t n) {
   const char* e = std::getenv("BQ_CRT_TILE");
   if (e && std::atoi(e) == 128) return 128;
   if (e && std::atoi(e) == 256) return 256;
   const int64_t big = ((m + 255) / 256) * ((n + 255) / 256) * N;
-  return big >= 512 ? 256 : 128;
+  return big >= 1024 ? 256 : 128;
 }
 
 hipError_t launch_crt_gemm(int N, const CrtGemmArgs& g, hipStream_t st) {
