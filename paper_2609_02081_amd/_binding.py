@@ -141,6 +141,21 @@ def _is_tensor(x) -> bool:
 def matrix(X, mask: int = FULL, rows=None, cols=None) -> BqMatrix:
     """BqMatrix over a (8, rows, cols) tensor or a list of 8 (rows, cols)
     tensors / None.  Components outside `mask` (or None) are passed as absent."""
+    if _is_tensor(X):
+        shape = X.shape
+        # A stacked tensor with rows of adjacent elements: the components'
+        # addresses from its strides (slicing it eight times takes a small
+        # call's time many times over).  Anything else, and every error, below.
+        if len(shape) == 3 and shape[0] >= 8 and shape[1] > 0 and shape[2] > 0:
+            step, ld, one = X.stride()
+            if one == 1:
+                if shape[1] == 1:
+                    ld = shape[2]
+                p, step = X.data_ptr(), step * X.element_size()
+                comp = (p, p + step, p + 2 * step, p + 3 * step, p + 4 * step, p + 5 * step, p + 6 * step, p + 7 * step)
+                if mask & FULL != FULL:
+                    comp = tuple(q if mask >> c & 1 else None for c, q in enumerate(comp))
+                return BqMatrix(comp, shape[1], shape[2], ld)
     M = BqMatrix()
     comps = list(X) if not _is_tensor(X) else [X[c] for c in range(8)]
     if len(comps) != 8:
@@ -248,12 +263,13 @@ def bq_gemm(A, B, C=None, *, opA="N", opB="N", mask_a=FULL, mask_b=FULL, prec="f
     n = Bm.rows if opB in ("T", "H") else Bm.cols
     dev = (A if _is_tensor(A) else next(t for t in A if t is not None)).device
     res, mn = workspace_size(m, n, k, _mask_of(Am), _mask_of(Bm), prec, slices)
-    with _on(stream):
-        if C is None:
-            C = torch.empty((8, m, n), dtype=torch.float64, device=dev)
-        if workspace is None:
-            need = mn if streamed else res
-            workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+    if C is None or workspace is None:
+        with _on(stream):
+            if C is None:
+                C = torch.empty((8, m, n), dtype=torch.float64, device=dev)
+            if workspace is None:
+                need = mn if streamed else res
+                workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     Cm = matrix(C)
     ws_bytes = workspace.numel() * workspace.element_size()
     if streamed:
@@ -280,7 +296,11 @@ def bq_gemm_noalloc(A, B, C, *, opA="N", opB="N", mask_a=FULL, mask_b=FULL, prec
 
 
 def _mask_of(M: BqMatrix) -> int:
-    return sum(1 << c for c in range(8) if M.comp[c])
+    mask = 0
+    for c, p in enumerate(M.comp):
+        if p:
+            mask |= 1 << c
+    return mask
 
 
 def _sub_gemm(name, mask, comps_a, comps_b, comps_c, opA, opB, prec, slices, workspace, stream):

@@ -99,9 +99,19 @@ struct Tgt {
   Cplx coef;
 };
 
+// At most four targets, one per unit: kept in place, so that planning a call
+// allocates next to nothing.
+struct Targets {
+  Tgt t[4];
+  int count = 0;
+  void push_back(const Tgt& x) { t[count++] = x; }
+  const Tgt* begin() const { return t; }
+  const Tgt* end() const { return t + count; }
+};
+
 struct Prod {
   Operand L, R;
-  std::vector<Tgt> tgts;
+  Targets tgts;
 };
 
 struct Plan {
@@ -141,6 +151,7 @@ Plan make_plan(const Problem& P) {
 
   // Component-wise form: 16 complex products, absent ones skipped.
   Plan cw;
+  cw.prods.reserve(16);
   for (int u = 0; u < 4; ++u)
     for (int v = 0; v < 4; ++v) {
       Prod p;
@@ -156,6 +167,7 @@ Plan make_plan(const Problem& P) {
 
   // Bilinear form, eq. bilinearH.
   Plan bl;
+  bl.prods.reserve(8);
   bl.bilinear = true;
   for (int q = 0; q < 4; ++q) {
     const int u = kPairs[q][0], v = kPairs[q][1];
@@ -199,7 +211,7 @@ Plan make_plan(const Problem& P) {
   best.k = P.k;
   best.ta = op_trans(P.opA);
   best.tb = op_trans(P.opB);
-  return best;
+  return std::move(best);
 }
 
 // Workspace slot of one pre-combined operand: the stored orientation (op T
@@ -505,9 +517,11 @@ bq_status_t validate(bq_op_t opA, bq_op_t opB, const bq_matrix_t* A, const bq_ma
   // Aliasing: output blocks against inputs, workspace and each other.
   if (m > 0 && n > 0) {
     std::vector<Range> outs;
+    outs.reserve(8);
     for (int c = 0; c < 8; ++c)
       if (out_mask >> c & 1) outs.push_back(block_range(C->comp[c], m, n, C->ld));
     std::vector<Range> ins;
+    ins.reserve(17);
     if (k > 0) {
       for (int c = 0; c < 8; ++c) {
         if (A->comp[c]) ins.push_back(block_range(A->comp[c], A->rows, A->cols, A->ld));
