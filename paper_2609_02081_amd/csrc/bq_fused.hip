@@ -14,8 +14,10 @@
 // holding (m / 64)(n / 64) blocks: 1 block at n = 64, 16 at n = 256, 256 (of
 // 512 slots) at n = 1024.  Here every tile of 16 x 16 or 32 x 32 carries
 // eight waves.  What bounds it at full size is the staging beside the matrix
-// pipe: at m = n = k = 1024 (32 x 32 tiles) 865 us, 59.6 TFLOP/s, and 731 us
-// without the Hadamard sums and their LDS writes.
+// pipe: at m = n = k = 1024 (32 x 32 tiles) 841 us, 61.3 TFLOP/s, and about
+// 730 us without the Hadamard sums and their LDS writes (865 us before the LDS
+// slots made every access conflict-free and the loads took 64 bytes of a row
+// together; with 8-byte loads, n = 1023, 1038 -> 911).
 //
 // The k order of every product, the order of the Hadamard sums and the order
 // of the additions into C are those of the per-product path, so the results
@@ -27,7 +29,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "bq_internal.h"
+#include "bq_tile_order.h"
 
 namespace bq {
 
@@ -41,13 +43,20 @@ __device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
 }
 
 // LDS position of (row or column r, k) in one T-wide plane: fragment (k / 4,
-// r / 16) is 64 consecutive doubles, 16 per k, even rows before odd ones.  A
-// fragment read and a staging write (16 rows at one k, or the even or the odd
-// rows of two k) then touch 16 distinct consecutive bank pairs.
+// r / 16) is 64 doubles, 16 per k.  An access serves 16 lanes on 16 bank pairs,
+// so the slot among the 16 is chosen to make the 16 lanes of every access
+// distinct: a fragment read (16 rows, one k), a staging write of a side stored
+// along k (2 rows by 8 pairs of k, 4 by 4 or 1 by 16: the pair's bits are
+// folded in) and of a side stored along the rows (the even or the odd rows of
+// two k, or of two fragments: even rows take slots 0..7, and bit 3 flips with
+// k and the fragment).
 __device__ __forceinline__ int row_at(int r) { return ((r & 15) >> 1) | ((r & 1) << 3); }
+__device__ __forceinline__ int slot_flip(int r, int k) {
+  return ((r >> 1) & 8) ^ ((k & 1) << 3) ^ (k & 6) ^ ((k >> 3) & 1) ^ ((k >> 1) & 8);
+}
 template <int T>
 __device__ __forceinline__ int plane_at(int r, int k) {
-  return ((k >> 2) * (T / 16) + (r >> 4)) * 64 + (k & 3) * 16 + row_at(r);
+  return ((k >> 2) * (T / 16) + (r >> 4)) * 64 + (k & 3) * 16 + (row_at(r) ^ slot_flip(r, k));
 }
 
 template <int... I, typename F>
@@ -64,9 +73,14 @@ __device__ __forceinline__ void static_for(F&& f) {
 // Staging: a unit is one pair of adjacent stored elements of four components
 // (one side, real or imaginary parts); a wave's units share side and part,
 // so its component bases are scalar.  U units per thread and k-step.
+// LDS of one block: two stages, each 8 planes per part and side.
 template <int IM, int T, int BK>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-bq_fused(const FusedArgs g) {
+constexpr int kFusedLds = 2 * 2 * (IM ? 2 : 1) * 8 * T * BK;
+
+// Tile (tm, tn) of C.  Args: FusedArgs as kernel arguments, or in a device
+// table read as constant memory.
+template <int IM, int T, int BK, typename Args>
+__device__ __forceinline__ void fused_block(const Args& g, int tm, int tn, double* lds) {
   constexpr int NPART = IM ? 2 : 1;
   constexpr int PLANE = T * BK;             // doubles per plane
   constexpr int SIDE = NPART * 8 * PLANE;   // 4 raw + 4 combined planes per part
@@ -77,30 +91,17 @@ bq_fused(const FusedArgs g) {
   static_assert(UNITS % 512 == 0 && PAIRS % 64 == 0, "whole waves per side and part");
   constexpr int NI = T / 16;
   constexpr int NACC = IM ? 3 : 1;
+  static_assert(2 * STAGE == kFusedLds<IM, T, BK>, "LDS size");
   static_assert(8 * NPART * T * T <= 2 * STAGE, "P of every product fits the stages");
-  __shared__ __attribute__((aligned(16))) double lds[2 * STAGE];
-
-  // Tile of this block: contiguous ranges of tiles per XCD (blocks are dealt
-  // to the 8 XCDs round-robin), columns fastest inside groups of 8 tile rows.
-  const int tiles_m = (int)((g.m + T - 1) / T), tiles_n = (int)((g.n + T - 1) / T);
-  int tm, tn;
-  {
-    const int n_tiles = tiles_m * tiles_n, w = blockIdx.x, x = w % 8, slot = w / 8;
-    const int base = n_tiles / 8, rem = n_tiles % 8;
-    const int t = x * base + (x < rem ? x : rem) + slot;
-    const int per_group = 8 * tiles_n, group = t / per_group, first_m = group * 8;
-    const int gm = min(tiles_m - first_m, 8), in_g = t - group * per_group;
-    tm = first_m + in_g % gm;
-    tn = in_g / gm;
-  }
   const int64_t m0 = (int64_t)tm * T, n0 = (int64_t)tn * T;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // This thread's units.  k-contiguous sides (A for op N, B for op T): pair
-  // = (row r, k 2 kp), rows fastest; the others: pair = (rows 2 rp, k).
+  // = (row r, k 2 kp), k fastest; the others: pair = (rows 2 rp, k), rows
+  // fastest: 64 bytes or more of each stored row.
   constexpr uint32_t kOut = 0x80000000u;  // past the resource's range: reads zero
-  int part[U], side[U], kk[U], lpos[U];
+  int part[U], side[U], kk[U], lpos[U][2];  // LDS positions of the pair's elements
   uint32_t off[U][2];   // byte offsets of the pair's two elements in the tile at k0 = 0
   bool kc[U];
   const double* base[U][4];
@@ -120,20 +121,23 @@ bq_fused(const FusedArgs g) {
       base[u][c] = (side[u] ? g.b[4 * part[u] + c] : g.a[4 * part[u] + c]) + (kc[u] ? o0 * ld : o0);
     kstride[u] = kc[u] ? 1 : ld;
     if (kc[u]) {
-      const int r = pair % T;
-      kk[u] = 2 * (pair / T);
+      const int r = pair / (BK / 2);
+      kk[u] = 2 * (pair % (BK / 2));
       off[u][0] = r < lim ? (uint32_t)((r * (uint32_t)ld + kk[u]) * 8u) : kOut;
       off[u][1] = r < lim ? off[u][0] + 8u : kOut;
-      lpos[u] = plane_at<T>(r, kk[u]);
+      lpos[u][0] = plane_at<T>(r, kk[u]);
+      lpos[u][1] = plane_at<T>(r, kk[u] + 1);
     } else {
       const int r = 2 * (pair % (T / 2));
       kk[u] = pair / (T / 2);
       const uint32_t o = (uint32_t)((kk[u] * (uint32_t)ld + r) * 8u);
       off[u][0] = r < lim ? o : kOut;
       off[u][1] = r + 1 < lim ? o + 8u : kOut;
-      lpos[u] = plane_at<T>(r, kk[u]);
+      lpos[u][0] = plane_at<T>(r, kk[u]);
+      lpos[u][1] = plane_at<T>(r + 1, kk[u]);
     }
-    lpos[u] += side[u] * SIDE + part[u] * 8 * PLANE;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) lpos[u][e] += side[u] * SIDE + part[u] * 8 * PLANE;
   }
 
   const int nk = (int)((g.k + BK - 1) / BK), nkf = (int)(g.k / BK);
@@ -182,8 +186,8 @@ bq_fused(const FusedArgs g) {
   auto chunk = [&](auto J, int kt, const d2 (&x)[U][4]) {
     constexpr int u = J.value / 4, j = J.value % 4;
     const double s1 = side[u] ? g.sb[1] : g.sa[1], s2 = side[u] ? g.sb[2] : g.sa[2], s3 = side[u] ? g.sb[3] : g.sa[3];
-    double* d0 = lds + (kt & 1) * STAGE + lpos[u] + 2 * j * PLANE;
-    double* d1 = d0 + (kc[u] ? 16 : 8);  // the next k, or the next (odd) row
+    double* d0 = lds + (kt & 1) * STAGE + lpos[u][0] + 2 * j * PLANE;
+    double* d1 = lds + (kt & 1) * STAGE + lpos[u][1] + 2 * j * PLANE;
     d2 h0, h1;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -210,9 +214,10 @@ bq_fused(const FusedArgs g) {
   // This wave's product: operand planes (direct: raw unit pairs; Hadamard:
   // combination wave - 4 on both sides).
   const int ua = wave < 4 ? g.pair_a[wave & 3] : wave, ub = wave < 4 ? g.pair_b[wave & 3] : wave;
-  const int frag = (lane & 48) + row_at(lane);
-  const double* pa = lds + ua * PLANE + frag;
-  const double* pb = lds + SIDE + ub * PLANE + frag;
+  const double* pa = lds + ua * PLANE;
+  const double* pb = lds + SIDE + ub * PLANE;
+  // Position of this lane's element of fragment (substep s, i) in a plane.
+  auto frag_at = [&](int s, int i) { return plane_at<T>(i * 16 + (lane & 15), 4 * s + (lane >> 4)); };
   const double sL = g.sL, sR = g.sR;
 
   d4 acc[NACC][NI][NI];
@@ -236,7 +241,7 @@ bq_fused(const FusedArgs g) {
       for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int p = 0; p < NPART; ++p) {
-          const int o = buf * STAGE + p * 8 * PLANE + ((half * HS + s) * NI + i) * 64;
+          const int o = buf * STAGE + p * 8 * PLANE + frag_at(half * HS + s, i);
           f.a[s][p][i] = pa[o];
           f.b[s][p][i] = pb[o];
         }
@@ -355,6 +360,32 @@ bq_fused(const FusedArgs g) {
 }
 
 template <int IM, int T, int BK>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+bq_fused(const FusedArgs g) {
+  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<IM, T, BK>];
+  // Contiguous ranges of tiles per XCD (blocks are dealt to the 8 XCDs
+  // round-robin), walked in groups of 8 tile rows.
+  const int tiles_m = (int)((g.m + T - 1) / T), tiles_n = (int)((g.n + T - 1) / T);
+  int tm, tn;
+  grouped_tile((int)xcd_position(blockIdx.x, 0, (int64_t)tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
+  fused_block<IM, T, BK>(g, tm, tn, lds);
+}
+
+// The same over the tiles of many problems: block b takes item b (problem,
+// tile edge, tile), the host having put them in order.
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+grouped_fused(const FusedArgs* probs, const FusedItem* items) {
+  static_assert(kFusedLds<1, 16, 16> == kFusedLds<1, 32, 8>, "one LDS size");
+  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<1, 32, 8>];
+  typedef const __attribute__((address_space(4))) FusedItem* item_ptr;
+  typedef const __attribute__((address_space(4))) FusedArgs table_args;
+  const item_ptr w = (item_ptr)items + blockIdx.x;
+  table_args& g = *((table_args*)probs + w->prob);
+  if (w->tile == 16) fused_block<1, 16, 16>(g, w->tm, w->tn, lds);
+  else fused_block<1, 32, 8>(g, w->tm, w->tn, lds);
+}
+
+template <int IM, int T, int BK>
 hipError_t launch_fused_t(const FusedArgs& g, hipStream_t s) {
   const int64_t tiles = ((g.m + T - 1) / T) * ((g.n + T - 1) / T);
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
@@ -364,13 +395,16 @@ hipError_t launch_fused_t(const FusedArgs& g, hipStream_t s) {
 
 }  // namespace
 
+// Buffer offsets inside a tile must reach every element (T <= 32, BK <= 32).
+bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) * 8 + 32 * 8 < 0x7fffffff; }
+
 // Which path a product takes: an estimate of both in microseconds, from rates
-// measured on an MI355X at m = n = k = 64 .. 4096 (each line of the model is
-// within 5 % of the measured times from n = 1200 on).  One round is one block
-// on each of the 256 CUs (fused) or two (per product).
-//   fused   a round of 32 x 32 blocks takes 0.233 us per unit of k (24 real
-//           products) or 0.0765 (8); of 16 x 16 blocks a third of that, so
-//           they win where three of their rounds replace more than one.
+// measured on an MI355X at m = n = k = 64 .. 4096.  One round is one block on
+// each of the 256 CUs (fused) or two (per product).
+//   fused   a round of 32 x 32 blocks takes 0.213 us per unit of k (24 real
+//           products) or 0.0755 (8), with rows that are not 16-byte aligned
+//           0.255 and 0.0815; of 16 x 16 blocks 0.066 and 0.028, so they win
+//           where about three of their rounds replace more than one.
 //   per     each of 8 launches: 0.20 us per unit of k and full round of 512
 //   product 64 x 64 tiles, 0.14 for a last round of at most 256 tiles (one
 //           per CU), 0.22 for a longer one; real products 0.07 per round of
@@ -378,19 +412,18 @@ hipError_t launch_fused_t(const FusedArgs& g, hipStream_t s) {
 //           blocks.  Plus the pre-combination (16 blocks read and 16
 //           written) and the read-modify-write of C at 4.8 TB/s, the latter
 //           0.6 exposed.
-// At n = 256 the fused kernel takes 24 us against 365, at 1024 865 us against
-// 1204, at 2300 11.3 ms against 12.5; at 2600 it loses (16.3 against 15.5 ms)
-// and at 3500 the per-product path is 11 % faster.
-int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb) {
+// Fused against per product: n = 256 23 us against 365, 1024 841 against 1204,
+// 2048 6.67 ms against 7.17, 3000 21.6 against 23.0; 3500 35.9 against 35.2 and
+// 4096 52.9 against 51.7; odd rows 3001 26.8 against 23.7.
+int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec) {
   constexpr int64_t kCUs = 256;
   auto tiles = [&](int64_t t) { return ((m + t - 1) / t) * ((n + t - 1) / t); };
   auto rounds = [&](int64_t t, int64_t per) { return (tiles(t) + per - 1) / per; };
-  // Buffer offsets inside a tile must reach every element (T <= 32, BK <= 32).
-  if (32 * std::max(lda, ldb) * 8 + 32 * 8 >= 0x7fffffff) return 0;
-  const int64_t r16 = rounds(16, kCUs), r32 = rounds(32, kCUs);
-  const int tile = r16 <= 3 * r32 ? 16 : 32;
-  const double per_k = im ? 0.233 : 0.0765;
-  const double fused = double(k) * per_k * (tile == 16 ? double(r16) / 3.0 : double(r32));
+  if (!fused_spans_fit(lda, ldb)) return 0;
+  const double t16 = double(rounds(16, kCUs)) * (im ? 0.066 : 0.028);
+  const double t32 = double(rounds(32, kCUs)) * (im ? (vec ? 0.213 : 0.255) : (vec ? 0.0755 : 0.0815));
+  const int tile = t16 <= t32 ? 16 : 32;
+  const double fused = double(k) * std::min(t16, t32);
   double launch;
   if (im) {
     const int64_t full = tiles(64) / (2 * kCUs), tail = tiles(64) % (2 * kCUs);
@@ -404,6 +437,12 @@ int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t 
   const double per_product = 8.0 * double(k) * launch + 128.0 * gb * (double(m) + double(n)) * double(k) +
                              0.6 * 576.0 * gb * double(m) * double(n);
   return fused <= per_product ? tile : 0;
+}
+
+hipError_t launch_grouped_fused(const FusedArgs* probs, const FusedItem* items, int nitems, hipStream_t s) {
+  if (nitems <= 0) return hipSuccess;
+  hipLaunchKernelGGL(grouped_fused, dim3((unsigned)nitems), dim3(512), 0, s, probs, items);
+  return hipGetLastError();
 }
 
 hipError_t launch_fused(const FusedArgs& g, int im, int tile, hipStream_t s) {
