@@ -218,8 +218,10 @@ int bq_plan_real_gemms(unsigned maskA, unsigned maskB);
 
 /* ---------------------------------------------------------------------------
  * Batched form: many independent products C_p = op(A_p) op(B_p) of
- * different sizes in one plan, run as one graph.  FP64: a pre-combination
- * launch for every problem, then persistent launches whose blocks take
+ * different sizes in one plan, run as one graph.  FP64: one launch whose
+ * blocks run all eight products of a 16 x 16 or 32 x 32 tile of one problem
+ * (the workspace stays unused), or a pre-combination launch for every
+ * problem, then persistent launches whose blocks take
  * (problem, 64 x 64 tile) work items, largest problems first: either one
  * launch whose items run the problem's eight complex products on their tile
  * in turn, or one launch per complex product (the autotuner picks); in the
@@ -264,9 +266,11 @@ bq_status_t bq_grouped_plan_workspace_size(bq_grouped_plan_t plan, size_t* bytes
  * split forms it returns BQ_OK without changes. */
 bq_status_t bq_grouped_plan_autotune(bq_grouped_plan_t plan, void* ws, size_t ws_bytes, bq_stream_t stream);
 bq_status_t bq_grouped_plan_launch(bq_grouped_plan_t plan, void* ws, size_t ws_bytes, bq_stream_t stream);
-/* Chosen tile configuration, schedule (bit 0: blocks take work items from a
- * device counter, else cyclically; bit 1: one launch per complex product)
- * and work items (FP64: tiles; CRT: real products). */
+/* Chosen tile configuration (0, 6: 64 x 64 tiles with k-steps of 16, 8; 13:
+ * all eight products of a tile in one block, one launch), schedule of 0 and 6
+ * (bit 0: blocks take work items from a device counter, else cyclically;
+ * bit 1: one launch per complex product) and work items (FP64: tiles; CRT:
+ * real products). */
 bq_status_t bq_grouped_plan_info(bq_grouped_plan_t plan, int* tile_config, int* dynamic_schedule, int* work_items);
 bq_status_t bq_grouped_plan_destroy(bq_grouped_plan_t plan);
 

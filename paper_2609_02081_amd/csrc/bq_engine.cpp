@@ -18,6 +18,7 @@
 
 #include "bq.h"
 #include "bq_internal.h"
+#include "bq_tile_order.h"
 
 struct TraceSlot {
   hipEvent_t start, stop;
@@ -1359,6 +1360,9 @@ struct bq_grouped_plan_s {
   int* d_counter = nullptr;
   bq::CombineArgs* d_comb = nullptr;
   int64_t* d_prefix = nullptr;
+  bq::FusedArgs* d_fused = nullptr;     // fused configuration: one entry per problem
+  bq::FusedItem* d_fused_items = nullptr;
+  int fused_items = 0;                  // 0: some problem cannot run fused
   bq::CombineArgs* d_ht = nullptr;  // per-product schedule: Hadamard sums of P5..P8, one per problem
   int64_t* d_ht_prefix = nullptr;
   int nitems = 0;
@@ -1380,7 +1384,10 @@ struct bq_grouped_plan_s {
 
 namespace {
 
-constexpr int kGroupedTile = 64;  // every grouped tile configuration is 64 x 64
+constexpr int kGroupedTile = 64;  // tile configurations 0 and 6 are 64 x 64
+// Tile configuration of the batched fused kernel: one launch whose blocks run
+// all eight products of a 16 x 16 or 32 x 32 tile (no schedule bits).
+constexpr int kGroupedFused = 13;
 
 void grouped_release_graph(bq_grouped_plan_t p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
@@ -1403,7 +1410,7 @@ bool tune_cache_lookup(const std::string& key, int* cfg, int* dyn) {
     std::istringstream ss(line);
     std::string k;
     int c = -1, d = -1;
-    if (ss >> k >> c >> d && k == key && (c == 0 || c == 6) && d >= 0 && d <= 3) {
+    if (ss >> k >> c >> d && k == key && (c == 0 || c == 6 || c == kGroupedFused) && d >= 0 && d <= 3) {
       *cfg = c;
       *dyn = d;
       found = true;  // the last entry for a key wins
@@ -1555,6 +1562,17 @@ bq_status_t grouped_bind(bq_grouped_plan_t p, void* ws) {
       bq_problem_t& q = p->probs[p->order[i]];
       st = execute(p->h, p->plans[p->order[i]], p->pr, &q.A, &q.B, &q.C, 0xFFu, ws, false, p->cap);
     }
+  } else if (p->cfg == kGroupedFused) {
+    std::vector<bq::FusedArgs> args(size_t(p->count));
+    for (int i = 0; i < p->count; ++i)
+      if (!fused_args(p->plans[i], &p->probs[i].A, &p->probs[i].B, &p->probs[i].C, 0xFFu, &args[i]))
+        return fail(BQ_ERR_INVALID_VALUE, "a problem of the batch cannot run fused");
+    e = hipMemcpy(p->d_fused, args.data(), args.size() * sizeof(bq::FusedArgs), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "grouped table upload");
+    e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
+    e = bq::launch_grouped_fused(p->d_fused, p->d_fused_items, p->fused_items, p->cap);
+    if (e != hipSuccess) st = hip_fail(e, "grouped launch");
   } else {
     // One launch per complex product (schedule bit 2): the Hadamard
     // products P5..P8 go first and write their P into the problem's
@@ -1741,6 +1759,67 @@ bq_status_t grouped_bind(bq_grouped_plan_t p, void* ws) {
   return BQ_OK;
 }
 
+// Items of the fused configuration (empty: a problem cannot run fused): per
+// problem the tile edge with the smaller total, or 16 throughout where larger
+// tiles leave CUs idle; problems in order, each one's tiles in contiguous runs
+// per XCD.  *wins: whether the fused configuration is the plan's default, by
+// an estimate of both in microseconds.  Fused: a tile takes 0.206 us per unit
+// of k (32 x 32; 0.24 where rows are not 16-byte aligned) or 0.066 (16 x 16)
+// plus 3 to fill and drain, 256 at a time.  Per complex product: 8 launches of
+// 64 x 64 tiles at 0.205 us per unit of k, 512 at a time, the pre-combination
+// (128 bytes per element of A and B) and the Hadamard sums (256 per element of
+// C) at 4.8 TB/s, and the launches themselves.  Fused against per product:
+// 256 products of n = 64 114 us against 392, of 512 28.6 ms against 33.5, 64 of
+// 1024 54.4 against 59.0 and of 1023 60.0 against 60.5, 3 of 4096 161 against 161.
+std::vector<bq::FusedItem> fused_plan_items(const bq_grouped_plan_s* p, bool* wins) {
+  std::vector<bq::FusedItem> items;
+  constexpr double kCUs = 256.0;
+  auto tiles = [&](const Plan& pl, int t) { return ((pl.m + t - 1) / t) * ((pl.n + t - 1) / t); };
+  struct Choice {
+    double c16, c32;  // time per tile
+    bool small;
+  };
+  std::vector<Choice> ch(size_t(p->count));
+  double sum16 = 0, max16 = 0, sum = 0, mx = 0, per_product = 0, kmax = 0;
+  int64_t total = 0;
+  *wins = false;
+  for (int i = 0; i < p->count; ++i) {
+    const Plan& pl = p->plans[i];
+    bq::FusedArgs g;
+    if (!fused_args(pl, &p->probs[i].A, &p->probs[i].B, &p->probs[i].C, 0xFFu, &g) || !g.a[4] ||
+        !bq::fused_spans_fit(g.lda, g.ldb))
+      return items;
+    const double k = double(pl.k), mk = double(pl.m) * k, kn = k * double(pl.n), mn = double(pl.m) * double(pl.n);
+    Choice& c = ch[i];
+    c.c16 = 0.066 * k + 3.0;
+    c.c32 = (g.vec ? 0.206 : 0.24) * k + 3.0;
+    const double s16 = c.c16 * double(tiles(pl, 16)), s32 = c.c32 * double(tiles(pl, 32));
+    c.small = s16 <= s32;
+    sum16 += s16;
+    max16 = std::max(max16, c.c16);
+    sum += std::min(s16, s32);
+    mx = std::max(mx, c.small ? c.c16 : c.c32);
+    per_product += 8.0 * double(tiles(pl, 64)) * k * 0.205 / 512.0 + (128.0 * (mk + kn) + 256.0 * mn) / 4.8e6;
+    kmax = std::max(kmax, k);
+    total += tiles(pl, 16);
+  }
+  if (total > 0x7fffffff) return items;
+  const double mixed = std::max(sum / kCUs, mx), all_small = std::max(sum16 / kCUs, max16);
+  *wins = std::min(mixed, all_small) + 10.0 <= std::max(per_product, 0.8 * kmax) + 80.0;
+  for (int i : p->order) {
+    const Plan& pl = p->plans[i];
+    const int t = all_small < mixed || ch[i].small ? 16 : 32;
+    const int tm = int((pl.m + t - 1) / t), tn = int((pl.n + t - 1) / t);
+    const int64_t p0 = int64_t(items.size()), p1 = p0 + int64_t(tm) * tn;
+    for (int64_t b = p0; b < p1; ++b) {
+      bq::FusedItem it{i, t, 0, 0};
+      bq::grouped_tile(int(bq::xcd_position(b, p0, p1)), tm, tn, it.tm, it.tn);
+      items.push_back(it);
+    }
+  }
+  return items;
+}
+
 bq_status_t grouped_check_ws(bq_grouped_plan_t p, void* ws, size_t ws_bytes) {
   if (ws_bytes < p->ws_bytes)
     return fail(BQ_ERR_WORKSPACE, "workspace " + std::to_string(ws_bytes) + " B < " + std::to_string(p->ws_bytes) + " B");
@@ -1873,7 +1952,19 @@ bq_status_t bq_grouped_plan_create(bq_handle_t h, int count, const bq_problem_t*
   }
   key << std::hex << hash;
   p->tune_key = key.str();
-  (void)tune_cache_lookup(p->tune_key, &p->cfg, &p->dyn);
+  bool fused_wins = false;
+  const std::vector<bq::FusedItem> fused =
+      pr.et < 0 ? fused_plan_items(p, &fused_wins) : std::vector<bq::FusedItem>();
+  p->fused_items = int(fused.size());
+  if (fused_wins) {
+    p->cfg = kGroupedFused;
+    p->dyn = 0;
+  }
+  int tuned_cfg = p->cfg, tuned_dyn = p->dyn;
+  if (tune_cache_lookup(p->tune_key, &tuned_cfg, &tuned_dyn) && (tuned_cfg != kGroupedFused || p->fused_items > 0)) {
+    p->cfg = tuned_cfg;
+    p->dyn = tuned_dyn;
+  }
 
   hipError_t e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
   if (e == hipSuccess && pr.et < 0 && count > 0) {
@@ -1909,6 +2000,12 @@ bq_status_t bq_grouped_plan_create(bq_handle_t h, int count, const bq_problem_t*
     if (e == hipSuccess) e = hipMalloc(&p->d_ht_prefix, sizeof(int64_t) * size_t(count));
     if (e == hipSuccess)
       e = hipMemcpy(p->d_items, items.data(), sizeof(bq::GroupedItem) * items.size(), hipMemcpyHostToDevice);
+    if (p->fused_items > 0) {
+      if (e == hipSuccess) e = hipMalloc(&p->d_fused, sizeof(bq::FusedArgs) * size_t(count));
+      if (e == hipSuccess) e = hipMalloc(&p->d_fused_items, sizeof(bq::FusedItem) * fused.size());
+      if (e == hipSuccess)
+        e = hipMemcpy(p->d_fused_items, fused.data(), sizeof(bq::FusedItem) * fused.size(), hipMemcpyHostToDevice);
+    }
   }
   if (e == hipSuccess && pr.et == 3 && count > 0) {
     // Table sizes do not depend on the workspace address: record against a
@@ -1944,7 +2041,7 @@ bq_status_t bq_grouped_plan_info(bq_grouped_plan_t plan, int* tile_config, int* 
   if (!plan) return fail(BQ_ERR_INVALID_VALUE, "plan is null");
   if (tile_config) *tile_config = plan->cfg;
   if (dynamic_schedule) *dynamic_schedule = plan->dyn;
-  if (work_items) *work_items = plan->nitems;
+  if (work_items) *work_items = plan->pr.et < 0 && plan->cfg == kGroupedFused ? plan->fused_items : plan->nitems;
   return BQ_OK;
 }
 
@@ -1982,11 +2079,12 @@ bq_status_t bq_grouped_plan_autotune(bq_grouped_plan_t plan, void* ws, size_t ws
     (void)hipEventDestroy(e0);
     return fail(BQ_ERR_HIP, "hipEventCreate");
   }
-  const int cfgs[2] = {0, 6};
+  const int cfgs[3] = {0, 6, kGroupedFused};
   float best = 1e30f;
   int best_cfg = plan->cfg, best_dyn = plan->dyn;
   for (int c : cfgs) {
     for (int d : {3, 2, 1, 0}) {
+      if (c == kGroupedFused && (d != 0 || plan->fused_items == 0)) continue;
       plan->cfg = c;
       plan->dyn = d;
       st = grouped_bind(plan, ws);
@@ -2031,6 +2129,8 @@ bq_status_t bq_grouped_plan_destroy(bq_grouped_plan_t plan) {
   if (plan->d_prefix) (void)hipFree(plan->d_prefix);
   if (plan->d_ht) (void)hipFree(plan->d_ht);
   if (plan->d_ht_prefix) (void)hipFree(plan->d_ht_prefix);
+  if (plan->d_fused) (void)hipFree(plan->d_fused);
+  if (plan->d_fused_items) (void)hipFree(plan->d_fused_items);
   if (plan->d_crt) (void)hipFree(plan->d_crt);
   delete plan;
   return BQ_OK;

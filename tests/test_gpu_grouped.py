@@ -308,3 +308,33 @@ def test_padded_operands_with_nan_padding(bq, oa, ob):
         torch.cuda.synchronize()
         assert oracle.rel_frobenius(c, single.cpu().numpy()) <= 1e-15, shape
     plan.close()
+
+
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("H", "T")])
+@pytest.mark.parametrize("odd", [0, 1])
+def test_one_launch_batches_equal_single_calls(bq, opA, opB, odd):
+    """The batched one-launch configuration (13) on small batches, chosen by
+    default: 16 x 16 and 32 x 32 tiles, ragged edges, one-element products,
+    even and odd leading dimensions.  Tiles run the code of the single call,
+    so every product equals it bit for bit."""
+    import torch
+
+    shapes = [(1, 1, 1), (16, 16, 16), (33, 40, 31), (100, 90, 80), (257, 64, 130), (400, 33, 390), (64, 300, 64)]
+    probs = []
+    for i, (m, k, n) in enumerate(shapes):
+        def draw(r, c, seed):
+            X = inputs.device_uniform(r, c + odd, seed, "cuda")
+            return X[:, :, :c]
+        A = draw(*((k, m) if opA == "H" else (m, k)), 500 + i)
+        B = draw(*((n, k) if opB == "T" else (k, n)), 600 + i)
+        probs.append((A, B, torch.full((8, m, n), float("nan"), dtype=torch.float64, device="cuda")))
+    print(f"one-launch batch {opA}{opB} odd {odd}", flush=True)
+    plan = bq.GroupedPlan(probs, opA=opA, opB=opB)
+    assert plan.info()["tile_config"] == 13
+    plan.launch()
+    torch.cuda.synchronize()
+    for (A, B, C), shape in zip(probs, shapes):
+        single = bq.bq_gemm(A, B, opA=opA, opB=opB)
+        torch.cuda.synchronize()
+        assert torch.equal(C, single), shape
+    plan.close()
