@@ -918,11 +918,13 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
   if (bq::FusedArgs fa; pr.et < 0 && k > 0 && fused_args(pl, A, B, C, out_mask, &fa)) {
     const int im = fa.a[4] != nullptr;
     // A forced tile configuration of the real products keeps their launches.
-    const int tile = !im && cfg_override >= 0 ? 0 : bq::fused_tile(im, m, n, k, fa.ta, fa.tb, fa.lda, fa.ldb, fa.vec);
-    if (tile > 0) {
+    const int64_t full = !im && cfg_override >= 0
+                             ? -1
+                             : bq::fused_full_tiles(im, m, n, k, fa.ta, fa.tb, fa.lda, fa.ldb, fa.vec);
+    if (full >= 0) {
       Tracer tr(h, s, im ? BQ_KERNEL_GEMM_GAUSS : BQ_KERNEL_GEMM_RR, -1, m, n, k,
                 double(pl.real_gemms) * 2.0 * double(m) * double(n) * double(k), 0.0);
-      hipError_t e = bq::launch_fused(fa, im, tile, s);
+      hipError_t e = bq::launch_fused(fa, im, full, s);
       tr.done();
       if (e != hipSuccess) return hip_fail(e, "fused product launch");
       for (int c = 0; c < (im ? 8 : 4); ++c) touched[c] = true;

@@ -359,38 +359,58 @@ __device__ __forceinline__ void fused_block(const Args& g, int tm, int tn, doubl
   }
 }
 
-template <int IM, int T, int BK>
+// k-steps of the two tile edges, and their LDS (the same for both).
+template <int IM>
+constexpr int kFusedBk16 = IM ? 16 : 32;
+template <int IM>
+constexpr int kFusedBk32 = IM ? 8 : 16;
+
+// One product in 16 x 16 tiles.  Contiguous ranges of tiles per XCD (blocks are
+// dealt to the 8 XCDs round-robin), walked in groups of 8 tile rows.
+template <int IM>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-bq_fused(const FusedArgs g) {
-  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<IM, T, BK>];
-  // Contiguous ranges of tiles per XCD (blocks are dealt to the 8 XCDs
-  // round-robin), walked in groups of 8 tile rows.
-  const int tiles_m = (int)((g.m + T - 1) / T), tiles_n = (int)((g.n + T - 1) / T);
+bq_fused16(const FusedArgs g) {
+  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<IM, 16, kFusedBk16<IM>>];
+  const int tiles_m = (int)((g.m + 15) / 16), tiles_n = (int)((g.n + 15) / 16);
   int tm, tn;
   grouped_tile((int)xcd_position(blockIdx.x, 0, (int64_t)tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
-  fused_block<IM, T, BK>(g, tm, tn, lds);
+  fused_block<IM, 16, kFusedBk16<IM>>(g, tm, tn, lds);
+}
+
+// One product: blocks 0 .. full - 1 take 32 x 32 tiles, four blocks each the
+// remaining ones in 16 x 16 quarters.
+template <int IM>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+bq_fused(const FusedArgs g, int full) {
+  static_assert(kFusedLds<IM, 16, kFusedBk16<IM>> == kFusedLds<IM, 32, kFusedBk32<IM>>, "one LDS size");
+  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<IM, 32, kFusedBk32<IM>>];
+  const int tiles_m = (int)((g.m + 31) / 32), tiles_n = (int)((g.n + 31) / 32);
+  const int b = blockIdx.x;
+  int tm, tn;
+  if (b < full) {
+    grouped_tile((int)xcd_position(b, 0, full), tiles_m, tiles_n, tm, tn);
+    fused_block<IM, 32, kFusedBk32<IM>>(g, tm, tn, lds);
+  } else {
+    const int q = (int)xcd_position(b, full, full + 4 * ((int64_t)tiles_m * tiles_n - full));
+    grouped_tile(full + (q >> 2), tiles_m, tiles_n, tm, tn);
+    tm = 2 * tm + (q >> 1 & 1);
+    tn = 2 * tn + (q & 1);
+    if ((int64_t)tm * 16 >= g.m || (int64_t)tn * 16 >= g.n) return;
+    fused_block<IM, 16, kFusedBk16<IM>>(g, tm, tn, lds);
+  }
 }
 
 // The same over the tiles of many problems: block b takes item b (problem,
 // tile edge, tile), the host having put them in order.
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 grouped_fused(const FusedArgs* probs, const FusedItem* items) {
-  static_assert(kFusedLds<1, 16, 16> == kFusedLds<1, 32, 8>, "one LDS size");
-  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<1, 32, 8>];
+  __shared__ __attribute__((aligned(16))) double lds[kFusedLds<1, 32, kFusedBk32<1>>];
   typedef const __attribute__((address_space(4))) FusedItem* item_ptr;
   typedef const __attribute__((address_space(4))) FusedArgs table_args;
   const item_ptr w = (item_ptr)items + blockIdx.x;
   table_args& g = *((table_args*)probs + w->prob);
-  if (w->tile == 16) fused_block<1, 16, 16>(g, w->tm, w->tn, lds);
-  else fused_block<1, 32, 8>(g, w->tm, w->tn, lds);
-}
-
-template <int IM, int T, int BK>
-hipError_t launch_fused_t(const FusedArgs& g, hipStream_t s) {
-  const int64_t tiles = ((g.m + T - 1) / T) * ((g.n + T - 1) / T);
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((bq_fused<IM, T, BK>), dim3((unsigned)tiles), dim3(512), 0, s, g);
-  return hipGetLastError();
+  if (w->tile == 16) fused_block<1, 16, kFusedBk16<1>>(g, w->tm, w->tn, lds);
+  else fused_block<1, 32, kFusedBk32<1>>(g, w->tm, w->tn, lds);
 }
 
 }  // namespace
@@ -403,8 +423,10 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 // each of the 256 CUs (fused) or two (per product).
 //   fused   a round of 32 x 32 blocks takes 0.213 us per unit of k (24 real
 //           products) or 0.0755 (8), with rows that are not 16-byte aligned
-//           0.255 and 0.0815; of 16 x 16 blocks 0.066 and 0.028, so they win
-//           where about three of their rounds replace more than one.
+//           0.255 and 0.0815; of 16 x 16 blocks 0.066 and 0.028.  A last round
+//           of r tiles runs as 4 r quarters where that takes less, up to half
+//           a round: 1000 x 777 x 515 (544 tiles) 478 -> 390 us, n = 800 500 ->
+//           438, n = 2300 10.38 -> 10.05 ms.
 //   per     each of 8 launches: 0.20 us per unit of k and full round of 512
 //   product 64 x 64 tiles, 0.14 for a last round of at most 256 tiles (one
 //           per CU), 0.22 for a longer one; real products 0.07 per round of
@@ -415,15 +437,21 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 // Fused against per product: n = 256 23 us against 365, 1024 841 against 1204,
 // 2048 6.67 ms against 7.17, 3000 21.6 against 23.0; 3500 35.9 against 35.2 and
 // 4096 52.9 against 51.7; odd rows 3001 26.8 against 23.7.
-int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec) {
+int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec) {
   constexpr int64_t kCUs = 256;
   auto tiles = [&](int64_t t) { return ((m + t - 1) / t) * ((n + t - 1) / t); };
   auto rounds = [&](int64_t t, int64_t per) { return (tiles(t) + per - 1) / per; };
-  if (!fused_spans_fit(lda, ldb)) return 0;
-  const double t16 = double(rounds(16, kCUs)) * (im ? 0.066 : 0.028);
-  const double t32 = double(rounds(32, kCUs)) * (im ? (vec ? 0.213 : 0.255) : (vec ? 0.0755 : 0.0815));
-  const int tile = t16 <= t32 ? 16 : 32;
-  const double fused = double(k) * std::min(t16, t32);
+  if (!fused_spans_fit(lda, ldb) || tiles(32) > 0x1fffffff) return -1;
+  const double c16 = im ? 0.066 : 0.028, c32 = im ? (vec ? 0.213 : 0.255) : (vec ? 0.0755 : 0.0815);
+  const int64_t t32 = tiles(32), whole = t32 / kCUs * kCUs;
+  // All in 32 x 32 tiles, the last round in quarters (those outside C end at
+  // once), or all in 16 x 16 tiles.
+  const double cost[3] = {c32 * double(rounds(32, kCUs)),
+                          c32 * double(whole / kCUs) + c16 * double((4 * (t32 - whole) + kCUs - 1) / kCUs),
+                          c16 * double(rounds(16, kCUs))};
+  const int64_t full[3] = {t32, whole, 0};
+  const int pick = int(std::min_element(cost, cost + 3) - cost);
+  const double fused = double(k) * cost[pick];
   double launch;
   if (im) {
     const int64_t full = tiles(64) / (2 * kCUs), tail = tiles(64) % (2 * kCUs);
@@ -436,7 +464,7 @@ int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t 
   const double gb = 1e-6 / 4.8 * (im ? 1.0 : 0.5);  // us per byte of the 24-product form
   const double per_product = 8.0 * double(k) * launch + 128.0 * gb * (double(m) + double(n)) * double(k) +
                              0.6 * 576.0 * gb * double(m) * double(n);
-  return fused <= per_product ? tile : 0;
+  return fused <= per_product ? full[pick] : -1;
 }
 
 hipError_t launch_grouped_fused(const FusedArgs* probs, const FusedItem* items, int nitems, hipStream_t s) {
@@ -445,10 +473,19 @@ hipError_t launch_grouped_fused(const FusedArgs* probs, const FusedItem* items, 
   return hipGetLastError();
 }
 
-hipError_t launch_fused(const FusedArgs& g, int im, int tile, hipStream_t s) {
+hipError_t launch_fused(const FusedArgs& g, int im, int64_t full, hipStream_t s) {
   if (g.m <= 0 || g.n <= 0 || g.k <= 0) return hipErrorInvalidValue;
-  if (im) return tile == 16 ? launch_fused_t<1, 16, 16>(g, s) : launch_fused_t<1, 32, 8>(g, s);
-  return tile == 16 ? launch_fused_t<0, 16, 32>(g, s) : launch_fused_t<0, 32, 16>(g, s);
+  const int64_t t32 = ((g.m + 31) / 32) * ((g.n + 31) / 32), blocks = full + 4 * (t32 - full);
+  if (full < 0 || full > t32 || blocks > 0x7fffffff) return hipErrorInvalidValue;
+  if (full == 0) {
+    const dim3 grid((unsigned)(((g.m + 15) / 16) * ((g.n + 15) / 16)));
+    if (im) hipLaunchKernelGGL(bq_fused16<1>, grid, dim3(512), 0, s, g);
+    else hipLaunchKernelGGL(bq_fused16<0>, grid, dim3(512), 0, s, g);
+    return hipGetLastError();
+  }
+  if (im) hipLaunchKernelGGL(bq_fused<1>, dim3((unsigned)blocks), dim3(512), 0, s, g, (int)full);
+  else hipLaunchKernelGGL(bq_fused<0>, dim3((unsigned)blocks), dim3(512), 0, s, g, (int)full);
+  return hipGetLastError();
 }
 
 }  // namespace bq

@@ -210,8 +210,9 @@ hipError_t launch_cgemm(int kind, const GemmArgs& g, int cfg, hipStream_t s);
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 hipError_t launch_fill_zero(double* p, int64_t rows, int64_t cols, int64_t ld, hipStream_t s);
 // The fused kernel (bq_fused.hip); im: 1 with imaginary components (24 real
-// products), 0 for real quaternions (8); tile: 16 or 32.
-hipError_t launch_fused(const FusedArgs& g, int im, int tile, hipStream_t s);
+// products), 0 for real quaternions (8); full: 32 x 32 tiles run whole, the
+// others in quarters (0: 16 x 16 tiles throughout).
+hipError_t launch_fused(const FusedArgs& g, int im, int64_t full, hipStream_t s);
 // Work item of the batched fused kernel: tile (tm, tn) of edge `tile` (16 or
 // 32) of problem prob.
 struct FusedItem {
@@ -219,8 +220,9 @@ struct FusedItem {
 };
 hipError_t launch_grouped_fused(const FusedArgs* probs, const FusedItem* items, int nitems, hipStream_t s);
 bool fused_spans_fit(int64_t lda, int64_t ldb);
-// Tile edge of the fused kernel for this product, 0: the per-product path.
-int fused_tile(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec);
+// 32 x 32 tiles the fused kernel runs whole for this product, -1: the
+// per-product path.
+int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec);
 int num_tile_configs();
 TileConfig tile_config(int cfg);
 int default_tile_config(int kind, int64_t m, int64_t n, int64_t k);

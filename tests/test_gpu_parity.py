@@ -514,12 +514,14 @@ def test_tuning_switches_same_products(bq, monkeypatch, env, value):
 
 @pytest.mark.parametrize("mask", [0xFF, 0x0F])
 @pytest.mark.parametrize("m,k,n,pad", [(1, 1, 1, 0), (16, 16, 16, 0), (17, 31, 33, 1), (31, 33, 15, 0), (48, 7, 100, 1),
-                                       (513, 8, 511, 0), (640, 24, 640, 0), (650, 41, 642, 1)])
+                                       (513, 8, 511, 0), (640, 24, 640, 0), (650, 41, 642, 1), (561, 40, 530, 0),
+                                       (529, 9, 545, 1)])
 @pytest.mark.parametrize("opA,opB", [("N", "N"), ("H", "T")])
 def test_one_launch_products(bq, mask, m, k, n, pad, opA, opB):
     """Small products run in one launch of 16 x 16 or 32 x 32 tiles (k-steps
     of 8, 16 or 32): one element, whole tiles, ragged m, n and k, odd and even
-    leading dimensions, both tile sizes.  Integer inputs: every product, sum
+    leading dimensions, both tile sizes, a last round in quarters (306 tiles of
+    32 x 32 over 256 CUs, some quarters outside C).  Integer inputs: every product, sum
     and Hadamard combination is exact, so the result equals the oracle's; the
     row padding holds NaN and the padding of C is left alone."""
     import torch
