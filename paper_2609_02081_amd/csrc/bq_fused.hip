@@ -427,11 +427,9 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 //           of r tiles runs as 4 r quarters where that takes less, up to half
 //           a round: 1000 x 777 x 515 (544 tiles) 478 -> 390 us, n = 800 500 ->
 //           438, n = 2300 10.38 -> 10.05 ms.
-//   per     each of 8 launches: 0.20 us per unit of k and full round of 512
-//   product 64 x 64 tiles, 0.14 for a last round of at most 256 tiles (one
-//           per CU), 0.22 for a longer one; real products 0.07 per round of
-//           512 (0.077 transposed), or 0.125 per round of 256 128 x 128
-//           blocks.  Plus the pre-combination (16 blocks read and 16
+//   per     each of 8 launches as tile_launch_cost estimates it (0.20 us per
+//   product unit of k and full round of 512 64 x 64 tiles of a complex product).
+//           Plus the pre-combination (16 blocks read and 16
 //           written) and the read-modify-write of C at 4.8 TB/s, the latter
 //           0.6 exposed.
 // Fused against per product: n = 256 23 us against 365, 1024 841 against 1204,
@@ -452,15 +450,11 @@ int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb
   const int64_t full[3] = {t32, whole, 0};
   const int pick = int(std::min_element(cost, cost + 3) - cost);
   const double fused = double(k) * cost[pick];
-  double launch;
-  if (im) {
-    const int64_t full = tiles(64) / (2 * kCUs), tail = tiles(64) % (2 * kCUs);
-    launch = 0.20 * double(full) + (tail == 0 ? 0.0 : tail <= kCUs ? 0.14 : 0.22);
-  } else if (!ta && !tb && default_tile_config(KIND_RR, m, n, k) == 11) {
-    launch = 0.125 * double(rounds(128, kCUs));
-  } else {
-    launch = (ta || tb ? 0.077 : 0.07) * double(rounds(64, 2 * kCUs));
-  }
+  const int kind = im ? KIND_GAUSS : KIND_RR;
+  const int cfg = default_tile_config(kind, m, n, k);
+  // Transposed real products run 64 x 64 tiles with k-steps of 16, 1.1 times as long.
+  const double launch = (!im && (ta || tb) && cfg != 14 ? 1.1 : 1.0) *
+                        tile_launch_cost(kind, (ta || tb) && cfg == 11 ? 3 : cfg, m, n);
   const double gb = 1e-6 / 4.8 * (im ? 1.0 : 0.5);  // us per byte of the 24-product form
   const double per_product = 8.0 * double(k) * launch + 128.0 * gb * (double(m) + double(n)) * double(k) +
                              0.6 * 576.0 * gb * double(m) * double(n);

@@ -824,6 +824,8 @@ static const TileConfig kConfigs[] = {
     {0, 0, 0, 0, 0},         // 10: retired (as 9, two-deep)
     {128, 128, 32, 32, 32},  // 11: 16 waves, 4 waves / SIMD, one block per CU (real x real only)
     {0, 0, 0, 0, 0},         // 12: retired (8 waves of 32 x 16, 4 waves / SIMD: slower, 2.4x the L2 misses)
+    {0, 0, 0, 0, 0},         // 13: the batched plans' one-launch configuration (bq_fused.hip)
+    {32, 32, 16, 16, 16},    // 14: 4 waves of 16 x 16, 4 waves / SIMD (products that leave 64 x 64 tiles short)
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 
@@ -837,15 +839,45 @@ TileConfig tile_config(int cfg) { return kConfigs[cfg]; }
 // 4 small tiles per large one at 1.12x the rate, so a round of large blocks
 // costs 2 / 1.12 rounds of small ones.  The complex kinds keep BK = 16,
 // which leaves room for two blocks per CU.
+//
+// Products with few 64 x 64 tiles take 32 x 32 ones (four times the blocks, a
+// quarter of the chain each), by the time of a launch per unit of k, in us: a
+// round of 256 small tiles 0.033 (complex) or 0.0135 (real); 64 x 64 tiles 0.19
+// or 0.07 per round of 512, a last one of at most 256 tiles (one per CU) 0.125
+// or 0.047, a longer one 0.195 or 0.065, with edge tiles 1.12 or 1.2 times that
+// (grids of 1024 tiles and more 0.20 a round, 0.14 or 0.22 the last, edges or
+// not); 128 x 128 ones 0.125.  One complex product, 64 x 64 against 32 x 32: n =
+// 256 33 us against 13, 512 63 against 26, 800 116 against 79, 1024 129 against
+// 139, 1100 243 against 189, 1300 296 against 310, 1536 468 against 398; real 256
+// 15 against 8, 800 48 against 32, 1024 48 against 51.
+double tile_launch_cost(int kind, int cfg, int64_t m, int64_t n) {
+  constexpr int64_t kCUs = 256;
+  auto tiles = [&](int64_t t) { return ((m + t - 1) / t) * ((n + t - 1) / t); };
+  auto rounds = [&](int64_t t, int64_t per) { return double((tiles(t) + per - 1) / per); };
+  const bool real = kind == KIND_RR;
+  if (cfg == 14) return (real ? 0.0135 : 0.033) * rounds(32, kCUs);
+  if (cfg == 11) return 0.125 * rounds(128, kCUs);
+  const int64_t full = tiles(64) / (2 * kCUs), tail = tiles(64) % (2 * kCUs);
+  if (tiles(64) >= 1024)
+    return real ? 0.07 * rounds(64, 2 * kCUs)
+                : 0.20 * double(full) + (tail == 0 ? 0.0 : tail <= kCUs ? 0.14 : 0.22);
+  const double c = (real ? 0.07 : 0.19) * double(full) +
+                   (tail == 0 ? 0.0 : tail <= kCUs ? (real ? 0.047 : 0.125) : (real ? 0.065 : 0.195));
+  return m % 64 != 0 || n % 64 != 0 ? c * (real ? 1.2 : 1.12) : c;
+}
+
 int default_tile_config(int kind, int64_t m, int64_t n, int64_t k) {
   (void)k;
-  if (kind != KIND_RR) return 0;
-  constexpr int64_t kCUs = 256;
-  const int64_t t128 = ((m + 127) / 128) * ((n + 127) / 128);
-  const int64_t t64 = ((m + 63) / 64) * ((n + 63) / 64);
-  const double rounds128 = double((t128 + kCUs - 1) / kCUs) * 2.0 / 1.12;
-  const double rounds64 = double((t64 + 2 * kCUs - 1) / (2 * kCUs));
-  return rounds128 < rounds64 ? 11 : 3;
+  int big = 0;
+  if (kind == KIND_RR) {
+    constexpr int64_t kCUs = 256;
+    const int64_t t128 = ((m + 127) / 128) * ((n + 127) / 128);
+    const int64_t t64 = ((m + 63) / 64) * ((n + 63) / 64);
+    const double rounds128 = double((t128 + kCUs - 1) / kCUs) * 2.0 / 1.12;
+    const double rounds64 = double((t64 + 2 * kCUs - 1) / (2 * kCUs));
+    big = rounds128 < rounds64 ? 11 : 3;
+  }
+  return tile_launch_cost(kind, 14, m, n) < tile_launch_cost(kind, big, m, n) ? 14 : big;
 }
 
 // Byte span of the stored A and B tiles of a BM x BN x BK block below 2^31,
@@ -894,11 +926,17 @@ static hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Complex kinds take configuration 0 (64 x 64 x 16), real products 3
-// (64 x 64 x 32) or 11 (128 x 128 x 32); tile_config_for maps a request to
-// one of these, and the launcher refuses any other.
+// Complex kinds take configuration 0 (64 x 64 x 16) or 14 (32 x 32 x 16), real
+// products 3 (64 x 64 x 32), 11 (128 x 128 x 32) or 14; tile_config_for maps a
+// request to one of these, and the launcher refuses any other.
 template <int KIND>
 static hipError_t launch_kind(const GemmArgs& g, int cfg, hipStream_t s) {
+  if (cfg == 14) {
+    if (g.ta && g.tb) return launch_one<KIND, 32, 32, 16, 16, 16, 4, 1, 1>(g, s);
+    if (g.ta) return launch_one<KIND, 32, 32, 16, 16, 16, 4, 1, 0>(g, s);
+    if (g.tb) return launch_one<KIND, 32, 32, 16, 16, 16, 4, 0, 1>(g, s);
+    return launch_one<KIND, 32, 32, 16, 16, 16, 4>(g, s);
+  }
   // Transposed operands (op T or H) run the 64 x 64 x 16 tile.
   if (g.ta || g.tb) {
     if (g.ta && g.tb) return launch_one<KIND, 64, 64, 16, 32, 32, 2, 1, 1>(g, s);
@@ -925,8 +963,8 @@ static hipError_t launch_kind(const GemmArgs& g, int cfg, hipStream_t s) {
 }
 
 int tile_config_for(int kind, int requested, int64_t m, int64_t n, int64_t k) {
-  if (kind != KIND_RR) return 0;
-  return (requested == 3 || requested == 11) ? requested : default_tile_config(kind, m, n, k);
+  if (kind == KIND_RR && (requested == 3 || requested == 11)) return requested;
+  return default_tile_config(kind, m, n, k);
 }
 
 hipError_t launch_cgemm(int kind, const GemmArgs& g, int cfg, hipStream_t s) {

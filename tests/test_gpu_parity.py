@@ -540,3 +540,24 @@ def test_one_launch_products(bq, mask, m, k, n, pad, opA, opB):
     got = Cbuf.cpu().numpy()
     assert np.array_equal(got[:, :, :n], oracle.gemm(OP_FN[opA](A), OP_FN[opB](B)))
     assert np.all(got[:, :, n:] == 12345.0)
+
+
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("H", "T")])
+@pytest.mark.parametrize("m,k,n,pad", [(1, 1, 1, 0), (32, 16, 32, 0), (33, 17, 31, 1), (70, 33, 95, 0), (300, 100, 290, 1)])
+def test_small_tiles_of_single_products(bq, m, k, n, pad, opA, opB):
+    """Products with few 64 x 64 tiles run in 32 x 32 ones: complex, real and
+    real x complex products (scalar algebras and a mixed mask) on whole and
+    edge tiles, ragged k, odd and even rows; integer inputs, so the result is
+    the oracle's exactly."""
+    import torch
+
+    for ma, mb in ((0x11, 0x11), (0x01, 0x01), (0x01, 0x11), (0x33, 0x01)):
+        A, B = stored_pair(m, k, n, opA, opB, "int", seed=m + k + n + ma, bound=512)
+        A[[c for c in range(8) if not ma >> c & 1]] = 0.0
+        B[[c for c in range(8) if not mb >> c & 1]] = 0.0
+        a = torch.zeros((8, A.shape[1], A.shape[2] + pad), dtype=torch.float64, device="cuda")
+        a[:, :, :A.shape[2]] = dev(A)
+        print(f"small tiles {m}x{k}x{n} pad {pad} {opA}{opB} masks {ma:#x} {mb:#x}", flush=True)
+        C = bq.bq_gemm(a[:, :, :A.shape[2]], dev(B), opA=opA, opB=opB, mask_a=ma, mask_b=mb)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), oracle.gemm(OP_FN[opA](A), OP_FN[opB](B))), (ma, mb)
