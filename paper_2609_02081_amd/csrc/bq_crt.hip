@@ -17,6 +17,7 @@
 #include <limits.h>
 
 #include <cstdlib>
+#include <cstring>
 
 #include "bq_split_common.h"
 
@@ -146,12 +147,22 @@ __global__ void __launch_bounds__(256) crt_split(const SplitOperand x, const Spl
   else crt_split_block(y, b - xblocks);
 }
 
-// One INT8 GEMM per modulus (blockIdx.y): residue planes of X (rows padded
-// to 256) and Y (columns padded to 256) in the tiled 64-byte layout, a 128 x
-// 128 block of 4 waves (64 x 64 each, 16 v_mfma_i32_16x16x64_i8 per k-step),
-// four LDS stages filled straight from global memory three k-steps ahead,
-// every wave moving 4 of the stage's 16 KB.  The int32 result is reduced to
-// its symmetric residue and stored as a byte plane R[i][row][col].
+// One INT8 GEMM per modulus: residue planes of X (rows padded to 256) and Y
+// (columns padded to 256) in the tiled 64-byte layout.  A block of 4 waves
+// takes 256 x 128 tiles (128 x 64 a wave, 32 v_mfma_i32_16x16x64_i8 per
+// k-step) or 128 x 128 ones (64 x 64, 16), three LDS stages filled straight
+// from global memory two k-steps ahead, every wave moving a quarter of each 4
+// KB operand tile.  The int32 result is reduced to its symmetric residue and
+// stored as a byte plane R[i][row][col].
+// What bounds it: the loads into LDS.  A launch that only issues the loads of
+// 128 x 128 tiles moves 16-21 TB/s (about 26 bytes a clock and CU) and takes
+// 48 of the 64 us of n = 1535, the MFMAs alone 43; the taller tile moves 3/4
+// of the bytes per MFMA and reads 3/4 of the LDS bytes.  Two blocks a CU, each
+// with tiles in a row, overlap the fill, the epilogue (8 instructions per
+// element) and the drain.  Launches, 128 x 128 blocks of one tile against 256
+// x 128 tiles in a row: n = 1024 24.2 -> 21.8 us, 1535 64.8 -> 59.3, 2048 132
+// -> 124, 3072 (against 256 x 256) 413 -> 407; batches of 64 products of n =
+// 64..1536 37.0 -> 35.0 ms.
 // Modulus and tile of block b of the blocks [p0, p0 + N T) that run the N
 // residue GEMMs of one product (T tiles each).  Small planes: each XCD takes
 // a contiguous run over (modulus, tile), so it reads one or two moduli's
@@ -163,120 +174,162 @@ __global__ void __launch_bounds__(256) crt_split(const SplitOperand x, const Spl
 // the 256 MB cache behind the L2s.
 constexpr int64_t kCrtXcdPlane = 9 << 20;
 
-__device__ __forceinline__ void crt_gemm_tile_of(const CrtGemmArgs& g, int64_t b, int64_t p0, int nmod, int tiles_m,
+template <typename Args>
+__device__ __forceinline__ void crt_gemm_tile_of(const Args& g, int64_t b, int64_t p0, int nmod, int tiles_m,
                                                  int tiles_n, int& mod, int& tm, int& tn) {
-  const int64_t T = (int64_t)tiles_m * tiles_n;
-  int t;
+  const unsigned T = (unsigned)(tiles_m * tiles_n);  // launches hold fewer than 2^31 blocks
+  unsigned t;
   if (g.plane_a + g.plane_b <= kCrtXcdPlane) {
-    const int64_t pos = xcd_position(b, p0, p0 + T * nmod);
+    const unsigned pos = (unsigned)xcd_position(b, p0, p0 + (int64_t)T * nmod);
     mod = (int)(pos / T);
-    t = (int)(pos % T);
+    t = pos % T;
   } else {
-    mod = (int)((b - p0) / T);
-    t = (int)xcd_position(b, p0 + mod * T, p0 + (mod + 1) * T);
+    mod = (int)((unsigned)(b - p0) / T);
+    t = (unsigned)xcd_position(b, p0 + (int64_t)mod * T, p0 + (int64_t)(mod + 1) * T);
   }
-  grouped_tile(t, tiles_m, tiles_n, tm, tn);
+  grouped_tile((int)t, tiles_m, tiles_n, tm, tn);
 }
 
-constexpr int kCrtGemmLds = 4 * 4 * 64 * 64;  // four stages of two A and two B 4 KB tiles
+// 128 x 128 (WI = 4) or 256 x 128 (WI = 8) tile: 4 waves of WI x 4 MFMA tiles.
+template <int WI>
+struct CrtShape {
+  static constexpr int BM = 32 * WI, BN = 128;
+  static constexpr int TA = BM / 64, TB = BN / 64;  // 64-row operand tiles of 4 KB
+  static constexpr int NPW = TA + TB;               // 1 KB pieces of a stage per wave
+  static constexpr int NST = 3;                     // stages: two blocks fit a CU's LDS
+  static constexpr int LDS = NST * NPW * 4096;
+};
+constexpr int kCrtGemmBlocks = 512;  // two on each of 256 CUs
 
-__device__ __forceinline__ void crt_gemm_block(const CrtGemmArgs& g, int tm, int tn, int mod, unsigned char* lds) {
-  constexpr int BM = 128, BN = 128, ROWB = 64, TILE = 64 * ROWB;  // 4 KB per 64-row tile
-  constexpr int STAGE = 4 * TILE;                                  // two A tiles, two B tiles
-  constexpr int NST = 4, NPW = 4;
-  static_assert(NST * STAGE == kCrtGemmLds, "LDS size");
-  const int p = kCrtModuli[mod];
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+// One output tile: its operand rows, and where its residues go.
+struct CrtTile {
+  const unsigned char *a, *b;
+  int64_t run;  // bytes of a 64-row operand tile
+  int nk, p;
+  signed char* out;
+  int rows, cols;  // from the tile's origin on: rows of the result, bytes of a residue row
+  int64_t ldr;
+};
+
+template <int WI, typename Args>
+__device__ __forceinline__ CrtTile crt_tile(const Args& g, int64_t v, int64_t p0, int nmod) {
+  typedef CrtShape<WI> S;
+  int mod, tm, tn;
+  crt_gemm_tile_of(g, v, p0, nmod, (int)((g.m + S::BM - 1) / S::BM), (int)((g.n + S::BN - 1) / S::BN), mod, tm, tn);
+  const int64_t m0 = (int64_t)tm * S::BM, n0 = (int64_t)tn * S::BN;
+  CrtTile t;
+  t.run = g.kp * 64;
+  t.a = static_cast<const unsigned char*>(g.a) + mod * g.plane_a + m0 * g.kp;
+  t.b = static_cast<const unsigned char*>(g.b) + mod * g.plane_b + n0 * g.kp;
+  t.nk = (int)(g.kp / 64);
+  t.p = kCrtModuli[mod];
+  t.out = g.out + mod * g.plane_r + m0 * g.ldr + n0;
+  t.rows = (int)(g.m - m0 < S::BM ? g.m - m0 : S::BM);
+  t.cols = (int)(g.ldr - n0 < S::BN ? g.ldr - n0 : S::BN);
+  t.ldr = g.ldr;
+  return t;
+}
+
+// The tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the launch's total;
+// tile_at(v) is tile v.  The ring of LDS stages runs on over the tiles (each
+// has two k-steps or more): the first two k-steps of the next tile arrive
+// while the last two of this one and its epilogue run, which uses no LDS.
+template <int WI, typename Lookup>
+__device__ __forceinline__ void crt_gemm_tiles(const Lookup& tile_at, int64_t total, unsigned char* lds) {
+  typedef CrtShape<WI> S;
+  constexpr int ROWB = 64, TILE = 64 * ROWB, STAGE = S::NPW * TILE;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wm0 = (wave >> 1) * (16 * WI), wn0 = (wave & 1) * 64;
   const int fr = lane & 15, fg = lane >> 4;
 
-  const int64_t nk = g.kp / ROWB;
-  const int64_t run = nk * TILE;
-  const unsigned char* ga = static_cast<const unsigned char*>(g.a) + mod * g.plane_a + (int64_t)(2 * tm) * run;
-  const unsigned char* gb = static_cast<const unsigned char*>(g.b) + mod * g.plane_b + (int64_t)(2 * tn) * run;
-  const int nrec = (int)(uint32_t)(2 * run);
-  // 1 KB piece q of a stage: q < 8 A (tile q / 4, quarter q % 4), else B.
-  auto dma = [&](int q, int64_t kt, int st) {
-    const int side = q >> 3, t = (q >> 2) & 1, quarter = q & 3;
-    const __amdgpu_buffer_rsrc_t r =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(side ? gb : ga), (short)0, nrec, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)(lds + st * STAGE + q * 1024), 16,
-                                             (int)(t * run) + quarter * 1024 + lane * 16, (int)(kt * TILE), 0, 0);
+  // Piece i of the wave: its quarter of operand tile i (those of A first).
+  auto dma = [&](const unsigned char* ga, const unsigned char* gb, int64_t run, int i, int kt, int st) {
+    const unsigned char* src = i < S::TA ? ga + i * run : gb + (i - S::TA) * run;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, (int)run, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)(lds + st * STAGE + i * TILE + wave * 1024), 16,
+                                             wave * 1024 + lane * 16, kt * TILE, 0, 0);
   };
   auto frag = [&](const unsigned char* base, int row) {
     return *reinterpret_cast<const i4v*>(base + row * ROWB + swz_chunk<16>(row & 63, fg) * 16);
   };
 
-  i4v acc[4][4];
+  int64_t v = blockIdx.x;
+  CrtTile c = tile_at(v);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = i4v{0, 0, 0, 0};
-
-  // Prologue: k-steps 0..NST-2 (past the end: the last one again).
-#pragma unroll
-  for (int s = 0; s < NST - 1; ++s)
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) dma(wave * NPW + i, s < nk ? s : nk - 1, s);
-  wait_vm<(NST - 2) * NPW>();
+    for (int i = 0; i < S::NPW; ++i) dma(c.a, c.b, c.run, i, s, s);
+  wait_vm<S::NPW>();
   block_sync();
-  for (int64_t kt = 0; kt < nk; ++kt) {
-    const int st = (int)(kt % NST);
-    const int sn = (int)((kt + NST - 1) % NST);
-    const int64_t knext = kt + NST - 1 < nk ? kt + NST - 1 : nk - 1;
-    const unsigned char* ta = lds + st * STAGE;
-    const unsigned char* tb = ta + 2 * TILE;
-    i4v fa[4], fb[4];
+  int st = 0;
+  for (;;) {
+    const bool more = v + gridDim.x < total;
+    CrtTile n = c;  // after the last tile: loads that nothing reads
+    if (more) n = tile_at(v + gridDim.x);
+    i4v acc[WI][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fa[i] = frag(ta, wm0 + i * 16 + fr);
+    for (int i = 0; i < WI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fb[j] = frag(tb, wn0 + j * 16 + fr);
+      for (int j = 0; j < 4; ++j) acc[i][j] = i4v{0, 0, 0, 0};
+    for (int kt = 0; kt < c.nk; ++kt) {
+      const int sn = st == 0 ? 2 : st - 1;  // the stage of k-step kt - 1
+      const bool over = kt + 2 >= c.nk;
+      const unsigned char *ga = over ? n.a : c.a, *gb = over ? n.b : c.b;
+      const int64_t run = over ? n.run : c.run;
+      const int kn = over ? kt + 2 - c.nk : kt + 2;
+      const unsigned char* ta = lds + st * STAGE;
+      const unsigned char* tb = ta + S::TA * TILE;
+      i4v fa[WI], fb[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+      for (int j = 0; j < 4; ++j) fb[j] = frag(tb, wn0 + j * 16 + fr);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i], acc[i][j], 0, 0, 0);
-      dma(wave * NPW + i, knext, sn);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < WI; ++i) fa[i] = frag(ta, wm0 + i * 16 + fr);
+#pragma unroll
+      for (int i = 0; i < WI; ++i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i], acc[i][j], 0, 0, 0);
+        if (i < S::NPW) dma(ga, gb, run, i, kn, sn);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // The next stage is complete once at most the loads of this k-step are
+      // still out (the stores of an epilogue before them count as well).
+      wait_vm<S::NPW>();
+      block_sync();
+      st = st == 2 ? 0 : st + 1;
     }
-    // Stage kt + 1 is complete once at most the loads of the last two
-    // k-steps (kt + NST - 2, kt + NST - 1) are still out.
-    wait_vm<(NST - 2) * NPW>();
-    block_sync();
-  }
-  wait_vm<0>();
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  block_sync();
-
-  // Residues into a 128 x 128 byte tile in LDS (rows of OUT_LD bytes), then
-  // 16-byte row stores (columns up to ldr, a multiple of 16).
-  constexpr int OUT_LD = BN + 16;
-  static_assert(BM * OUT_LD <= kCrtGemmLds, "output tile fits the stages");
-  const double pd = (double)p, inv_p = 1.0 / pd;
+    // Residues as 16-byte stores (a residue row has a multiple of 16 bytes).
+    // The right operand goes first into the MFMA, so a lane holds four columns
+    // of a row per result: word j of lane row fg is columns 16 j + 4 fg.  A 4
+    // x 4 transpose over the lane rows makes it word fg of lane row j.
+    const double pd = (double)c.p, inv_p = 1.0 / pd;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < WI; ++i) {
+      unsigned w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      *reinterpret_cast<int*>(lds + (wm0 + i * 16 + fr) * OUT_LD + wn0 + j * 16 + 4 * fg) =
-          pack_bytes(sym_mod_rt(acc[i][j][0], pd, inv_p), sym_mod_rt(acc[i][j][1], pd, inv_p),
-                     sym_mod_rt(acc[i][j][2], pd, inv_p), sym_mod_rt(acc[i][j][3], pd, inv_p));
-  __syncthreads();
-  signed char* out = g.out + (int64_t)mod * g.plane_r;
-  for (int w = tid; w < BM * (BN / 16); w += 256) {
-    const int r = w / (BN / 16), ch = w % (BN / 16);
-    const int64_t grow = m0 + r, gcol = n0 + ch * 16;
-    if (grow < g.m && gcol < g.ldr)
-      *reinterpret_cast<i4v*>(out + grow * g.ldr + gcol) = *reinterpret_cast<const i4v*>(lds + r * OUT_LD + ch * 16);
+      for (int j = 0; j < 4; ++j)
+        w[j] = (unsigned)pack_bytes(sym_mod_rt(acc[i][j][0], pd, inv_p), sym_mod_rt(acc[i][j][1], pd, inv_p),
+                                    sym_mod_rt(acc[i][j][2], pd, inv_p), sym_mod_rt(acc[i][j][3], pd, inv_p));
+      const auto x = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+      const auto y = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+      const auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+      const int r = wm0 + i * 16 + fr, col = wn0 + fg * 16;
+      if (r < c.rows && col < c.cols)
+        *reinterpret_cast<i4v*>(c.out + r * c.ldr + col) = i4v{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+    }
+    if (!more) break;
+    v += gridDim.x;
+    c = n;
   }
+  wait_vm<0>();  // no load into LDS outlives the block
 }
 
+template <int WI>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-crt_gemm(const CrtGemmArgs g, int nmod) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kCrtGemmLds];
-  int mod, tm, tn;
-  crt_gemm_tile_of(g, blockIdx.x, 0, nmod, (int)((g.m + 127) / 128), (int)((g.n + 127) / 128), mod, tm, tn);
-  crt_gemm_block(g, tm, tn, mod, lds);
+crt_gemm(const CrtGemmArgs g, int nmod, int64_t total) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[CrtShape<WI>::LDS];
+  crt_gemm_tiles<WI>([&](int64_t v) { return crt_tile<WI>(g, v, 0, nmod); }, total, lds);
 }
 
 // The same GEMM for large products: a 256 x 256 block of 4 waves (128 x 128
@@ -668,15 +721,22 @@ __global__ void __launch_bounds__(256) crt_split_grouped(const SplitOperand* ite
   crt_split_block(a, b - prefix[i]);
 }
 
+// The tables are read through the constant address space, so that the search
+// for the next tile is scalar loads: a vector load would wait for the loads
+// into LDS that are on their way.
+template <int WI>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kCrtGemmLds];
-  const int64_t b = blockIdx.x;
-  const int i = find_item(prefix, count, b);
-  const CrtGemmArgs& g = items[i].g;
-  int mod, tm, tn;
-  crt_gemm_tile_of(g, b, prefix[i], items[i].nmod, (int)((g.m + 127) / 128), (int)((g.n + 127) / 128), mod, tm, tn);
-  crt_gemm_block(g, tm, tn, mod, lds);
+crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t total) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[CrtShape<WI>::LDS];
+  typedef const __attribute__((address_space(4))) CrtGemmItem table_item;
+  typedef const __attribute__((address_space(4))) int64_t table_prefix;
+  table_item* ti = (table_item*)items;
+  table_prefix* tp = (table_prefix*)prefix;
+  auto tile_at = [&](int64_t v) {
+    const int i = find_item(tp, count, v);
+    return crt_tile<WI>(ti[i].g, v, tp[i], ti[i].nmod);
+  };
+  crt_gemm_tiles<WI>(tile_at, total, lds);
 }
 
 template <int NG>
@@ -703,32 +763,50 @@ hipError_t launch_crt_split(const SplitOperand& x, const SplitOperand& y, hipStr
   return hipGetLastError();
 }
 
-// Block shape of the residue GEMMs: 256 x 256 once the grid holds four blocks
-// per CU (the larger block halves the bytes per MFMA), else 128 x 128: a large
-// block's fill and drain are not covered by another block on its CU.  Traced
-// launches, 128 against 256: n = 1024 (240 large blocks) 24.2 against 26.2 us,
-// 1536 (576) 63 against 78, 2048 (1024) 133 against 129, 3072 444 against 395,
-// 4096 1036 against 889.  BQ_CRT_TILE=128 or 256 overrides.
-int crt_gemm_tile(int N, int64_t m, int64_t n) {
-  const char* e = std::getenv("BQ_CRT_TILE");
-  if (e && std::atoi(e) == 128) return 128;
-  if (e && std::atoi(e) == 256) return 256;
-  const int64_t big = ((m + 255) / 256) * ((n + 255) / 256) * N;
-  return big >= 1024 ? 256 : 128;
+// Rows of the 128-column tiles of a launch that would hold `small` tiles of
+// 128 rows or `tall` of 256: the tall tile where it leaves 1.5 tiles a CU or
+// more and little padding (it takes about 1.6 times as long as the small one).
+// Launches, 128 against 256 rows: n = 512 (120 tall tiles) 9.8 against 11.8
+// us, 768 (270) 16.7 against 17.3, 1024 (480) 22.8 against 21.8, 1535 62.7
+// against 59.3, 1700 95.6 against 88.6; batches: 16 products of 1024 18.0
+// against 16.3 ms, 64 of 100 (as many tall as small) 1.02 against 1.12.
+int crt_tile_rows(int64_t small, int64_t tall) { return tall >= 384 && 8 * tall <= 5 * small ? 256 : 128; }
+
+// Tile of one product's residue GEMMs: 256 x 256 from 16 of them a CU on (a
+// third less to move into LDS, but one block a CU, whose fill and drain
+// nothing covers), else by the rule above.  256 x 128 against 256 x 256: n =
+// 2048 (1024 large tiles) 124 against 132 us, 3072 (2448) 407 against 410,
+// 3328 (2873) 524 against 520, 3584 (3332) 637 against 661, 4096 (4608) 934
+// against 918.  BQ_CRT_TILE=128, 256x128 or 256 overrides.
+enum class CrtTileShape { k128, k256x128, k256 };
+CrtTileShape crt_tile_shape(int64_t small, int64_t tall, int64_t large) {
+  if (const char* e = std::getenv("BQ_CRT_TILE")) {
+    if (std::strcmp(e, "256x128") == 0) return CrtTileShape::k256x128;
+    if (std::atoi(e) == 128) return CrtTileShape::k128;
+    if (std::atoi(e) == 256) return CrtTileShape::k256;
+  }
+  if (large >= 4096) return CrtTileShape::k256;
+  return crt_tile_rows(small, tall) == 256 ? CrtTileShape::k256x128 : CrtTileShape::k128;
+}
+
+template <int WI>
+void launch_crt_tiles(int N, const CrtGemmArgs& g, int64_t total, hipStream_t st) {
+  const int64_t grid = total < kCrtGemmBlocks ? total : kCrtGemmBlocks;
+  hipLaunchKernelGGL(crt_gemm<WI>, dim3((unsigned)grid), dim3(256), 0, st, g, N, total);
 }
 
 hipError_t launch_crt_gemm(int N, const CrtGemmArgs& g, hipStream_t st) {
   if (g.m <= 0 || g.n <= 0 || N <= 0) return hipSuccess;
-  if (N > kMaxCrtModuli || (g.ldr & 15) != 0) return hipErrorInvalidValue;
-  if (crt_gemm_tile(N, g.m, g.n) == 256) {
-    if (g.kp % 128 != 0) return hipErrorInvalidValue;  // the loop takes k-steps in pairs
-    const int64_t tiles = ((g.m + 255) / 256) * ((g.n + 255) / 256);
-    if (tiles * N > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(crt_gemm_256<4>, dim3((unsigned)(tiles * N)), dim3(256), 0, st, g, N);
-  } else {
-    const int64_t tiles = ((g.m + 127) / 128) * ((g.n + 127) / 128);
-    if (tiles * N > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(crt_gemm, dim3((unsigned)(tiles * N)), dim3(256), 0, st, g, N);
+  if (N > kMaxCrtModuli || (g.ldr & 15) != 0 || g.kp % 128 != 0) return hipErrorInvalidValue;  // two k-steps or more
+  const int64_t small = crt_gemm_blocks({g, N, 128}), tall = crt_gemm_blocks({g, N, 256});
+  const int64_t large = ((g.m + 255) / 256) * ((g.n + 255) / 256) * N;
+  const CrtTileShape shape = crt_tile_shape(small, tall, large);
+  const int64_t total = shape == CrtTileShape::k128 ? small : (shape == CrtTileShape::k256 ? large : tall);
+  if (total > 0x7fffffff) return hipErrorInvalidValue;
+  switch (shape) {
+    case CrtTileShape::k128: launch_crt_tiles<4>(N, g, total, st); break;
+    case CrtTileShape::k256x128: launch_crt_tiles<8>(N, g, total, st); break;
+    case CrtTileShape::k256: hipLaunchKernelGGL(crt_gemm_256<4>, dim3((unsigned)total), dim3(256), 0, st, g, N); break;
   }
   return hipGetLastError();
 }
@@ -762,11 +840,13 @@ hipError_t launch_crt_split_grouped(const SplitOperand* items, const int64_t* pr
   return hipGetLastError();
 }
 
-hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t blocks,
+hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t blocks, int rows,
                                    hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_gemm_grouped, dim3((unsigned)blocks), dim3(256), 0, st, items, prefix, count);
+  if (blocks > 0x7fffffff || (rows != 128 && rows != 256)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(blocks < kCrtGemmBlocks ? blocks : kCrtGemmBlocks)), block(256);
+  if (rows == 256) hipLaunchKernelGGL(crt_gemm_grouped<8>, grid, block, 0, st, items, prefix, count, blocks);
+  else hipLaunchKernelGGL(crt_gemm_grouped<4>, grid, block, 0, st, items, prefix, count, blocks);
   return hipGetLastError();
 }
 

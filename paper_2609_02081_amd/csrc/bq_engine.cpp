@@ -847,7 +847,7 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
       for (int q = 0; q < np; ++q) {
         x.out[xs[q]] = crt_da[xf[xs[q]]];
         y.out[ys[q]] = crt_db[yf[ys[q]]];
-        rec->gemms.push_back({{gemm_args(q), S}, round});
+        rec->gemms.push_back({{gemm_args(q), S, 128}, round});
       }
       rec->splits.push_back({x, round});
       rec->splits.push_back({y, round});
@@ -1435,7 +1435,7 @@ void tune_cache_store(const std::string& key, int cfg, int dyn) {
 // residue GEMMs and the reconstructions (one launch per modulus count).
 struct CrtLaunch {
   enum Type { PRE, EXP, SPLIT, GEMM, COMBINE } type;
-  int N;
+  int N;  // GEMM: rows of a tile, COMBINE: moduli
   int count;
   int64_t blocks;
   size_t items, prefix;  // byte offsets into the table buffer
@@ -1486,7 +1486,16 @@ void crt_tables(const CrtRecord& rec, std::vector<char>* bytes, std::vector<CrtL
     std::vector<bq::CrtGemmItem> gm;
     for (const auto& x : rec.gemms)
       if (x.round == r) gm.push_back(x.it);
-    add(CrtLaunch::GEMM, 0, gm, [](const bq::CrtGemmItem& it) { return bq::crt_gemm_blocks(it); });
+    int64_t small = 0, tall = 0;
+    for (auto& it : gm) {
+      it.rows = 256;
+      tall += bq::crt_gemm_blocks(it);
+      it.rows = 128;
+      small += bq::crt_gemm_blocks(it);
+    }
+    const int tile_rows = bq::crt_tile_rows(small, tall);
+    for (auto& it : gm) it.rows = tile_rows;
+    add(CrtLaunch::GEMM, tile_rows, gm, [](const bq::CrtGemmItem& it) { return bq::crt_gemm_blocks(it); });
     std::vector<CrtRecord::Comb> cb;
     for (const auto& x : rec.combs)
       if (x.round == r) cb.push_back(x);
@@ -1516,7 +1525,7 @@ hipError_t crt_launch(const CrtLaunch& L, const char* d, hipStream_t s) {
                                           L.blocks, s);
     case CrtLaunch::GEMM:
       return bq::launch_crt_gemm_grouped(reinterpret_cast<const bq::CrtGemmItem*>(d + L.items), prefix, L.count,
-                                         L.blocks, s);
+                                         L.blocks, L.N, s);
     case CrtLaunch::COMBINE:
       return bq::launch_crt_combine_grouped(L.N, reinterpret_cast<const bq::CrtCombineArgs*>(d + L.items), prefix,
                                             L.count, L.blocks, s);

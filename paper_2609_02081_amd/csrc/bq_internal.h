@@ -269,14 +269,17 @@ int crt_modulus(int i);
 // grid, and a block finds its item by binary search in prefix.
 //   exponents: one operand side of a complex product per item, exponent_blocks;
 //   residues:  the same items, split_blocks;
-//   GEMM:      one real product per item, 128 x 128 tiles x moduli;
+//   GEMM:      one real product per item, 128- or 256-row tiles (one height
+//              per launch) x moduli;
 //   combine:   one complex product per item (all items one N).
 struct CrtGemmItem {
   CrtGemmArgs g;
   int nmod;
+  int rows;  // of a 128-column tile: 128 or 256
 };
+int crt_tile_rows(int64_t small, int64_t tall);
 inline int64_t crt_gemm_blocks(const CrtGemmItem& it) {
-  return ((it.g.m + 127) / 128) * ((it.g.n + 127) / 128) * it.nmod;
+  return ((it.g.m + it.rows - 1) / it.rows) * ((it.g.n + 127) / 128) * it.nmod;
 }
 int64_t crt_combine_blocks(const CrtCombineArgs& c);
 hipError_t launch_exponents_grouped(const SplitOperand* items, const int64_t* prefix, int count, int64_t blocks,
@@ -284,7 +287,7 @@ hipError_t launch_exponents_grouped(const SplitOperand* items, const int64_t* pr
 hipError_t launch_crt_split_grouped(const SplitOperand* items, const int64_t* prefix, int count, int64_t blocks,
                                     hipStream_t s);
 hipError_t launch_crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int64_t blocks,
-                                   hipStream_t s);
+                                   int rows, hipStream_t s);
 hipError_t launch_crt_combine_grouped(int N, const CrtCombineArgs* items, const int64_t* prefix, int count,
                                       int64_t blocks, hipStream_t s);
 // Hermitian eigenproblem kernels (bq_heev.hip).

@@ -96,7 +96,8 @@ __device__ __forceinline__ int pack_bytes(int a, int b, int c, int d) {
 }
 
 // Last item whose first block is at or before block b.
-__device__ __forceinline__ int find_item(const int64_t* prefix, int count, int64_t b) {
+template <typename Prefix>
+__device__ __forceinline__ int find_item(Prefix* prefix, int count, int64_t b) {
   int lo = 0, hi = count - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;

@@ -282,6 +282,20 @@ def test_residue_gemm_tile_order(bq, monkeypatch, m, k, n, tile):
     assert np.array_equal(got[:, rows], oracle.gemm(A[:, rows], B))
 
 
+@pytest.mark.parametrize("m,k,n", [(1, 1, 1), (128, 128, 128), (257, 129, 129), (300, 200, 70), (900, 300, 1000)])
+@pytest.mark.parametrize("tile", ["128", "256x128"])
+def test_tiles_in_a_row(bq, monkeypatch, m, k, n, tile):
+    """Tiles of 128 x 128 and 256 x 128: one tile a block, two k-steps (the
+    loads run to the next tile from the first step on), ragged rows and
+    columns, and more tiles than the 512 blocks of a launch, some with a
+    second tile and some without.  An integer product is the oracle's."""
+    monkeypatch.setenv("BQ_CRT_TILE", tile)
+    print(f"residue tiles in a row {m}x{k}x{n} tile {tile}", flush=True)
+    A, B = inputs.pair(m, k, n, "int", seed=93, bound=512)
+    rows = np.arange(0, m, max(1, m // 60))
+    assert np.array_equal(run(bq, A, B)[:, rows], oracle.gemm(A[:, rows], B))
+
+
 @pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 8, 12, 13, 16, 17])
 @pytest.mark.parametrize("m,k,n", [(5, 3, 7), (66, 130, 33), (17, 64, 18)])
 def test_modulus_groups_and_edges(bq, N, m, k, n):

@@ -173,3 +173,12 @@ def test_smallest_problem_with_fewest_products(bq):
     probs = [_problem(rng, 96, 80, 72), _problem(rng, 40, 30, 20, mask_a=0x0F, mask_b=0x0F),
              _problem(rng, 12, 10, 9, mask_a=0x11, mask_b=0x11), _problem(rng, 8, 8, 8, mask_a=0x01, mask_b=0x01)]
     _check(bq, probs).close()
+
+
+def test_tall_tiles_of_a_batch(bq):
+    """Batches whose residue GEMMs run 256 x 128 tiles (384 of them or more,
+    with little padding): many tiles a block, items of different k and ragged
+    sizes in a block's row of tiles."""
+    rng = np.random.default_rng(94)
+    sizes = [(256, 256, 256)] * 6 + [(250, 64, 300), (512, 130, 129), (500, 1030, 260), (100, 40, 70)]
+    _check(bq, [_problem(rng, *s) for s in sizes], oracle_check=False).close()
