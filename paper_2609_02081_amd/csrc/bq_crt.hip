@@ -15,6 +15,7 @@
 // rounded product of the scaled integers.  N moduli with M > 2 k 2^(2b)
 // carry b bits.
 #include <limits.h>
+#include <stddef.h>
 
 #include <cstdlib>
 #include <cstring>
@@ -505,15 +506,8 @@ constexpr CrtConstTable make_crt_const_table() {
 }
 __constant__ constexpr CrtConstTable kCrtC = make_crt_const_table();
 
-// The same pointer, opaque to the compiler: constants read through it are
-// loaded where they are used rather than all at once (more than the scalar
-// registers hold, which would spill them).
 typedef const __attribute__((address_space(4))) CrtConsts* crt_consts_ptr;
-typedef const __attribute__((address_space(4))) int* const_ints;
-__device__ __forceinline__ crt_consts_ptr reload(crt_consts_ptr p) {
-  asm volatile("" : "+s"(p));
-  return p;
-}
+typedef int i16v __attribute__((ext_vector_type(16)));
 
 // |P| 2^shift rounded to FP64 once (to nearest even): the leading 64 bits with
 // every lower bit folded into a sticky bit, converted as two exact 32-bit
@@ -531,22 +525,52 @@ __device__ __forceinline__ double u128_to_double(uint64_t hi, uint64_t lo, int s
 // P_p from its residues, T_p = P_p 2^(e + f - 2b) for the np real
 // products, sum_p coef[q][p] T_p into every target.  Thread: 4 consecutive
 // columns of one row (one 32-bit load per residue plane).  P = sum_i r_i c_i -
-// q M modulo 2^128 in integers: the residues of four moduli of an element sit
-// in one register (a byte transpose of four planes' words), so a four-byte dot
-// product adds four terms to one byte place of P; two places share a 32-bit
-// sum (|sum| < 2^28 with q M taken off), and one pass of carries leaves the
-// 16-bit limbs.  q is rint(s), s = sum_i r_i c_i / M from 23-bit fractions the
-// same way (error below 2^-12): for at most 16 moduli P may come near M / 2,
-// so a fraction of s within 2^-11 of 1/2 is settled by comparing P with M / 2
-// (M < 2^125: an estimate one off leaves P - M or P + M, both in range); with
-// more moduli |P| < 2^-6 M.  About 200 instructions an element and product;
-// FP64 sums over 32-bit parts of c_i with a conversion per residue took 330:
-// n = 4096, 16 moduli, 481 against 761 us per complex product (of which the
-// 48 planes and the targets take 220-610 at the copy rate).
+// q M modulo 2^128 in integers: the byte places of sum_i r_i c_i are a product
+// of the constants' bytes (rows) and the residues (a byte transpose of four
+// planes' words puts an element's moduli into one lane's operand), two v_mfma
+// for 64 elements; two places share a 32-bit sum (|sum| < 2^28 with q M taken
+// off), and one pass of carries leaves the 16-bit limbs.  q is rint(s), s =
+// sum_i r_i c_i / M from 23-bit fractions the same way (error below 2^-12): for
+// at most 16 moduli P may come near M / 2, so a fraction of s within 2^-11 of
+// 1/2 is settled by comparing P with M / 2 (M < 2^125: an estimate one off
+// leaves P - M or P + M, both in range); with more moduli |P| < 2^-6 M.
+// Bound by the vector instructions: 76 four-byte dot products an element and
+// real product took the matrix products' place before.  Launches: n = 1024
+// 37.4 -> 31.1 us, 1535 98 -> 88, 4096 477 -> 427 (of which the 48 planes and
+// the targets take 220-610 at the copy rate).
 constexpr int kCombineCols = 4;
 
+// The constants as left operands of v_mfma_i32_32x32x32_i8: a lane holds 16 k
+// of row (lane & 31), k being the modulus.  The results of a lane are the rows
+// 8 (u / 4) + 4 (lane / 32) + u % 4, u = 0..15, of column (lane & 31), so
+// digit 2 u + h (c in 0..15, f in 16..18) is put into the row that result u of
+// lane half h holds.  lo[i] has zeros in the other half's k: the product with
+// [i] sums the residues of the elements of lane half i alone.  top: moduli 16..19.
+template <int NG>
+struct CrtRows {
+  i4v lo[2], top[2];
+};
+
+template <int NG>
+__device__ __forceinline__ CrtRows<NG> crt_rows(int nmod) {
+  static_assert(offsetof(CrtConsts, c) == 0 && offsetof(CrtConsts, f) == 16 * 32, "digits in rows of 32 bytes");
+  const int lane = threadIdx.x & 63, row = lane & 31;
+  const int digit = 8 * (row >> 3) + 2 * (row & 3) + (row >> 2 & 1);
+  const int* k = reinterpret_cast<const int*>(&kCrtC.n[nmod]) + 8 * (digit < 19 ? digit : 0);
+  CrtRows<NG> A;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool mine = digit < 19 && (lane >> 5) == i;
+    const i4v lo = *reinterpret_cast<const i4v*>(k);
+    A.lo[i] = mine ? lo : i4v{0, 0, 0, 0};
+    A.top[i] = i4v{NG > 4 && mine ? k[4] : 0, 0, 0, 0};
+  }
+  return A;
+}
+
 template <int NG, typename Args>
-__device__ __forceinline__ void crt_values(const Args& g, int nmod, const signed char* res, int64_t off,
+__device__ __forceinline__ void crt_values(const Args& g, int nmod, const CrtRows<NG>& A, const signed char* res,
+                                           int64_t off,
                                            const int (&shift)[4], double (&out)[4]) {
   // R[e][G]: residues 4 G .. 4 G + 3 of element e.
   int R[4][NG];
@@ -565,36 +589,44 @@ __device__ __forceinline__ void crt_values(const Args& g, int nmod, const signed
     R[2][G] = (int)__builtin_amdgcn_perm(cd1, ab1, 0x05040100u);
     R[3][G] = (int)__builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
   }
-  auto dots = [&](int e, const_ints k, int acc) {
-#pragma unroll
-    for (int G = 0; G < NG; ++G) acc = __builtin_amdgcn_sdot4(R[e][G], k[G], acc, false);
-    return acc;
-  };
-  crt_consts_ptr K = reload((crt_consts_ptr)&kCrtC.n[nmod]);
-  int v[4], y[4][8];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = dots(e, K->f[1], dots(e, K->f[2], 0) << 8) + (dots(e, K->f[0], 0) >> 8);
-#pragma unroll
-  for (int h = 0; h < 8; ++h) {
-    if (h % 2 == 0) K = reload(K);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) y[e][h] = dots(e, K->c[2 * h], dots(e, K->c[2 * h + 1], 0) << 8);
-  }
-  K = reload(K);
+  const crt_consts_ptr K = (crt_consts_ptr)&kCrtC.n[nmod];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int q = (v[e] + (1 << 14)) >> 15;  // s 2^15 in v
+    i4v x{0, 0, 0, 0};
+#pragma unroll
+    for (int G = 0; G < (NG < 4 ? NG : 4); ++G) x[G] = R[e][G];
+    i16v d[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      i16v z;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) z[u] = 0;
+      d[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A.lo[i], x, z, 0, 0, 0);
+      if constexpr (NG > 4)
+        d[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A.top[i], i4v{R[e][NG - 1], 0, 0, 0}, d[i], 0, 0, 0);
+    }
+    // Digits 2 u, 2 u + 1 of this lane's element.
+    auto digits = [&](int u) { return __builtin_amdgcn_permlane32_swap((unsigned)d[0][u], (unsigned)d[1][u], false, false); };
+    int y[8];
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
-      y[e][h] += __mul24(-q, K->m16[h]);
-      if (h > 0) y[e][h] += y[e][h - 1] >> 16;
+      const auto t = digits(h);
+      y[h] = (int)t[0] + ((int)t[1] << 8);
+    }
+    const auto f0 = digits(8), f2 = digits(9);
+    const int v = ((int)f2[0] << 8) + (int)f0[1] + ((int)f0[0] >> 8);
+    const int q = (v + (1 << 14)) >> 15;  // s 2^15 in v
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+      y[h] += __mul24(-q, K->m16[h]);
+      if (h > 0) y[h] += y[h - 1] >> 16;
     }
     auto limb = [&](int j) {
-      return __builtin_amdgcn_perm((unsigned)y[e][2 * j + 1], (unsigned)y[e][2 * j], 0x05040100u);
+      return __builtin_amdgcn_perm((unsigned)y[2 * j + 1], (unsigned)y[2 * j], 0x05040100u);
     };
     uint64_t lo = ((uint64_t)limb(1) << 32) | limb(0), hi = ((uint64_t)limb(3) << 32) | limb(2);
     if constexpr (NG <= 4) {
-      if (((unsigned)(v[e] + (1 << 14) + 16) & 0x7fffu) < 32u) {
+      if (((unsigned)(v + (1 << 14) + 16) & 0x7fffu) < 32u) {
         unsigned __int128 Mu = 0;
 #pragma unroll
         for (int h = 0; h < 8; ++h) Mu |= (unsigned __int128)(unsigned)K->m16[h] << (16 * h);
@@ -623,9 +655,13 @@ __device__ __forceinline__ void crt_values(const Args& g, int nmod, const signed
 template <int NG, typename Args>
 __device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t r, int64_t c0) {
   constexpr int CC = kCombineCols;
-  if (r >= g.m || c0 >= g.n) return;
+  // A thread without columns takes the first ones and stores nothing: the
+  // matrix products need the operand rows of every lane.
+  const bool live = r < g.m && c0 < g.n;
+  if (!live) r = c0 = 0;
   const int np = g.np;
   const int64_t n = g.n;
+  const CrtRows<NG> A = crt_rows<NG>(nmod);
   double t[kCrtProducts][CC];
 #pragma unroll
   for (int p = 0; p < kCrtProducts; ++p) {
@@ -639,12 +675,13 @@ __device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t 
         eb[e] = (c0 + e < n) ? g.eb[p][c0 + e] : INT_MIN;
         shift[e] = exp_special(ea) || exp_special(eb[e]) ? 0 : ea + eb[e] - 2 * g.bits;
       }
-      crt_values<NG>(g, nmod, g.res[p], r * g.ldr + c0, shift, t[p]);
+      crt_values<NG>(g, nmod, A, g.res[p], r * g.ldr + c0, shift, t[p]);
 #pragma unroll
       for (int e = 0; e < CC; ++e)
         if (exp_special(ea) || exp_special(eb[e])) t[p][e] = exp_scaled(0.0, ea, eb[e], 0);
     }
   }
+  if (!live) return;
   // Targets in fours: their old values are loaded together before the first
   // store (the blocks of C do not overlap, which the compiler cannot know).
   // The loop stays a loop, so that the targets' arguments are read as needed.
@@ -706,7 +743,8 @@ __device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t 
 }
 
 template <int NG>
-__global__ void __launch_bounds__(256) crt_combine(const CrtCombineArgs g, int nmod) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+crt_combine(const CrtCombineArgs g, int nmod) {
   const int64_t bpr = (g.n + 256 * kCombineCols - 1) / (256 * kCombineCols);
   crt_combine_at<NG>(g, nmod, blockIdx.x / bpr, (blockIdx.x % bpr) * (256 * kCombineCols) + threadIdx.x * kCombineCols);
 }
@@ -740,8 +778,8 @@ crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int
 }
 
 template <int NG>
-__global__ void __launch_bounds__(256) crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix,
-                                                           int count, int nmod) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix, int count, int nmod) {
   const int64_t b = blockIdx.x;
   const int i = find_item(prefix, count, b);
   // thread: four columns; the quads of consecutive rows packed into the block
