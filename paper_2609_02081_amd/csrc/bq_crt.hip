@@ -534,10 +534,11 @@ __device__ __forceinline__ double u128_to_double(uint64_t hi, uint64_t lo, int s
 // at most 16 moduli P may come near M / 2, so a fraction of s within 2^-11 of
 // 1/2 is settled by comparing P with M / 2 (M < 2^125: an estimate one off
 // leaves P - M or P + M, both in range); with more moduli |P| < 2^-6 M.
-// Bound by the vector instructions: 76 four-byte dot products an element and
-// real product took the matrix products' place before.  Launches: n = 1024
-// 37.4 -> 31.1 us, 1535 98 -> 88, 4096 477 -> 427 (of which the 48 planes and
-// the targets take 220-610 at the copy rate).
+// 76 four-byte dot products an element and real product took the matrix
+// products' place before; the rare correction and the special exponents are one
+// branch for four elements, the sign none.  Launches: n = 1024 37.4 -> 31.3 us,
+// 1535 98 -> 88, 4096 477 -> 416; now near the planes' and the targets' traffic
+// (87 us at n = 1535 at the copy rate).
 constexpr int kCombineCols = 4;
 
 // The constants as left operands of v_mfma_i32_32x32x32_i8: a lane holds 16 k
@@ -590,6 +591,8 @@ __device__ __forceinline__ void crt_values(const Args& g, int nmod, const CrtRow
     R[3][G] = (int)__builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
   }
   const crt_consts_ptr K = (crt_consts_ptr)&kCrtC.n[nmod];
+  uint64_t lo[4], hi[4];
+  unsigned near[4];  // below 32: s within 2^-10 of 1/2
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     i4v x{0, 0, 0, 0};
@@ -624,27 +627,34 @@ __device__ __forceinline__ void crt_values(const Args& g, int nmod, const CrtRow
     auto limb = [&](int j) {
       return __builtin_amdgcn_perm((unsigned)y[2 * j + 1], (unsigned)y[2 * j], 0x05040100u);
     };
-    uint64_t lo = ((uint64_t)limb(1) << 32) | limb(0), hi = ((uint64_t)limb(3) << 32) | limb(2);
-    if constexpr (NG <= 4) {
-      if (((unsigned)(v + (1 << 14) + 16) & 0x7fffu) < 32u) {
-        unsigned __int128 Mu = 0;
+    lo[e] = ((uint64_t)limb(1) << 32) | limb(0);
+    hi[e] = ((uint64_t)limb(3) << 32) | limb(2);
+    near[e] = (unsigned)(v + (1 << 14) + 16) & 0x7fffu;
+  }
+  if constexpr (NG <= 4) {
+    if (min(min(near[0], near[1]), min(near[2], near[3])) < 32u) {
+      unsigned __int128 Mu = 0;
 #pragma unroll
-        for (int h = 0; h < 8; ++h) Mu |= (unsigned __int128)(unsigned)K->m16[h] << (16 * h);
-        const __int128 M = (__int128)Mu, half = (M - 1) >> 1;
-        __int128 P = (__int128)(((unsigned __int128)hi << 64) | lo);
-        if (P > half) P -= M;
-        else if (P < -half) P += M;
-        lo = (uint64_t)P;
-        hi = (uint64_t)((unsigned __int128)P >> 64);
+      for (int h = 0; h < 8; ++h) Mu |= (unsigned __int128)(unsigned)K->m16[h] << (16 * h);
+      const __int128 M = (__int128)Mu, half = (M - 1) >> 1;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        __int128 P = (__int128)(((unsigned __int128)hi[e] << 64) | lo[e]);
+        const __int128 d = P > half ? M : (P < -half ? -M : (__int128)0);
+        P -= near[e] < 32u ? d : (__int128)0;
+        lo[e] = (uint64_t)P;
+        hi[e] = (uint64_t)((unsigned __int128)P >> 64);
       }
     }
-    const bool neg = (int64_t)hi < 0;
-    if (neg) {
-      hi = ~hi + (uint64_t)(lo == 0);
-      lo = 0 - lo;
-    }
-    const double a = u128_to_double(hi, lo, shift[e]);
-    out[e] = neg ? -a : a;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    // |P| and the sign without a branch: x ^ s - s over 128 bits.
+    const uint64_t sg = (uint64_t)((int64_t)hi[e] >> 63);
+    const unsigned __int128 sw = ((unsigned __int128)sg << 64) | sg;
+    const unsigned __int128 u = ((((unsigned __int128)hi[e] << 64) | lo[e]) ^ sw) - sw;
+    const double a = u128_to_double((uint64_t)(u >> 64), (uint64_t)u, shift[e]);
+    out[e] = sg ? -a : a;
   }
 }
 
@@ -670,15 +680,20 @@ __device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t 
     if (p < np) {
       const int ea = g.ea[p][r];
       int eb[CC], shift[CC];
+      bool special = exp_special(ea);
 #pragma unroll
       for (int e = 0; e < CC; ++e) {
-        eb[e] = (c0 + e < n) ? g.eb[p][c0 + e] : INT_MIN;
-        shift[e] = exp_special(ea) || exp_special(eb[e]) ? 0 : ea + eb[e] - 2 * g.bits;
+        eb[e] = g.eb[p][c0 + e < n ? c0 + e : n - 1];
+        const bool sp = exp_special(ea) || exp_special(eb[e]);
+        special = special || sp;
+        shift[e] = sp ? 0 : ea + eb[e] - 2 * g.bits;
       }
       crt_values<NG>(g, nmod, A, g.res[p], r * g.ldr + c0, shift, t[p]);
+      if (special) {
 #pragma unroll
-      for (int e = 0; e < CC; ++e)
-        if (exp_special(ea) || exp_special(eb[e])) t[p][e] = exp_scaled(0.0, ea, eb[e], 0);
+        for (int e = 0; e < CC; ++e)
+          if (exp_special(ea) || exp_special(eb[e])) t[p][e] = exp_scaled(0.0, ea, eb[e], 0);
+      }
     }
   }
   if (!live) return;
@@ -743,7 +758,7 @@ __device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t 
 }
 
 template <int NG>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 crt_combine(const CrtCombineArgs g, int nmod) {
   const int64_t bpr = (g.n + 256 * kCombineCols - 1) / (256 * kCombineCols);
   crt_combine_at<NG>(g, nmod, blockIdx.x / bpr, (blockIdx.x % bpr) * (256 * kCombineCols) + threadIdx.x * kCombineCols);
@@ -778,7 +793,7 @@ crt_gemm_grouped(const CrtGemmItem* items, const int64_t* prefix, int count, int
 }
 
 template <int NG>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix, int count, int nmod) {
   const int64_t b = blockIdx.x;
   const int i = find_item(prefix, count, b);
