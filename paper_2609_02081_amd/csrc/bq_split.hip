@@ -56,14 +56,19 @@ struct MaxMagnitude {
 // columns (128 bytes of a stored row) by 64 row lanes.  Indices past the end
 // are clamped to the last one (a repeated element leaves the maximum), so the
 // loads of four steps are in flight together.  One launch per complex product
-// reads r and i once for three exponents; no initialisation and no atomics.
+// reads r and i once for three exponents; no initialisation and no atomics, but
+// for a long inner dimension and few blocks (CHUNK): inner elements c0 .. c1 - 1
+// only, the exponent joined to the one in memory (which starts at INT_MIN) by an
+// atomic maximum; c0 is even.
 constexpr int kExpThreads = 1024;
 struct ExpLds {
   unsigned hi[3][16][16], lo[3][16][16];  // value, wave, column
 };
-__device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b, ExpLds& red) {
+template <bool CHUNK>
+__device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b, int64_t c0, int64_t c1, ExpLds& red) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t K = a.along ? a.cols : a.rows;
+  const int64_t begin = CHUNK ? c0 : 0, end = CHUNK ? c1 : K;
   const bool want_i = a.e[1] != nullptr || a.e[2] != nullptr;
   MaxMagnitude mx[3];
   auto add = [&](double r, double i) {
@@ -76,11 +81,11 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
     const double* pr = a.r + v * a.ld;
     const double* pi = want_i ? a.i + v * a.ld : pr;
     if (a.vec && (K & 1) == 0) {
-      for (int64_t c = 2 * lane; c < K + 2 * lane; c += 512) {
+      for (int64_t c = begin + 2 * lane; c < end + 2 * lane; c += 512) {
         double2 x[4], y[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int64_t q = min(c + 128 * u, K - 2);
+          const int64_t q = min(c + 128 * u, end - 2);
           x[u] = *reinterpret_cast<const double2*>(pr + q);
           y[u] = want_i ? *reinterpret_cast<const double2*>(pi + q) : x[u];
         }
@@ -91,11 +96,11 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
         }
       }
     } else {
-      for (int64_t c = lane; c < K + lane; c += 256) {
+      for (int64_t c = begin + lane; c < end + lane; c += 256) {
         double x[4], y[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int64_t q = min(c + 64 * u, K - 1);
+          const int64_t q = min(c + 64 * u, end - 1);
           x[u] = pr[q];
           y[u] = want_i ? pi[q] : x[u];
         }
@@ -106,11 +111,11 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
   } else {
     const int64_t v = min(b * 16 + (t & 15), a.dim - 1);
     const int rl = t >> 4;
-    for (int64_t c = rl; c < K + rl; c += 256) {
+    for (int64_t c = begin + rl; c < end + rl; c += 256) {
       double x[4], y[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int64_t q = min(c + 64 * u, K - 1) * a.ld + v;
+        const int64_t q = min(c + 64 * u, end - 1) * a.ld + v;
         x[u] = a.r[q];
         y[u] = want_i ? a.i[q] : x[u];
       }
@@ -118,6 +123,13 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
       for (int u = 0; u < 4; ++u) add(x[u], y[u]);
     }
   }
+  auto put = [&](int* e, int x) {
+    if constexpr (CHUNK) {
+      if (x != INT_MIN) atomicMax(e, x);
+    } else {
+      *e = x;
+    }
+  };
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     if (!a.e[s]) continue;
@@ -125,7 +137,7 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
       mx[s].merge(__shfl_xor(mx[s].hi, o), __shfl_xor(mx[s].lo, o));
     if (a.along) {
       const int64_t v = b * 16 + wave;
-      if (lane == 0 && v < a.dim) a.e[s][v] = mx[s].exponent(a.head);
+      if (lane == 0 && v < a.dim) put(a.e[s] + v, mx[s].exponent(a.head));
     } else if (lane < 16) {
       red.hi[s][wave][lane] = mx[s].hi;
       red.lo[s][wave][lane] = mx[s].lo;
@@ -139,7 +151,7 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
       if (t >> 4 != s || !a.e[s] || b * 16 + c >= a.dim) continue;
       MaxMagnitude m;
       for (int w = 0; w < 16; ++w) m.merge(red.hi[s][w][c], red.lo[s][w][c]);
-      a.e[s][b * 16 + c] = m.exponent(a.head);
+      put(a.e[s] + b * 16 + c, m.exponent(a.head));
     }
   }
 }
@@ -148,8 +160,26 @@ __device__ __forceinline__ void exponent_block(const SplitOperand& a, int64_t b,
 __global__ void __launch_bounds__(kExpThreads) operand_exponents(const SplitOperand x, const SplitOperand y, int64_t xblocks) {
   __shared__ ExpLds red;
   const int64_t b = blockIdx.x;
-  if (b < xblocks) exponent_block(x, b, red);
-  else exponent_block(y, b - xblocks, red);
+  if (b < xblocks) exponent_block<false>(x, b, 0, 0, red);
+  else exponent_block<false>(y, b - xblocks, 0, 0, red);
+}
+
+// The same with the inner dimension (of K elements) in chunks, blockIdx.y, and
+// the launch before it, which sets the exponents to INT_MIN.
+__global__ void __launch_bounds__(kExpThreads) operand_exponents_chunked(const SplitOperand x, const SplitOperand y,
+                                                                         int64_t xblocks, int64_t K, int64_t chunk) {
+  __shared__ ExpLds red;
+  const int64_t b = blockIdx.x, c0 = blockIdx.y * chunk, c1 = min(K, c0 + chunk);
+  if (b < xblocks) exponent_block<true>(x, b, c0, c1, red);
+  else exponent_block<true>(y, b - xblocks, c0, c1, red);
+}
+__global__ void __launch_bounds__(256) clear_exponents(const SplitOperand x, const SplitOperand y) {
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    if (v < x.dim && x.e[s]) x.e[s][v] = INT_MIN;
+    if (v < y.dim && y.e[s]) y.e[s][v] = INT_MIN;
+  }
 }
 
 // The same over the items of many problems.
@@ -159,7 +189,7 @@ __global__ void __launch_bounds__(kExpThreads) operand_exponents_grouped(const S
   const int64_t b = blockIdx.x;
   const int i = find_item(prefix, count, b);
   const SplitOperand a = items[i];
-  exponent_block(a, b - prefix[i], red);
+  exponent_block<false>(a, b - prefix[i], 0, 0, red);
 }
 
 // Digits of one 64 x 64 tile (64 rows of the left factor, or columns of the
@@ -439,11 +469,33 @@ slice_gemm_dma(const SliceGemmArgs g) {
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Chunks of the inner dimension (K elements) of an exponent launch of `blocks`
+// blocks: one where the blocks occupy the card (512 fit at a time) or K is short,
+// else enough to fill it, none below kExpChunkMin elements.  A block alone reads
+// about 30 GB/s, 256 elements of the inner dimension in 2.2 us.  Whole calls, one
+// chunk against this rule: CRT 16 x 8192 x 16 (m, k, n) 1836 against 1493 us, 256
+// x 2048 x 256 (two chunks) 974 against 938, 40 x 78008 x 197 23.5 against 17.4
+// ms, 1024 x 4096 x 1024 3.73 against 3.58, 2000 x 5000 x 2000 (two chunks) 12.81
+// against 12.76; INT8 digits 256 x 16384 x 256 13.7 against 10.7.  With at least
+// 2048 elements a chunk 256 x 4096 x 256 takes 1286 us, 1206 this way.
+constexpr int64_t kExpChunkMin = 1024;
+int64_t exponent_chunks(int64_t blocks, int64_t K) {
+  return std::max<int64_t>(1, std::min<int64_t>(512 / std::max<int64_t>(1, blocks), K / kExpChunkMin));
+}
+
 hipError_t launch_exponents(const SplitOperand& x, const SplitOperand& y, hipStream_t st) {
   const int64_t xb = exponent_blocks(x), blocks = xb + exponent_blocks(y);
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(operand_exponents, dim3((unsigned)blocks), dim3(kExpThreads), 0, st, x, y, xb);
+  const int64_t K = x.along ? x.cols : x.rows, chunks = exponent_chunks(blocks, K);
+  if (chunks == 1) {
+    hipLaunchKernelGGL(operand_exponents, dim3((unsigned)blocks), dim3(kExpThreads), 0, st, x, y, xb);
+    return hipGetLastError();
+  }
+  const int64_t chunk = ((K + chunks - 1) / chunks + 511) / 512 * 512;
+  hipLaunchKernelGGL(clear_exponents, dim3((unsigned)((std::max(x.dim, y.dim) + 255) / 256)), dim3(256), 0, st, x, y);
+  hipLaunchKernelGGL(operand_exponents_chunked, dim3((unsigned)blocks, (unsigned)((K + chunk - 1) / chunk)),
+                     dim3(kExpThreads), 0, st, x, y, xb, K, chunk);
   return hipGetLastError();
 }
 

@@ -315,3 +315,56 @@ def test_modulus_groups_and_edges(bq, N, m, k, n):
         pytest.skip("too few moduli for this inner dimension")
     got = run(bq, A, B, N, mask_a=R, mask_b=R)
     assert np.array_equal(got[0], ozaki2.product(A[0], B[0], N))
+
+
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("T", "T")])
+@pytest.mark.parametrize("k", [1024, 2047, 2048, 2050, 3073, 5001])
+def test_exponents_over_a_long_inner_dimension(bq, k, opA, opB):
+    """Few rows and columns and a long inner dimension: the exponents are
+    formed in chunks of it, from 2048 elements on.  Rows and columns whose
+    largest element is the first or last of all, or lies on either side of a
+    chunk's edge, a zero row and column, denormal and huge ones; few moduli, so
+    that the rounding shows every exponent.  Every element equals the
+    oracle's."""
+    m, n, N = 17, 7, 6
+    A, B = inputs.pair(m, k, n, "uniform", seed=95 + k)
+    A, B = A * 1e-3, B * 1e-3
+    for r, c in enumerate((0, k - 1, 511, 512, 1023, min(1024, k - 1), k // 2)):
+        A[0, r, c] = 0.9
+        B[0, (k - 1 - c), r] = -0.9
+    A[0, 7] = 0.0
+    A[0, 8] *= 2.0 ** -1060
+    A[0, 9] *= 2.0 ** 400
+    B[0, :, 3] = 0.0
+    R = inputs.MASKS["real"]
+    for c in range(1, 8):
+        A[c] = B[c] = 0.0
+    print(f"crt exponents k={k} {opA}{opB}", flush=True)
+    stored = [np.ascontiguousarray(X.transpose(0, 2, 1)) if op == "T" else X for X, op in ((A, opA), (B, opB))]
+    got = run(bq, *stored, N, mask_a=R, mask_b=R, opA=opA, opB=opB)
+    assert np.array_equal(got[0], ozaki2.product(A[0], B[0], N))
+    A[0, 4, k - 2] = np.nan
+    A[0, 5, 1] = np.inf
+    got = run(bq, A, B, N, mask_a=R, mask_b=R)[0]
+    assert np.all(np.isnan(got[4:6])) and np.all(np.isfinite(np.delete(got, (4, 5), axis=0)))
+
+
+def test_a_long_inner_dimension_is_shared_by_blocks(bq):
+    """The exponents of 16 rows and 16 columns of 131072 elements: 34 MB, read
+    by many blocks (a block alone takes about 1 ms)."""
+    import torch
+
+    A = torch.rand((8, 16, 131072), dtype=torch.float64, device="cuda")
+    B = torch.rand((8, 131072, 16), dtype=torch.float64, device="cuda")
+    R = inputs.MASKS["real"]
+    for _ in range(2):
+        bq.bq_gemm(A, B, prec=PREC, mask_a=R, mask_b=R)
+    torch.cuda.synchronize()
+    bq.trace_enable(True)
+    for _ in range(5):
+        bq.bq_gemm(A, B, prec=PREC, mask_a=R, mask_b=R)
+    recs = [r for r in bq.trace_read() if r["kernel"] == "split"]
+    bq.trace_enable(False)
+    us = min(r["ms"] for r in recs[::2]) * 1e3  # exponents, residues in turn
+    print(f"exponents of 16 x 131072 and 131072 x 16: {us:.0f} us", flush=True)
+    assert len(recs) == 10 and us < 250.0
