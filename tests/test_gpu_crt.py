@@ -368,3 +368,27 @@ def test_a_long_inner_dimension_is_shared_by_blocks(bq):
     us = min(r["ms"] for r in recs[::2]) * 1e3  # exponents, residues in turn
     print(f"exponents of 16 x 131072 and 131072 x 16: {us:.0f} us", flush=True)
     assert len(recs) == 10 and us < 250.0
+
+
+def test_few_columns_reconstruct_in_few_waves(bq):
+    """20000 rows of 16 columns: a block of the reconstruction takes 1024
+    columns of one row, so three of its four waves have none and end at once
+    (0.66 ms for the eight launches of a product, 1.75 with all four at
+    work)."""
+    import torch
+
+    A = torch.rand((8, 20000, 64), dtype=torch.float64, device="cuda")
+    B = torch.rand((8, 64, 16), dtype=torch.float64, device="cuda")
+    C = bq.bq_gemm(A, B, prec=PREC)
+    torch.cuda.synchronize()
+    rows = torch.tensor([0, 1, 9999, 19999], device="cuda")
+    ref = oracle.gemm(A[:, rows].cpu().numpy(), B.cpu().numpy())
+    assert oracle.rel_frobenius(C[:, rows].cpu().numpy(), ref) <= TOL
+    bq.trace_enable(True)
+    for _ in range(5):
+        bq.bq_gemm(A, B, prec=PREC)
+    ms = [r["ms"] for r in bq.trace_read() if r["kernel"] == "crt_combine"]
+    bq.trace_enable(False)
+    total = sum(min(ms[q::8]) for q in range(8))
+    print(f"reconstruction of 20000 x 16: {total:.2f} ms", flush=True)
+    assert len(ms) == 40 and total < 1.2
