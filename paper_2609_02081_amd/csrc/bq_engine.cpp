@@ -580,6 +580,8 @@ int slice_flush(int et, int S) {
   return v > 0 ? std::min(v, bound) : bound;
 }
 
+// BQ_TILE_CONFIG: the tile configuration of the products it suits, each of
+// which then has its own launch (-1: none asked for, or no such configuration).
 int tile_override() {
   const char* e = std::getenv("BQ_TILE_CONFIG");
   if (!e || !*e) return -1;
@@ -917,8 +919,9 @@ bq_status_t execute(bq_handle_t h, const Plan& pl, const Prec& pr, const bq_matr
   bool fused = false;
   if (bq::FusedArgs fa; pr.et < 0 && k > 0 && fused_args(pl, A, B, C, out_mask, &fa)) {
     const int im = fa.a[4] != nullptr;
-    // A forced tile configuration of the real products keeps their launches.
-    const int64_t full = !im && cfg_override >= 0
+    // A forced tile configuration of the kind of the eight products keeps their
+    // launches.
+    const int64_t full = bq::tile_config_suits(im ? bq::KIND_GAUSS : bq::KIND_RR, cfg_override)
                              ? -1
                              : bq::fused_full_tiles(im, m, n, k, fa.ta, fa.tb, fa.lda, fa.ldb, fa.vec);
     if (full >= 0) {

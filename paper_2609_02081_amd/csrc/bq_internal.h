@@ -229,7 +229,9 @@ int default_tile_config(int kind, int64_t m, int64_t n, int64_t k);
 // Estimated time of one launch of configuration cfg, us per unit of k.
 double tile_launch_cost(int kind, int cfg, int64_t m, int64_t n);
 // The configuration a single product runs: the request where it suits the
-// kind (3 or 11 for real products; complex kinds ignore it), else the default.
+// kind (3, 11 or 14 for real products, 0 or 14 for complex kinds), else the
+// default.
+bool tile_config_suits(int kind, int cfg);
 int tile_config_for(int kind, int requested, int64_t m, int64_t n, int64_t k);
 // Batched form (complex x complex products only).  cfg: 0 or 6 (tile
 // configurations above); dyn: 1 = device work counter, 0 = cyclic; ops:

@@ -929,6 +929,10 @@ static hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
 // Complex kinds take configuration 0 (64 x 64 x 16) or 14 (32 x 32 x 16), real
 // products 3 (64 x 64 x 32), 11 (128 x 128 x 32) or 14; tile_config_for maps a
 // request to one of these, and the launcher refuses any other.
+bool tile_config_suits(int kind, int cfg) {
+  return cfg == 14 || (kind == KIND_RR ? cfg == 3 || cfg == 11 : cfg == 0);
+}
+
 template <int KIND>
 static hipError_t launch_kind(const GemmArgs& g, int cfg, hipStream_t s) {
   if (cfg == 14) {
@@ -963,8 +967,7 @@ static hipError_t launch_kind(const GemmArgs& g, int cfg, hipStream_t s) {
 }
 
 int tile_config_for(int kind, int requested, int64_t m, int64_t n, int64_t k) {
-  if (kind == KIND_RR && (requested == 3 || requested == 11)) return requested;
-  return default_tile_config(kind, m, n, k);
+  return tile_config_suits(kind, requested) ? requested : default_tile_config(kind, m, n, k);
 }
 
 hipError_t launch_cgemm(int kind, const GemmArgs& g, int cfg, hipStream_t s) {
