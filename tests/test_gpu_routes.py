@@ -90,3 +90,114 @@ def test_one_launch_equals_one_per_product(bq, monkeypatch, mask, config, opA, o
         assert c1 == [-1] and c8 == cs == [int(config)] * 8
         assert torch.equal(one, per), (m, k, n)
         assert torch.equal(streamed, per), (m, k, n)
+
+
+# The tests of the per-product kernels (by function, arguments), which small and
+# ordinary products reach with BQ_TILE_CONFIG only.
+import test_gpu_capture as capture  # noqa: E402
+import test_gpu_grouped as grouped  # noqa: E402
+import test_gpu_parity as parity  # noqa: E402
+import test_zz_no_alloc as noalloc  # noqa: E402
+
+OPS = [(a, b) for a in "NTCH" for b in "NTCH"]
+SMALL_PRODUCTS = [
+    *((parity.test_random_uniform, s) for s in [(256, 256, 256), (1, 1, 1), (130, 257, 67), (200, 16, 300), (64, 1000, 33)]),
+    *((parity.test_integer_bit_exact, s) for s in [(64, 64, 64), (70, 50, 45), (129, 96, 130)]),
+    *((parity.test_all_ops, s) for s in OPS),
+    *((parity.test_transposed_ops_integer_bit_exact, s) for s in [("T", "N"), ("N", "H"), ("H", "T")]),
+    *((parity.test_transposed_ops_streamed_and_masks, s) for s in [("T", "H"), ("H", "N")]),
+    (parity.test_transpose_reverses_products, ()),
+    (parity.test_streamed_equals_resident, ()),
+    (parity.test_side_stream, ()),
+    (parity.test_guard_band_untouched, ()),
+    (parity.test_nan_row_propagation, ()),
+    (noalloc.test_two_calls_second_smaller, ()),
+]
+LARGE_PRODUCTS = [
+    *(("0", parity.test_two_deep_with_edge_tiles, s) for s in [(2050, 1030, 2060), (2047, 1041, 2049)]),
+    *(("0", parity.test_large_products_odd_and_ragged_k, (k, 0xFF)) for k in (1040, 1031, 1024)),
+    *(("11", parity.test_real_products_in_large_blocks, (*s, 0x0F))
+      for s in [(2040, 1001, 2040), (4100, 96, 4100), (2048, 33, 2056)]),
+    ("0", noalloc.test_streamed_plan_and_split_form, ()),
+]
+
+
+def _name(x):
+    return x.__name__ if callable(x) else str(x)
+
+
+def _run_forced(bq, monkeypatch, config, test, args):
+    monkeypatch.setenv("BQ_TILE_CONFIG", config)
+    _, configs = traced(bq, lambda: test(bq, *args))
+    assert int(config) in configs, set(configs)
+    if config in ("0", "14"):
+        assert -1 not in configs or test is parity.test_transposed_ops_streamed_and_masks  # its mask is a real one
+
+
+@pytest.mark.parametrize("config", ["0", "14"])
+@pytest.mark.parametrize("test,args", SMALL_PRODUCTS, ids=_name)
+def test_small_products_in_a_launch_each(bq, monkeypatch, config, test, args):
+    """64 x 64 and 32 x 32 tiles of the complex products, resident and
+    streamed, plain and transposed loads, edge tiles, NaN, a side stream."""
+    _run_forced(bq, monkeypatch, config, test, args)
+
+
+@pytest.mark.parametrize("config,test,args", LARGE_PRODUCTS, ids=_name)
+def test_large_products_in_a_launch_each(bq, monkeypatch, config, test, args):
+    """The two-deep pipeline with and without edge tiles, 128 x 128 blocks of
+    real-quaternion products, the streamed plan of bq_gemm_noalloc."""
+    _run_forced(bq, monkeypatch, config, test, args)
+
+
+@pytest.mark.parametrize("order", ["0,4", "1,1", "1,16"])
+@pytest.mark.parametrize("config", ["0", "14"])
+def test_tile_orders_of_a_launch_each(bq, monkeypatch, config, order):
+    monkeypatch.setenv("BQ_TILE_ORDER", order)
+    _run_forced(bq, monkeypatch, config, parity.test_integer_bit_exact, (330, 200, 270))
+
+
+@pytest.mark.parametrize("entry", ["bq_gemm", "bq_gemm_noalloc"])
+@pytest.mark.parametrize("config", ["0", "14"])
+def test_captured_launches_of_each_product(bq, monkeypatch, config, entry):
+    """Ten launches in a captured graph, replayed with eager work between."""
+    monkeypatch.setenv("BQ_TILE_CONFIG", config)
+    capture.test_captured_product_replays(bq, entry)
+
+
+@pytest.mark.parametrize("cfg,schedule", [(0, 3), (0, 0), (6, 2), (6, 1), (13, 0)])
+@pytest.mark.parametrize("test,args", [(grouped.test_small_batch_matches_oracle_and_single_calls, ()),
+                                       (grouped.test_mixed_ops_batch, ("fp64",)),
+                                       (grouped.test_replays_identical_with_eager_work_between, ()),
+                                       *((grouped.test_uniform_op_batches, s)
+                                         for s in [("N", "N"), ("C", "T"), ("H", "C"), ("T", "H")]),
+                                       *((grouped.test_padded_operands_with_nan_padding, s)
+                                         for s in [("N", "N"), ("T", "H"), ("H", "N"), ("C", "T")])], ids=_name)
+def test_batches_in_every_configuration(bq, monkeypatch, tmp_path, test, args, cfg, schedule):
+    """Each configuration and schedule of a batched plan on batches that run
+    in one launch by default: mixed and uniform ops, NaN in the padding."""
+    _force_plans(bq, monkeypatch, tmp_path, cfg, schedule)
+    test(bq, *args)
+
+
+def _force_plans(bq, monkeypatch, tmp_path, cfg, schedule):
+    """Plans made by bq.GroupedPlan take the configuration through the tune
+    cache (the last entry of a key wins)."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("BQ_TUNE_CACHE", str(cache))
+    Plan = bq.GroupedPlan
+
+    def make(problems, **kw):
+        p = Plan(problems, **kw)
+        p.autotune()
+        p.close()
+        for prob in problems:
+            prob[2].fill_(float("nan"))
+        key = cache.read_text().splitlines()[-1].split()[0]
+        with open(cache, "a") as f:
+            f.write(f"{key} {cfg} {schedule}\n")
+        p = Plan(problems, **kw)
+        info = p.info()
+        assert (info["tile_config"], info["dynamic"], info["per_product_launches"]) == (cfg, schedule & 1, schedule >> 1)
+        return p
+
+    monkeypatch.setattr(bq, "GroupedPlan", make)
