@@ -201,3 +201,57 @@ def _force_plans(bq, monkeypatch, tmp_path, cfg, schedule):
         return p
 
     monkeypatch.setattr(bq, "GroupedPlan", make)
+
+
+def _far_rows(rng, rows, cols, ld, torch):
+    """Eight components (rows x cols) in one buffer, their rows ld apart."""
+    X = inputs.blocks(rng, rows, cols, "uniform")
+    buf = torch.zeros((rows, ld), dtype=torch.float64, device="cuda")
+    comps = [buf[:, 64 * c:64 * c + cols] for c in range(8)]
+    for c in range(8):
+        comps[c].copy_(torch.from_numpy(X[c]))
+    return X, comps
+
+
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("T", "N"), ("N", "T"), ("T", "T")])
+@pytest.mark.parametrize("ld", [4_500_000, 8_388_592, 9_000_000])
+def test_rows_far_apart(bq, monkeypatch, tmp_path, ld, opA, opB):
+    """Rows 4.5e6, 8388592 and 9e6 doubles apart, single calls and batched
+    plans.  A tile of 32 rows spans 2^31 bytes from 8388607 on, so the first two
+    run in one launch, the second with offsets up to the last that buffer loads
+    reach, and the third in a launch for each product; 64 rows span as much from
+    4.2e6 on, so that operands stored along k reach the kernels with pointer
+    loads in all three where 64 x 64 tiles are asked for.  38 rows and 35 columns
+    (two tiles of 32, the second short), against the oracle."""
+    import torch
+
+    m, k, n = 38, 40, 35
+    rng = np.random.default_rng(81)
+    a, A = _far_rows(rng, *((k, m) if opA == "T" else (m, k)), ld, torch)
+    b, B = _far_rows(rng, *((n, k) if opB == "T" else (k, n)), ld, torch)
+    ref = oracle.gemm(oracle.transpose(a) if opA == "T" else a, oracle.transpose(b) if opB == "T" else b)
+    one = ld < 8_388_607
+    print(f"rows {ld} apart, {opA}{opB}: single calls", flush=True)
+    C, configs = traced(bq, lambda: bq.bq_gemm(A, B, opA=opA, opB=opB))
+    assert configs == ([-1] if one else [14] * 8)
+    assert oracle.rel_frobenius(C.cpu().numpy(), ref) <= 1e-12
+    monkeypatch.setenv("BQ_TILE_CONFIG", "0")
+    C, configs = traced(bq, lambda: bq.bq_gemm(A, B, opA=opA, opB=opB))
+    assert configs == [0] * 8
+    assert oracle.rel_frobenius(C.cpu().numpy(), ref) <= 1e-12
+    print("batched plans", flush=True)
+    C.fill_(float("nan"))
+    plan = bq.GroupedPlan([(A, B, C)], opA=opA, opB=opB)
+    assert (plan.info()["tile_config"] == 13) == one
+    plan.launch()
+    torch.cuda.synchronize()
+    assert oracle.rel_frobenius(C.cpu().numpy(), ref) <= 1e-12
+    plan.close()
+    for cfg in (0, 6):
+        with monkeypatch.context() as mp:
+            _force_plans(bq, mp, tmp_path, cfg, 3)
+            plan = bq.GroupedPlan([(A, B, C)], opA=opA, opB=opB)
+        plan.launch()
+        torch.cuda.synchronize()
+        assert oracle.rel_frobenius(C.cpu().numpy(), ref) <= 1e-12
+        plan.close()
