@@ -261,9 +261,10 @@ bq_status_t bq_grouped_plan_workspace_size(bq_grouped_plan_t plan, size_t* bytes
 /* Autotuner: times every candidate tile configuration and work schedule of
  * the FP64 plan on the given workspace and stream (synchronising it), keeps
  * the fastest, and records it in the cache file named by BQ_TUNE_CACHE (if
- * set) under a key of device architecture, CU count, precision and problem
- * sizes; a later plan with the same key reads it back at creation.  For the
- * split forms it returns BQ_OK without changes. */
+ * set) under a key of the candidates, device architecture, CU count,
+ * precision, problem sizes, transpositions and row alignment; a later plan
+ * with the same key reads it back at creation.  For the split forms it returns
+ * BQ_OK without changes. */
 bq_status_t bq_grouped_plan_autotune(bq_grouped_plan_t plan, void* ws, size_t ws_bytes, bq_stream_t stream);
 bq_status_t bq_grouped_plan_launch(bq_grouped_plan_t plan, void* ws, size_t ws_bytes, bq_stream_t stream);
 /* Chosen tile configuration (0, 6: 64 x 64 tiles with k-steps of 16, 8; 13:

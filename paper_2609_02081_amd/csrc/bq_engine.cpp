@@ -1394,6 +1394,10 @@ constexpr int kGroupedTile = 64;  // tile configurations 0 and 6 are 64 x 64
 // all eight products of a 16 x 16 or 32 x 32 tile (no schedule bits).
 constexpr int kGroupedFused = 13;
 
+// The configurations the autotuner chooses from, in the cache's keys: a choice
+// made from others (or before the keys held ops and alignment) is not taken.
+constexpr const char* kTuneCandidates = "0,6,13";
+
 void grouped_release_graph(bq_grouped_plan_t p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   p->exec = nullptr;
@@ -1953,12 +1957,16 @@ bq_status_t bq_grouped_plan_create(bq_handle_t h, int count, const bq_problem_t*
     p->ops = (i == 0 || p->ops == o) ? o : -1;
   }
 
+  // What the choice depends on: the device, the candidates, and every problem's
+  // sizes, transposed loads and whether its rows are 16-byte aligned.
   std::ostringstream key;
-  key << h->arch << ":" << h->cu_count << ":" << pr.et << ":" << pr.S << ":";
+  key << kTuneCandidates << ":" << h->arch << ":" << h->cu_count << ":" << pr.et << ":" << pr.S << ":";
   uint64_t hash = 1469598103934665603ull;
   for (int i : p->order) {
     const Plan& pl = p->plans[i];
-    const int64_t d[3] = {pl.m, pl.n, pl.k};
+    bq::FusedArgs g{};
+    (void)fused_args(pl, &p->probs[i].A, &p->probs[i].B, &p->probs[i].C, 0xFFu, &g);
+    const int64_t d[4] = {pl.m, pl.n, pl.k, int64_t(pl.ta) + 2 * int64_t(pl.tb) + 4 * int64_t(g.vec)};
     for (int64_t x : d) {
       hash ^= uint64_t(x);
       hash *= 1099511628211ull;

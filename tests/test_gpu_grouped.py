@@ -338,3 +338,52 @@ def test_one_launch_batches_equal_single_calls(bq, opA, opB, odd):
         torch.cuda.synchronize()
         assert torch.equal(C, single), shape
     plan.close()
+
+
+def test_tune_cache_keys(bq, tmp_path, monkeypatch):
+    """A cached choice holds for batches that it was made on: the key tells
+    even rows from odd ones and plain operands from transposed ones, and an
+    entry whose key has sizes alone (written when there were two
+    configurations to choose from) leaves the default."""
+    import torch
+
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("BQ_TUNE_CACHE", str(cache))
+    n, count = 64, 5
+
+    def problems(pad):
+        draw = lambda s: inputs.device_uniform(n, n + pad, s, "cuda")[:, :, :n]
+        return [(draw(70 + i), draw(80 + i), torch.empty((8, n, n), dtype=torch.float64, device="cuda"))
+                for i in range(count)]
+
+    kinds = [(problems(0), "N", "N"), (problems(1), "N", "N"), (problems(0), "H", "N"), (problems(0), "N", "T")]
+    keys = []
+    for probs, oa, ob in kinds:
+        plan = bq.GroupedPlan(probs, opA=oa, opB=ob)
+        default = plan.info()["tile_config"]
+        assert default == 13
+        plan.autotune()
+        plan.close()
+        keys.append(cache.read_text().splitlines()[-1].split()[0])
+    print(f"tune cache keys: {keys}", flush=True)
+    assert len(set(keys)) == len(keys)
+
+    # The choice 0 for the first batch is the first batch's alone.
+    cache.write_text(f"{keys[0]} 0 3\n")
+    chosen = []
+    for probs, oa, ob in kinds:
+        plan = bq.GroupedPlan(probs, opA=oa, opB=ob)
+        chosen.append(plan.info()["tile_config"])
+        plan.close()
+    assert chosen == [0, 13, 13, 13]
+
+    # A key of device, precision and sizes: FNV-1a over m, n, k.
+    h = 1469598103934665603
+    for _ in range(count):
+        for x in (n, n, n):
+            h = (h ^ x) * 1099511628211 % 2 ** 64
+    device = keys[0][keys[0].index("gfx"):].rsplit(":", 1)[0]
+    cache.write_text(f"{device}:{h:x} 0 3\n")
+    plan = bq.GroupedPlan(kinds[0][0])
+    assert plan.info()["tile_config"] == 13
+    plan.close()
