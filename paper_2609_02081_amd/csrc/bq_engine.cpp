@@ -1365,9 +1365,13 @@ struct bq_grouped_plan_s {
   int* d_counter = nullptr;
   bq::CombineArgs* d_comb = nullptr;
   int64_t* d_prefix = nullptr;
-  bq::FusedArgs* d_fused = nullptr;     // fused configuration: one entry per problem
+  // Fused configuration: tile edge per problem (in the order of `order`; empty:
+  // some problem cannot run fused), its items, and its tables, one entry per
+  // problem and per item, made when a plan first takes the configuration.
+  std::vector<int> fused_tile;
+  int fused_items = 0;
+  bq::FusedArgs* d_fused = nullptr;
   bq::FusedItem* d_fused_items = nullptr;
-  int fused_items = 0;                  // 0: some problem cannot run fused
   bq::CombineArgs* d_ht = nullptr;  // per-product schedule: Hadamard sums of P5..P8, one per problem
   int64_t* d_ht_prefix = nullptr;
   int nitems = 0;
@@ -1540,6 +1544,82 @@ hipError_t crt_launch(const CrtLaunch& L, const char* d, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// Tiles of the fused configuration (none: a problem cannot run fused): per
+// problem the tile edge with the smaller total, or 16 throughout where larger
+// tiles leave CUs idle.  *wins: whether the fused configuration is the plan's
+// default, by an estimate of both in microseconds.  Fused: a tile takes 0.206 us
+// per unit of k (32 x 32; 0.24 where rows are not 16-byte aligned) or 0.066 (16 x
+// 16) plus 3 to fill and drain, 256 at a time.  Per complex product: 8 launches of
+// 64 x 64 tiles at 0.205 us per unit of k, 512 at a time, the pre-combination
+// (128 bytes per element of A and B) and the Hadamard sums (256 per element of
+// C) at 4.8 TB/s, and the launches themselves.  Fused against per product:
+// 256 products of n = 64 114 us against 392, of 512 28.6 ms against 33.5, 64 of
+// 1024 54.4 against 59.0 and of 1023 60.0 against 60.5, 3 of 4096 161 against 161.
+void fused_plan_tiles(bq_grouped_plan_s* p, bool* wins) {
+  constexpr double kCUs = 256.0;
+  auto tiles = [&](const Plan& pl, int t) { return ((pl.m + t - 1) / t) * ((pl.n + t - 1) / t); };
+  std::vector<char> small(size_t(p->count));
+  double sum16 = 0, max16 = 0, sum = 0, mx = 0, per_product = 0, kmax = 0;
+  int64_t total = 0;
+  *wins = false;
+  for (int i = 0; i < p->count; ++i) {
+    const Plan& pl = p->plans[i];
+    bq::FusedArgs g;
+    if (!fused_args(pl, &p->probs[i].A, &p->probs[i].B, &p->probs[i].C, 0xFFu, &g) || !g.a[4] ||
+        !bq::fused_spans_fit(g.lda, g.ldb))
+      return;
+    const double k = double(pl.k), mk = double(pl.m) * k, kn = k * double(pl.n), mn = double(pl.m) * double(pl.n);
+    const double c16 = 0.066 * k + 3.0, c32 = (g.vec ? 0.206 : 0.24) * k + 3.0;  // time per tile
+    const double s16 = c16 * double(tiles(pl, 16)), s32 = c32 * double(tiles(pl, 32));
+    small[i] = s16 <= s32;
+    sum16 += s16;
+    max16 = std::max(max16, c16);
+    sum += std::min(s16, s32);
+    mx = std::max(mx, small[i] ? c16 : c32);
+    per_product += 8.0 * double(tiles(pl, 64)) * k * 0.205 / 512.0 + (128.0 * (mk + kn) + 256.0 * mn) / 4.8e6;
+    kmax = std::max(kmax, k);
+    total += tiles(pl, 16);
+  }
+  if (total > 0x7fffffff) return;
+  const double mixed = std::max(sum / kCUs, mx), all_small = std::max(sum16 / kCUs, max16);
+  *wins = std::min(mixed, all_small) + 10.0 <= std::max(per_product, 0.8 * kmax) + 80.0;
+  for (int i : p->order) {
+    p->fused_tile.push_back(all_small < mixed || small[i] ? 16 : 32);
+    p->fused_items += int(tiles(p->plans[i], p->fused_tile.back()));
+  }
+}
+
+// The tables of the fused configuration, once per plan: the items, problems in
+// order, each one's tiles in contiguous runs per XCD, and room for the problems'
+// arguments.  A plan that runs another configuration goes without: one product of
+// n = 24575 is planned in 6.2 ms with 25 MB of tables, 14.8 ms and 36 MB with these.
+hipError_t fused_tables(bq_grouped_plan_s* p) {
+  if (p->d_fused_items) return hipSuccess;
+  std::vector<bq::FusedItem> items;
+  items.reserve(size_t(p->fused_items));
+  for (size_t o = 0; o < p->fused_tile.size(); ++o) {
+    const Plan& pl = p->plans[p->order[o]];
+    const int t = p->fused_tile[o];
+    const int tm = int((pl.m + t - 1) / t), tn = int((pl.n + t - 1) / t);
+    const int64_t p0 = int64_t(items.size()), p1 = p0 + int64_t(tm) * tn;
+    for (int64_t b = p0; b < p1; ++b) {
+      bq::FusedItem it{p->order[o], t, 0, 0};
+      bq::grouped_tile(int(bq::xcd_position(b, p0, p1)), tm, tn, it.tm, it.tn);
+      items.push_back(it);
+    }
+  }
+  hipError_t e = hipSuccess;
+  if (!p->d_fused) e = hipMalloc(&p->d_fused, sizeof(bq::FusedArgs) * size_t(p->count));
+  if (e == hipSuccess) e = hipMalloc(&p->d_fused_items, sizeof(bq::FusedItem) * items.size());
+  if (e == hipSuccess)
+    e = hipMemcpy(p->d_fused_items, items.data(), sizeof(bq::FusedItem) * items.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    (void)hipFree(p->d_fused_items);  // none, or unfilled
+    p->d_fused_items = nullptr;
+  }
+  return e;
+}
+
 // Host tables of an FP64 plan for workspace ws, copied to the device, then
 // the graph [grouped pre-combination -> persistent grouped GEMM] recorded.
 bq_status_t grouped_bind(bq_grouped_plan_t p, void* ws) {
@@ -1581,6 +1661,7 @@ bq_status_t grouped_bind(bq_grouped_plan_t p, void* ws) {
       st = execute(p->h, p->plans[p->order[i]], p->pr, &q.A, &q.B, &q.C, 0xFFu, ws, false, p->cap);
     }
   } else if (p->cfg == kGroupedFused) {
+    if ((e = fused_tables(p)) != hipSuccess) return hip_fail(e, "grouped table upload");
     std::vector<bq::FusedArgs> args(size_t(p->count));
     for (int i = 0; i < p->count; ++i)
       if (!fused_args(p->plans[i], &p->probs[i].A, &p->probs[i].B, &p->probs[i].C, 0xFFu, &args[i]))
@@ -1777,67 +1858,6 @@ bq_status_t grouped_bind(bq_grouped_plan_t p, void* ws) {
   return BQ_OK;
 }
 
-// Items of the fused configuration (empty: a problem cannot run fused): per
-// problem the tile edge with the smaller total, or 16 throughout where larger
-// tiles leave CUs idle; problems in order, each one's tiles in contiguous runs
-// per XCD.  *wins: whether the fused configuration is the plan's default, by
-// an estimate of both in microseconds.  Fused: a tile takes 0.206 us per unit
-// of k (32 x 32; 0.24 where rows are not 16-byte aligned) or 0.066 (16 x 16)
-// plus 3 to fill and drain, 256 at a time.  Per complex product: 8 launches of
-// 64 x 64 tiles at 0.205 us per unit of k, 512 at a time, the pre-combination
-// (128 bytes per element of A and B) and the Hadamard sums (256 per element of
-// C) at 4.8 TB/s, and the launches themselves.  Fused against per product:
-// 256 products of n = 64 114 us against 392, of 512 28.6 ms against 33.5, 64 of
-// 1024 54.4 against 59.0 and of 1023 60.0 against 60.5, 3 of 4096 161 against 161.
-std::vector<bq::FusedItem> fused_plan_items(const bq_grouped_plan_s* p, bool* wins) {
-  std::vector<bq::FusedItem> items;
-  constexpr double kCUs = 256.0;
-  auto tiles = [&](const Plan& pl, int t) { return ((pl.m + t - 1) / t) * ((pl.n + t - 1) / t); };
-  struct Choice {
-    double c16, c32;  // time per tile
-    bool small;
-  };
-  std::vector<Choice> ch(size_t(p->count));
-  double sum16 = 0, max16 = 0, sum = 0, mx = 0, per_product = 0, kmax = 0;
-  int64_t total = 0;
-  *wins = false;
-  for (int i = 0; i < p->count; ++i) {
-    const Plan& pl = p->plans[i];
-    bq::FusedArgs g;
-    if (!fused_args(pl, &p->probs[i].A, &p->probs[i].B, &p->probs[i].C, 0xFFu, &g) || !g.a[4] ||
-        !bq::fused_spans_fit(g.lda, g.ldb))
-      return items;
-    const double k = double(pl.k), mk = double(pl.m) * k, kn = k * double(pl.n), mn = double(pl.m) * double(pl.n);
-    Choice& c = ch[i];
-    c.c16 = 0.066 * k + 3.0;
-    c.c32 = (g.vec ? 0.206 : 0.24) * k + 3.0;
-    const double s16 = c.c16 * double(tiles(pl, 16)), s32 = c.c32 * double(tiles(pl, 32));
-    c.small = s16 <= s32;
-    sum16 += s16;
-    max16 = std::max(max16, c.c16);
-    sum += std::min(s16, s32);
-    mx = std::max(mx, c.small ? c.c16 : c.c32);
-    per_product += 8.0 * double(tiles(pl, 64)) * k * 0.205 / 512.0 + (128.0 * (mk + kn) + 256.0 * mn) / 4.8e6;
-    kmax = std::max(kmax, k);
-    total += tiles(pl, 16);
-  }
-  if (total > 0x7fffffff) return items;
-  const double mixed = std::max(sum / kCUs, mx), all_small = std::max(sum16 / kCUs, max16);
-  *wins = std::min(mixed, all_small) + 10.0 <= std::max(per_product, 0.8 * kmax) + 80.0;
-  for (int i : p->order) {
-    const Plan& pl = p->plans[i];
-    const int t = all_small < mixed || ch[i].small ? 16 : 32;
-    const int tm = int((pl.m + t - 1) / t), tn = int((pl.n + t - 1) / t);
-    const int64_t p0 = int64_t(items.size()), p1 = p0 + int64_t(tm) * tn;
-    for (int64_t b = p0; b < p1; ++b) {
-      bq::FusedItem it{i, t, 0, 0};
-      bq::grouped_tile(int(bq::xcd_position(b, p0, p1)), tm, tn, it.tm, it.tn);
-      items.push_back(it);
-    }
-  }
-  return items;
-}
-
 bq_status_t grouped_check_ws(bq_grouped_plan_t p, void* ws, size_t ws_bytes) {
   if (ws_bytes < p->ws_bytes)
     return fail(BQ_ERR_WORKSPACE, "workspace " + std::to_string(ws_bytes) + " B < " + std::to_string(p->ws_bytes) + " B");
@@ -1975,9 +1995,7 @@ bq_status_t bq_grouped_plan_create(bq_handle_t h, int count, const bq_problem_t*
   key << std::hex << hash;
   p->tune_key = key.str();
   bool fused_wins = false;
-  const std::vector<bq::FusedItem> fused =
-      pr.et < 0 ? fused_plan_items(p, &fused_wins) : std::vector<bq::FusedItem>();
-  p->fused_items = int(fused.size());
+  if (pr.et < 0) fused_plan_tiles(p, &fused_wins);
   if (fused_wins) {
     p->cfg = kGroupedFused;
     p->dyn = 0;
@@ -2022,12 +2040,7 @@ bq_status_t bq_grouped_plan_create(bq_handle_t h, int count, const bq_problem_t*
     if (e == hipSuccess) e = hipMalloc(&p->d_ht_prefix, sizeof(int64_t) * size_t(count));
     if (e == hipSuccess)
       e = hipMemcpy(p->d_items, items.data(), sizeof(bq::GroupedItem) * items.size(), hipMemcpyHostToDevice);
-    if (p->fused_items > 0) {
-      if (e == hipSuccess) e = hipMalloc(&p->d_fused, sizeof(bq::FusedArgs) * size_t(count));
-      if (e == hipSuccess) e = hipMalloc(&p->d_fused_items, sizeof(bq::FusedItem) * fused.size());
-      if (e == hipSuccess)
-        e = hipMemcpy(p->d_fused_items, fused.data(), sizeof(bq::FusedItem) * fused.size(), hipMemcpyHostToDevice);
-    }
+    if (e == hipSuccess && p->cfg == kGroupedFused) e = fused_tables(p);
   }
   if (e == hipSuccess && pr.et == 3 && count > 0) {
     // Table sizes do not depend on the workspace address: record against a

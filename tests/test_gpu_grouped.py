@@ -387,3 +387,54 @@ def test_tune_cache_keys(bq, tmp_path, monkeypatch):
     plan = bq.GroupedPlan(kinds[0][0])
     assert plan.info()["tile_config"] == 13
     plan.close()
+
+
+def test_tables_of_the_configuration_in_use(bq, tmp_path, monkeypatch):
+    """A plan holds the item table of the one-launch tiles only once it runs
+    them: one product of odd rows, n = 16383, takes configuration 0, whose items
+    (nine for each 64 x 64 tile, 16 bytes) are 9.4 MB; the one-launch items would
+    be 4.2 MB more.  Small odd batches take 0 by their cache entry and 13 by the
+    autotuner afterwards, with the same products."""
+    import torch
+
+    n = 16383
+    A = torch.empty((8, n, n), dtype=torch.float64, device="cuda")
+    C = torch.empty_like(A)
+    bq.GroupedPlan(_batch(SMALL[:1], 66)).close()  # the library's own memory, from its first plan on
+    torch.cuda.synchronize()
+    print(f"plan of one product, n = {n}", flush=True)
+    before = torch.cuda.mem_get_info()[0]
+    plan = bq.GroupedPlan([(A, A, C)])
+    used = before - torch.cuda.mem_get_info()[0]
+    assert plan.info()["tile_config"] == 0
+    plan.close()
+    del A, C
+    print(f"{used / 1e6:.1f} MB", flush=True)
+    assert used < 14.5e6
+
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("BQ_TUNE_CACHE", str(cache))
+    probs = _batch(SMALL[:4], 67)
+    plan = bq.GroupedPlan(probs)
+    plan.autotune()
+    plan.close()
+    key = cache.read_text().split()[0]
+    cache.write_text(f"{key} 0 3\n")
+    plan = bq.GroupedPlan(probs)
+    assert plan.info()["tile_config"] == 0
+    plan.launch()
+    torch.cuda.synchronize()
+    ref = [C.clone() for (_, _, C) in probs]
+    cache.write_text(f"{key} 13 0\n")
+    other = bq.GroupedPlan(probs)
+    assert other.info()["tile_config"] == 13
+    for p in (other, plan):
+        for (_, _, C) in probs:
+            C.fill_(float("nan"))
+        if p is plan:
+            p.autotune()  # its first use of configuration 13, or a choice among all
+        p.launch()
+        torch.cuda.synchronize()
+        for r, (_, _, C) in zip(ref, probs):
+            assert oracle.rel_frobenius(C.cpu().numpy(), r.cpu().numpy()) <= 1e-15
+        p.close()
