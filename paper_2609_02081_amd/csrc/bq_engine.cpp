@@ -1402,6 +1402,11 @@ constexpr int kGroupedFused = 13;
 // made from others (or before the keys held ops and alignment) is not taken.
 constexpr const char* kTuneCandidates = "0,6,13";
 
+// Work items of the plan's configuration.
+int grouped_work_items(const bq_grouped_plan_s* p) {
+  return p->pr.et < 0 && p->cfg == kGroupedFused ? p->fused_items : p->nitems;
+}
+
 void grouped_release_graph(bq_grouped_plan_t p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   p->exec = nullptr;
@@ -2076,7 +2081,7 @@ bq_status_t bq_grouped_plan_info(bq_grouped_plan_t plan, int* tile_config, int* 
   if (!plan) return fail(BQ_ERR_INVALID_VALUE, "plan is null");
   if (tile_config) *tile_config = plan->cfg;
   if (dynamic_schedule) *dynamic_schedule = plan->dyn;
-  if (work_items) *work_items = plan->pr.et < 0 && plan->cfg == kGroupedFused ? plan->fused_items : plan->nitems;
+  if (work_items) *work_items = grouped_work_items(plan);
   return BQ_OK;
 }
 
@@ -2092,8 +2097,8 @@ bq_status_t bq_grouped_plan_launch(bq_grouped_plan_t plan, void* ws, size_t ws_b
     if (st != BQ_OK) return st;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Tracer tr(plan->h, s, BQ_KERNEL_GROUPED, plan->pr.et >= 0 ? plan->pr.S : plan->cfg, plan->count, plan->nitems, 0,
-            plan->flops, 0.0);
+  Tracer tr(plan->h, s, BQ_KERNEL_GROUPED, plan->pr.et >= 0 ? plan->pr.S : plan->cfg, plan->count,
+            grouped_work_items(plan), 0, plan->flops, 0.0);
   hipError_t e = hipGraphLaunch(plan->exec, s);
   tr.done();
   if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");

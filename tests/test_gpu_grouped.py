@@ -438,3 +438,26 @@ def test_tables_of_the_configuration_in_use(bq, tmp_path, monkeypatch):
         for r, (_, _, C) in zip(ref, probs):
             assert oracle.rel_frobenius(C.cpu().numpy(), r.cpu().numpy()) <= 1e-15
         p.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "split_int8_crt"])
+def test_traced_launch_names_the_plans_work_items(bq, prec):
+    """The trace record of a launch has the problem count and the work items
+    that the plan reports (of the one-launch tiles, where it runs them)."""
+    import torch
+
+    probs = _batch(SMALL[:5], 68)
+    plan = bq.GroupedPlan(probs, prec=prec)
+    info = plan.info()
+    plan.launch()
+    torch.cuda.synchronize()
+    bq.trace_read()
+    bq.trace_enable(True)
+    plan.launch()
+    recs = bq.trace_read()
+    bq.trace_enable(False)
+    plan.close()
+    print(f"{prec}: {info}", flush=True)
+    assert [(r["kernel"], r["m"], r["n"]) for r in recs] == [("grouped", len(probs), info["work_items"])]
+    if prec == "fp64":
+        assert info["tile_config"] == recs[0]["config"] == 13
