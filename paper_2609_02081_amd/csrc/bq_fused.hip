@@ -59,6 +59,13 @@ __device__ __forceinline__ int plane_at(int r, int k) {
   return ((k >> 2) * (T / 16) + (r >> 4)) * 64 + (k & 3) * 16 + (row_at(r) ^ slot_flip(r, k));
 }
 
+// sum + coef * P, the product rounded before it is added, as in the per-product
+// path (it is exact but for denormals).
+__device__ __forceinline__ double add_product(double sum, double coef, double P) {
+#pragma clang fp contract(off)
+  return sum + coef * P;
+}
+
 template <int... I, typename F>
 __device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, F&& f) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -353,7 +360,7 @@ __device__ __forceinline__ void fused_block(const Args& g, int tm, int tn, doubl
     const double* s = lds + pt * T * T + e;
     double val = g.cd[w] * s[w * NPART * T * T];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) val = __builtin_fma(g.ch[w][q], s[(4 + q) * NPART * T * T], val);
+    for (int q = 0; q < 4; ++q) val = add_product(val, g.ch[w][q], s[(4 + q) * NPART * T * T]);
     double* dst = g.c[comp];
     if (dst && r < g.m && c < g.n) dst[r * g.ldc + c] = val;
   }

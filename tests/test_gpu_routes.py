@@ -92,6 +92,27 @@ def test_one_launch_equals_one_per_product(bq, monkeypatch, mask, config, opA, o
         assert torch.equal(streamed, per), (m, k, n)
 
 
+@pytest.mark.parametrize("mask,config", [(0xFF, "0"), (0x0F, "14")])
+@pytest.mark.parametrize("scale", [-1072, -1060, -1022])
+def test_routes_agree_on_denormals(bq, monkeypatch, mask, config, scale):
+    """Products among the denormals, where a quarter of a product of the
+    Hadamard part rounds: both routes round it before they add it."""
+    import torch
+
+    m, k, n = 45, 30, 50
+    A, B = inputs.pair(m, k, n, "normal", seed=15, mask_a=mask, mask_b=mask)
+    a, b = torch.from_numpy(A).to("cuda") * 2.0 ** (scale + 1000), torch.from_numpy(B).to("cuda") * 2.0 ** -1000
+    a, b = a.contiguous(), b.contiguous()
+    print(f"denormal products 2^{scale} mask {mask:#x} config {config}", flush=True)
+    monkeypatch.delenv("BQ_TILE_CONFIG", raising=False)
+    one, c1 = traced(bq, lambda: bq.bq_gemm(a, b, mask_a=mask, mask_b=mask))
+    monkeypatch.setenv("BQ_TILE_CONFIG", config)
+    per, c8 = traced(bq, lambda: bq.bq_gemm(a, b, mask_a=mask, mask_b=mask))
+    assert c1 == [-1] and c8 == [int(config)] * 8
+    assert torch.equal(one, per)
+    assert bool((one[:4] != 0).any())
+
+
 # The tests of the per-product kernels (by function, arguments), which small and
 # ordinary products reach with BQ_TILE_CONFIG only.
 import test_gpu_capture as capture  # noqa: E402
