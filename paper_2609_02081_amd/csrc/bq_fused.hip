@@ -429,11 +429,16 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 // measured on an MI355X at m = n = k = 64 .. 4096.  One round is one block on
 // each of the 256 CUs (fused) or two (per product).
 //   fused   a round of 32 x 32 blocks takes 0.213 us per unit of k (24 real
-//           products) or 0.0755 (8), with rows that are not 16-byte aligned
-//           0.255 and 0.0815; of 16 x 16 blocks 0.066 and 0.028.  A last round
-//           of r tiles runs as 4 r quarters where that takes less, up to half
-//           a round: 1000 x 777 x 515 (544 tiles) 478 -> 390 us, n = 800 500 ->
-//           438, n = 2300 10.38 -> 10.05 ms.
+//           products; 0.203-0.216 measured) or 0.0755 (8; 0.070-0.077), with
+//           rows that are not 16-byte aligned 0.255 or 0.0825, and the latter
+//           0.0885 where A and B together exceed 1.5 times the 256 MB cache
+//           behind the L2s (n = 2301, 339 MB, 0.0825; 2701, 467 MB, 0.087; 3001,
+//           576 MB, 0.089).  24 products take 0.223-0.227 below that (n = 1023 to
+//           1535) and 0.248-0.255 above; with either the smaller ones run in one
+//           launch.  A round of 16 x 16 blocks takes 0.066 and 0.028.  A last
+//           round of r tiles runs as 4 r quarters where that takes less, up to
+//           half a round: 1000 x 777 x 515 (544 tiles) 478 -> 390 us, n = 800 500
+//           -> 438, n = 2300 10.38 -> 10.05 ms.
 //   per     each of 8 launches as tile_launch_cost estimates it (0.20 us per
 //   product unit of k and full round of 512 64 x 64 tiles of a complex product).
 //           Plus the pre-combination (16 blocks read and 16
@@ -441,13 +446,17 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 //           0.6 exposed.
 // Fused against per product: n = 256 23 us against 365, 1024 841 against 1204,
 // 2048 6.67 ms against 7.17, 3000 21.6 against 23.0; 3500 35.9 against 35.2 and
-// 4096 52.9 against 51.7; odd rows 3001 26.8 against 23.7.
+// 4096 52.9 against 51.7; odd rows 2301 11.8 against 12.6, 3001 26.5 against 23.7.
+// Real quaternions: 1024 314 us against 514, 3000 7.65 ms against 8.38, odd rows
+// 2301 3.86 against 4.70, 3001 9.37 against 8.77.
 int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec) {
   constexpr int64_t kCUs = 256;
   auto tiles = [&](int64_t t) { return ((m + t - 1) / t) * ((n + t - 1) / t); };
   auto rounds = [&](int64_t t, int64_t per) { return (tiles(t) + per - 1) / per; };
   if (!fused_spans_fit(lda, ldb) || tiles(32) > 0x1fffffff) return -1;
-  const double c16 = im ? 0.066 : 0.028, c32 = im ? (vec ? 0.213 : 0.255) : (vec ? 0.0755 : 0.0815);
+  const bool past_cache = (im ? 64.0 : 32.0) * double(k) * (double(m) + double(n)) > 1.5 * 268435456.0;
+  const double c16 = im ? 0.066 : 0.028;
+  const double c32 = im ? (vec ? 0.213 : 0.255) : (vec ? 0.0755 : past_cache ? 0.0885 : 0.0825);
   const int64_t t32 = tiles(32), whole = t32 / kCUs * kCUs;
   // All in 32 x 32 tiles, the last round in quarters (those outside C end at
   // once), or all in 16 x 16 tiles.
