@@ -428,35 +428,64 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 // Which path a product takes: an estimate of both in microseconds, from rates
 // measured on an MI355X at m = n = k = 64 .. 4096.  One round is one block on
 // each of the 256 CUs (fused) or two (per product).
-//   fused   a round of 32 x 32 blocks takes 0.213 us per unit of k (24 real
-//           products; 0.203-0.216 measured) or 0.0755 (8; 0.070-0.077), with
-//           rows that are not 16-byte aligned 0.255 or 0.0825, and the latter
-//           0.0885 where A and B together exceed 1.5 times the 256 MB cache
-//           behind the L2s (n = 2301, 339 MB, 0.0825; 2701, 467 MB, 0.087; 3001,
-//           576 MB, 0.089).  24 products take 0.223-0.227 below that (n = 1023 to
-//           1535) and 0.248-0.255 above; with either the smaller ones run in one
-//           launch.  A round of 16 x 16 blocks takes 0.066 and 0.028.  A last
-//           round of r tiles runs as 4 r quarters where that takes less, up to
-//           half a round: 1000 x 777 x 515 (544 tiles) 478 -> 390 us, n = 800 500
-//           -> 438, n = 2300 10.38 -> 10.05 ms.
-//   per     each of 8 launches as tile_launch_cost estimates it (0.20 us per
-//   product unit of k and full round of 512 64 x 64 tiles of a complex product).
+//   fused   a round of 32 x 32 blocks takes, per unit of k, kRound us: past the
+//           cache by how A and B are stored and by their rows (where A or B have
+//           odd rows, both are loaded 8 bytes at a time; such loads of an A that is
+//           stored along k cost most), else by its first orientation and whether
+//           rows are odd.  24 products: past the cache 0.201-0.213 with rows of
+//           whole 64-byte lines, 0.216 with other even ones (N N, N T), 0.214-0.276
+//           with odd ones; n = 1024 and 1280 0.204-0.208 and 0.210-0.243.  8
+//           products: 0.069-0.075, and 0.079-0.089 with odd rows (n = 3008; 0.077-
+//           0.082 at 2304, 340 MB).  A round of 16 x 16 blocks takes 0.066 and
+//           0.028.  A last round of r tiles runs as 4 r quarters where that takes
+//           less, up to half a round: 1000 x 777 x 515 (544 tiles) 478 -> 390 us,
+//           n = 800 500 -> 438, n = 2300 10.38 -> 10.05 ms.
+//   per     each of 8 launches as tile_launch_cost estimates it for one alone, or
+//   product for the 64 x 64 tiles of grids of 1024 of them and more, which follow
+//           each other, by the rounds and ends of kLaunch and kEnds (24 products,
+//           op N N: within 1 % of n = 2048 .. 4096 in steps of 64; with edge tiles
+//           1.04 times that, 1.03 to 1.09 measured; 8 products: 3 % mostly).
 //           Plus the pre-combination (16 blocks read and 16
 //           written) and the read-modify-write of C at 4.8 TB/s, the latter
 //           0.6 exposed.
 // Fused against per product: n = 256 23 us against 365, 1024 841 against 1204,
-// 2048 6.67 ms against 7.17, 3000 21.6 against 23.0; 3500 35.9 against 35.2 and
-// 4096 52.9 against 51.7; odd rows 2301 11.8 against 12.6, 3001 26.5 against 23.7.
-// Real quaternions: 1024 314 us against 514, 3000 7.65 ms against 8.38, odd rows
+// 2048 6.67 ms against 7.17, 3000 21.5 against 23.1, 3072 23.6 against 22.6, 3136
+// 24.5 against 25.4, 3200 26.4 against 26.0, 3334 31.3 against 30.6, 3392 30.8
+// against 30.1 (T N 30.1 against 29.0), 3500 35.4 against 35.5, 4096 53.2 against
+// 52.0; odd rows 2301 11.8 against 12.6, 2501 T N 13.7 against 15.3, N T 16.9
+// against 16.0, 3001 26.5 against 23.7.
+// Real quaternions: 1024 314 us against 514, 3000 7.65 ms against 8.38, 3456 11.5
+// against 11.3, 3520 12.1 against 13.9, 4096 18.3 against 17.4, odd rows
 // 2301 3.86 against 4.70, 3001 9.37 against 8.77.
 int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb, int64_t lda, int64_t ldb, int vec) {
   constexpr int64_t kCUs = 256;
   auto tiles = [&](int64_t t) { return ((m + t - 1) / t) * ((n + t - 1) / t); };
   auto rounds = [&](int64_t t, int64_t per) { return (tiles(t) + per - 1) / per; };
   if (!fused_spans_fit(lda, ldb) || tiles(32) > 0x1fffffff) return -1;
-  const bool past_cache = (im ? 64.0 : 32.0) * double(k) * (double(m) + double(n)) > 1.5 * 268435456.0;
-  const double c16 = im ? 0.066 : 0.028;
-  const double c32 = im ? (vec ? 0.213 : 0.255) : (vec ? 0.0755 : past_cache ? 0.0885 : 0.0825);
+  // A and B past the 256 MB cache behind the L2s (24 products slow down around 300
+  // MB: n = 1511 N T, 292 MB, 0.237, 1600 0.265; 8 between 340 and 467).
+  const bool past_cache = (im ? 64.0 : 32.0) * double(k) * (double(m) + double(n)) > (im ? 1.2 : 1.5) * 268435456.0;
+  // Rows: 0 of whole 64-byte lines, 1 16-byte aligned, 2 of A odd, 3 of B, 4 both.
+  const bool odd_a = lda % 2 != 0, odd_b = ldb % 2 != 0;
+  const int rows = vec ? (lda % 8 != 0 || ldb % 8 != 0 ? 1 : 0) : (odd_a == odd_b ? 4 : (odd_a ? 2 : 3));
+  // [A stored k x m][B stored n x k][rows]
+  constexpr double kRound24[2][2][5] = {{{0.2075, 0.2165, 0.249, 0.2275, 0.2555}, {0.2095, 0.2165, 0.2665, 0.233, 0.276}},
+                                        {{0.202, 0.202, 0.216, 0.2135, 0.2215}, {0.202, 0.2045, 0.228, 0.229, 0.236}}};
+  constexpr double kRound8[2][2][5] = {{{0.0735, 0.0755, 0.0865, 0.0795, 0.0885}, {0.0735, 0.0755, 0.0865, 0.0805, 0.0895}},
+                                       {{0.0735, 0.0755, 0.0795, 0.079, 0.0845}, {0.0735, 0.0755, 0.08, 0.0805, 0.0855}}};
+  // In the cache: [A stored k x m][odd rows].
+  constexpr double kCached24[2][2] = {{0.207, 0.235}, {0.206, 0.216}};
+  // Launches of one product on 1024 64 x 64 tiles and more: a round of 512, and the
+  // end of the last whole one, a last one of at most 256 tiles or a longer one.
+  constexpr double kEnds24[3] = {0.02, 0.122, 0.213};
+  constexpr double kLaunch24[2][2][2] = {{{1.0, 1.03}, {1.02, 1.05}}, {{0.96, 0.99}, {1.01, 1.04}}};  // [ta][tb][odd rows]
+  constexpr double kLaunch8[2][4] = {{0.07, 0.076, 0.072, 0.072}, {0.07, 0.0773, 0.0744, 0.0757}};  // [odd][2 ta + tb]
+  constexpr double kEnds8[2][2][3] = {{{0.0, 0.043, 0.1}, {0.02, 0.06, 0.08}},  // [odd][transposed]
+                                      {{0.0, 0.063, 0.1}, {0.0225, 0.075, 0.105}}};
+  const double c32 = past_cache ? (im ? kRound24 : kRound8)[ta != 0][tb != 0][rows]
+                                : (im ? kCached24[ta != 0][rows > 1] : (rows > 1 ? 0.0825 : 0.0735));
+  // Past the cache 16 x 16 blocks wait for their loads as well (n = 2067 N T 0.076).
+  const double c16 = im ? std::max(0.066, c32 / 3.6) : 0.028;
   const int64_t t32 = tiles(32), whole = t32 / kCUs * kCUs;
   // All in 32 x 32 tiles, the last round in quarters (those outside C end at
   // once), or all in 16 x 16 tiles.
@@ -468,13 +497,27 @@ int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb
   const double fused = double(k) * cost[pick];
   const int kind = im ? KIND_GAUSS : KIND_RR;
   const int cfg = default_tile_config(kind, m, n, k);
-  // Transposed real products run 64 x 64 tiles with k-steps of 16, 1.1 times as long.
-  const double launch = (!im && (ta || tb) && cfg != 14 ? 1.1 : 1.0) *
-                        tile_launch_cost(kind, (ta || tb) && cfg == 11 ? 3 : cfg, m, n);
+  const bool trans = ta || tb, odd = vec == 0, edges = m % 64 != 0 || n % 64 != 0;
+  const int64_t t64 = tiles(64), tail = t64 % 512;
+  const int end = tail == 0 ? 0 : (tail <= 256 ? 1 : 2);
+  // Transposed real products run 64 x 64 tiles with k-steps of 16.
+  const int run = !im && trans && cfg == 11 ? 3 : cfg;
+  double launch = (!im && trans && run == 3 ? 1.1 : 1.0) * tile_launch_cost(kind, run, m, n);
+  if (run == 0) {
+    const double rows24 = kLaunch24[ta != 0][tb != 0][odd];
+    launch = t64 >= 1024 ? (0.1885 * double(t64 / 512) + kEnds24[end]) * rows24 * (edges ? 1.04 : 1.0)
+                         : launch * rows24 * (odd && trans ? 1.08 : 1.0);
+  } else if (t64 >= 1024 && run == 3) {
+    launch = kLaunch8[odd][(ta ? 2 : 0) + (tb ? 1 : 0)] * double(t64 / 512) + kEnds8[odd][trans][end];
+    if (trans ? edges && !odd : k < 1024) launch *= trans ? 1.045 : 1.2;  // below 1024 without the two-deep loop
+  } else if (run == 11) {
+    launch *= odd ? 1.09 : (m % 128 != 0 || n % 128 != 0 ? 1.045 : 1.0);
+  }
   const double gb = 1e-6 / 4.8 * (im ? 1.0 : 0.5);  // us per byte of the 24-product form
   const double per_product = 8.0 * double(k) * launch + 128.0 * gb * (double(m) + double(n)) * double(k) +
                              0.6 * 576.0 * gb * double(m) * double(n);
-  return fused <= per_product ? full[pick] : -1;
+  // Where both come within 1 %, the launches of one product each.
+  return 1.01 * fused <= per_product ? full[pick] : -1;
 }
 
 hipError_t launch_grouped_fused(const FusedArgs* probs, const FusedItem* items, int nitems, hipStream_t s) {

@@ -81,6 +81,27 @@ def test_large_real_quaternions_with_odd_rows(bq, n, one):
                                 oracle.gemm(*full)) <= 1e-12
 
 
+@pytest.mark.parametrize("n,opA,opB,one", [(3072, "N", "N", False), (3136, "N", "N", True), (3392, "T", "N", False),
+                                           (2501, "T", "N", True), (2501, "N", "T", False)])
+def test_large_biquaternions_take_the_shorter_route(bq, n, opA, opB, one):
+    """Sizes where the routes lie 4 to 11 % apart (one launch against one for
+    each product: n = 3072 23.6 ms against 22.6, 3136 24.5 against 25.4, 3392
+    with A transposed 30.1 against 29.0; odd rows, 2501 with A transposed 13.7
+    against 15.3, with B transposed 16.9 against 16.0)."""
+    import torch
+
+    A = inputs.device_uniform(n, n, 18, "cuda")
+    B = inputs.device_uniform(n, n, 19, "cuda")
+    print(f"biquaternions n={n} {opA}{opB}", flush=True)
+    C, configs = traced(bq, lambda: bq.bq_gemm(A, B, opA=opA, opB=opB))
+    assert (configs == [-1]) == one, configs
+    rows, cols = torch.tensor([0, 1, 1500, n - 1], device="cuda"), torch.tensor([0, 63, 1001, n - 1], device="cuda")
+    a = (A[:, :, rows] if opA == "T" else A[:, rows]).cpu().numpy()
+    b = (B[:, cols] if opB == "T" else B[:, :, cols]).cpu().numpy()
+    ref = oracle.gemm(oracle.transpose(a) if opA == "T" else a, oracle.transpose(b) if opB == "T" else b)
+    assert oracle.rel_frobenius(C[:, rows][:, :, cols].cpu().numpy(), ref) <= 1e-12
+
+
 @pytest.mark.parametrize("mask,config", [(0xFF, "0"), (0xFF, "14"), (0x0F, "3"), (0x0F, "14")])
 @pytest.mark.parametrize("opA,opB", [("N", "N"), ("H", "N"), ("C", "T"), ("T", "H")])
 def test_one_launch_equals_one_per_product(bq, monkeypatch, mask, config, opA, opB):
