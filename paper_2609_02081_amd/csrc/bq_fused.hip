@@ -442,9 +442,10 @@ bool fused_spans_fit(int64_t lda, int64_t ldb) { return 32 * std::max(lda, ldb) 
 //           n = 800 500 -> 438, n = 2300 10.38 -> 10.05 ms.
 //   per     each of 8 launches as tile_launch_cost estimates it for one alone, or
 //   product for the 64 x 64 tiles of grids of 1024 of them and more, which follow
-//           each other, by the rounds and ends of kLaunch and kEnds (24 products,
-//           op N N: within 1 % of n = 2048 .. 4096 in steps of 64; with edge tiles
-//           1.04 times that, 1.03 to 1.09 measured; 8 products: 3 % mostly).
+//           each other, by their rounds and ends (24 products, op N N: 0.1885 us a
+//           round and kEnds24, within 1 % of n = 2048 .. 4096 in steps of 64; with
+//           edge tiles 1.05 times that, 1.03 to 1.10 measured; 8 products: kLaunch8
+//           and kEnds8, 3 % mostly).
 //           Plus the pre-combination (16 blocks read and 16
 //           written) and the read-modify-write of C at 4.8 TB/s, the latter
 //           0.6 exposed.
@@ -471,18 +472,21 @@ int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb
   // [A stored k x m][B stored n x k][rows]
   constexpr double kRound24[2][2][5] = {{{0.2075, 0.2165, 0.249, 0.2275, 0.2555}, {0.2095, 0.2165, 0.2665, 0.233, 0.276}},
                                         {{0.202, 0.202, 0.216, 0.2135, 0.2215}, {0.202, 0.2045, 0.228, 0.229, 0.236}}};
-  constexpr double kRound8[2][2][5] = {{{0.0735, 0.0755, 0.0865, 0.0795, 0.0885}, {0.0735, 0.0755, 0.0865, 0.0805, 0.0895}},
+  constexpr double kRound8[2][2][5] = {{{0.0735, 0.0755, 0.0865, 0.0795, 0.0885}, {0.0735, 0.0755, 0.0865, 0.0805, 0.088}},
                                        {{0.0735, 0.0755, 0.0795, 0.079, 0.0845}, {0.0735, 0.0755, 0.08, 0.0805, 0.0855}}};
   // In the cache: [A stored k x m][odd rows].
   constexpr double kCached24[2][2] = {{0.207, 0.235}, {0.206, 0.216}};
   // Launches of one product on 1024 64 x 64 tiles and more: a round of 512, and the
   // end of the last whole one, a last one of at most 256 tiles or a longer one.
   constexpr double kEnds24[3] = {0.02, 0.122, 0.213};
-  constexpr double kLaunch24[2][2][2] = {{{1.0, 1.03}, {1.02, 1.05}}, {{0.96, 0.99}, {1.01, 1.04}}};  // [ta][tb][odd rows]
+  constexpr double kOp24[2][2] = {{1.0, 1.025}, {0.96, 1.01}};
   constexpr double kLaunch8[2][4] = {{0.07, 0.076, 0.072, 0.072}, {0.07, 0.0773, 0.0744, 0.0757}};  // [odd][2 ta + tb]
   constexpr double kEnds8[2][2][3] = {{{0.0, 0.043, 0.1}, {0.02, 0.06, 0.08}},  // [odd][transposed]
                                       {{0.0, 0.063, 0.1}, {0.0225, 0.075, 0.105}}};
-  const double c32 = past_cache ? (im ? kRound24 : kRound8)[ta != 0][tb != 0][rows]
+  // Odd rows beside rows that are no whole lines: 2878 x 1406 x 3383 0.248.
+  const bool lines_beside = rows == 2 ? ldb % 8 == 0 : lda % 8 == 0;
+  const double c32 = past_cache ? (im ? kRound24 : kRound8)[ta != 0][tb != 0][rows] +
+                                      (!ta && (rows == 2 || rows == 3) && !lines_beside ? (im ? 0.01 : 0.0065) : 0.0)
                                 : (im ? kCached24[ta != 0][rows > 1] : (rows > 1 ? 0.0825 : 0.0735));
   // Past the cache 16 x 16 blocks wait for their loads as well (n = 2067 N T 0.076).
   const double c16 = im ? std::max(0.066, c32 / 3.6) : 0.028;
@@ -504,9 +508,9 @@ int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb
   const int run = !im && trans && cfg == 11 ? 3 : cfg;
   double launch = (!im && trans && run == 3 ? 1.1 : 1.0) * tile_launch_cost(kind, run, m, n);
   if (run == 0) {
-    const double rows24 = kLaunch24[ta != 0][tb != 0][odd];
-    launch = t64 >= 1024 ? (0.1885 * double(t64 / 512) + kEnds24[end]) * rows24 * (edges ? 1.04 : 1.0)
-                         : launch * rows24 * (odd && trans ? 1.08 : 1.0);
+    const double op = kOp24[ta != 0][tb != 0];
+    launch = t64 >= 1024 ? (0.1885 * op * double(t64 / 512) + kEnds24[end]) * (odd ? 1.03 : 1.0) * (edges ? 1.05 : 1.0)
+                         : launch * op * (odd ? (trans ? 1.06 : 1.03) : 1.0);
   } else if (t64 >= 1024 && run == 3) {
     launch = kLaunch8[odd][(ta ? 2 : 0) + (tb ? 1 : 0)] * double(t64 / 512) + kEnds8[odd][trans][end];
     if (trans ? edges && !odd : k < 1024) launch *= trans ? 1.045 : 1.2;  // below 1024 without the two-deep loop
@@ -516,8 +520,8 @@ int64_t fused_full_tiles(int im, int64_t m, int64_t n, int64_t k, int ta, int tb
   const double gb = 1e-6 / 4.8 * (im ? 1.0 : 0.5);  // us per byte of the 24-product form
   const double per_product = 8.0 * double(k) * launch + 128.0 * gb * (double(m) + double(n)) * double(k) +
                              0.6 * 576.0 * gb * double(m) * double(n);
-  // Where both come within 1 %, the launches of one product each.
-  return 1.01 * fused <= per_product ? full[pick] : -1;
+  // Eight products within 1 %: the launches of one each, whose estimate is rougher.
+  return (im ? 1.0 : 1.01) * fused <= per_product ? full[pick] : -1;
 }
 
 hipError_t launch_grouped_fused(const FusedArgs* probs, const FusedItem* items, int nitems, hipStream_t s) {
