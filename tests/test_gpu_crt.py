@@ -392,3 +392,34 @@ def test_few_columns_reconstruct_in_few_waves(bq):
     total = sum(min(ms[q::8]) for q in range(8))
     print(f"reconstruction of 20000 x 16: {total:.2f} ms", flush=True)
     assert len(ms) == 40 and total < 1.2
+
+
+def test_chunked_exponents_in_a_captured_graph(bq):
+    """The exponents of a long inner dimension are cleared and joined by the
+    launches of every replay: operands that change between replays, smaller
+    ones after larger."""
+    import torch
+
+    m, k, n = 20, 4100, 30
+    A, B = (torch.from_numpy(X).to("cuda") for X in inputs.pair(m, k, n, "normal", seed=97))
+    C = torch.empty((8, m, n), dtype=torch.float64, device="cuda")
+    ws = torch.empty(bq.workspace_size(m, n, k, prec=PREC)[0], dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    print(f"capture crt {m}x{k}x{n}", flush=True)
+    with torch.cuda.stream(s):
+        g.capture_begin(capture_error_mode="thread_local")
+        bq.bq_gemm(A, B, C, prec=PREC, workspace=ws, stream=s)
+        g.capture_end()
+    torch.cuda.synchronize()
+    for scale in (1.0, 2.0 ** 40, 2.0 ** -90):
+        A.mul_(scale)
+        C.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        eager = bq.bq_gemm(A, B, prec=PREC)
+        torch.cuda.synchronize()
+        assert torch.equal(C, eager), scale
+        assert oracle.rel_frobenius(C.cpu().numpy(), oracle.gemm(A.cpu().numpy(), B.cpu().numpy())) <= TOL
+    del g
