@@ -333,9 +333,10 @@ typedef BQ_ENUM(bq_kernel_e) {
                                launch of all eight products (8 real)   */
   BQ_KERNEL_COMBINE = 10,   /* Hadamard pre-combination              */
   BQ_KERNEL_FILL = 11,      /* zero fill of a structurally zero block */
-  BQ_KERNEL_SPLIT = 12,     /* exponents + digit slices of one operand;
-                               CRT form: exponents of a complex product's
-                               operands, or residues of a real product's */
+  BQ_KERNEL_SPLIT = 12,     /* exponents of both operands of a real product,
+                               or their digit slices; CRT form: exponents of
+                               a complex product's operands, or residues of
+                               a real product's */
   BQ_KERNEL_SLICE_GEMM = 13, /* one real product from digit slices;
                                flops = pairs * 2 m n k, config = slices */
   BQ_KERNEL_GROUPED = 14,    /* one launch of a batched plan (whole graph);

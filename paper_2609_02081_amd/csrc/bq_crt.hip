@@ -549,18 +549,17 @@ constexpr int kCombineCols = 4;
 // digit 2 u + h (c in 0..15, f in 16..18) is put into the row that result u of
 // lane half h holds.  lo[i] has zeros in the other half's k: the product with
 // [i] sums the residues of the elements of lane half i alone.  top: moduli 16..19.
-template <int NG>
 struct CrtRows {
   i4v lo[2], top[2];
 };
 
 template <int NG>
-__device__ __forceinline__ CrtRows<NG> crt_rows(int nmod) {
+__device__ __forceinline__ CrtRows crt_rows(int nmod) {
   static_assert(offsetof(CrtConsts, c) == 0 && offsetof(CrtConsts, f) == 16 * 32, "digits in rows of 32 bytes");
   const int lane = threadIdx.x & 63, row = lane & 31;
   const int digit = 8 * (row >> 3) + 2 * (row & 3) + (row >> 2 & 1);
   const int* k = reinterpret_cast<const int*>(&kCrtC.n[nmod]) + 8 * (digit < 19 ? digit : 0);
-  CrtRows<NG> A;
+  CrtRows A;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const bool mine = digit < 19 && (lane >> 5) == i;
@@ -572,9 +571,8 @@ __device__ __forceinline__ CrtRows<NG> crt_rows(int nmod) {
 }
 
 template <int NG, typename Args>
-__device__ __forceinline__ void crt_values(const Args& g, int nmod, const CrtRows<NG>& A, const signed char* res,
-                                           int64_t off,
-                                           const int (&shift)[4], double (&out)[4]) {
+__device__ __forceinline__ void crt_values(const Args& g, int nmod, const CrtRows& A, const signed char* res,
+                                           int64_t off, const int (&shift)[4], double (&out)[4]) {
   // R[e][G]: residues 4 G .. 4 G + 3 of element e.
   int R[4][NG];
 #pragma unroll
@@ -594,7 +592,7 @@ __device__ __forceinline__ void crt_values(const Args& g, int nmod, const CrtRow
   }
   const crt_consts_ptr K = (crt_consts_ptr)&kCrtC.n[nmod];
   uint64_t lo[4], hi[4];
-  unsigned near[4];  // below 32: s within 2^-10 of 1/2
+  unsigned near[4];  // below 32: the fraction of s within 2^-11 of 1/2
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     i4v x{0, 0, 0, 0};
@@ -675,7 +673,7 @@ __device__ __forceinline__ void crt_combine_at(const Args& g, int nmod, int64_t 
   if (!live) r = c0 = 0;
   const int np = g.np;
   const int64_t n = g.n;
-  const CrtRows<NG> A = crt_rows<NG>(nmod);
+  const CrtRows A = crt_rows<NG>(nmod);
   double t[kCrtProducts][CC];
 #pragma unroll
   for (int p = 0; p < kCrtProducts; ++p) {

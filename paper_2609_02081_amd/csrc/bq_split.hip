@@ -567,8 +567,6 @@ hipError_t launch_slice_gemm(int et, int S, const SliceGemmArgs& g, hipStream_t 
   return hipErrorInvalidValue;
 }
 
-
-
 int max_slices(int et) { return et == 0 ? 8 : (et == 1 ? 13 : 9); }
 
 }  // namespace bq

@@ -14,7 +14,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef double d4s __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef int i4v __attribute__((ext_vector_type(4)));
-typedef int i2v __attribute__((ext_vector_type(2)));
 
 // Row / column exponent markers: INT_MIN for an all-zero row or column (its
 // digits are zero and so is its part of the product), kExpNonFinite for one
