@@ -17,6 +17,7 @@
 #include <limits.h>
 #include <stddef.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -103,8 +104,11 @@ __device__ __forceinline__ int crt_residue(int lo, int hi, const CrtModulus& m) 
 // bound (8 or 16 bytes read and N written per element and value): at n = 4096
 // all exponents and residues of a product take 6.8 ms (28 GB, 4.1 TB/s)
 // against 9.6 with a launch and an atomic pass per operand; at n = 1024 0.59
-// ms against 1.35 (32 launches against 144).
-__device__ __forceinline__ void crt_split_block(const SplitOperand& a, int64_t b) {
+// ms against 1.35 (32 launches against 144).  A thread's chain of 16 elements,
+// three values and 15 moduli takes 20 us however few blocks there are: small
+// launches divide the moduli among `parts` blocks, each of which forms the digits
+// again (crt_split_parts).
+__device__ __forceinline__ void crt_split_block(const SplitOperand& a, int64_t b, int part, int parts) {
   const int64_t nkt = a.kp / 64;
   const int64_t rt = b / nkt, kt = b % nkt;
   const int t = threadIdx.x;
@@ -117,6 +121,7 @@ __device__ __forceinline__ void crt_split_block(const SplitOperand& a, int64_t b
   load_inner16(a, a.r, v, k0, K, in, r);
   if (want_i) load_inner16(a, a.i, v, k0, K, in, im);
   const int64_t o = digit_offset(v, k0, a.kp);
+  const int i0 = part * a.count / parts, i1 = (part + 1) * a.count / parts;  // this part's moduli
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     if (!a.out[s]) continue;
@@ -127,8 +132,8 @@ __device__ __forceinline__ void crt_split_block(const SplitOperand& a, int64_t b
       const double x = s == 0 ? r[j] : (s == 1 ? im[j] : __builtin_fma(a.w2, im[j], r[j]));
       crt_digits(x, e, a.bits, lo[j], hi[j]);
     }
-    unsigned char* out = static_cast<unsigned char*>(a.out[s]) + o;
-    for (int i = 0; i < a.count; ++i) {
+    unsigned char* out = static_cast<unsigned char*>(a.out[s]) + o + i0 * a.plane;
+    for (int i = i0; i < i1; ++i) {
       const CrtModulus m = kCrtW.m[i];
       i4v q;
 #pragma unroll
@@ -141,11 +146,12 @@ __device__ __forceinline__ void crt_split_block(const SplitOperand& a, int64_t b
   }
 }
 
-// Both operands of a product in one launch: the blocks of x, then those of y.
+// Both operands of a product in one launch: the blocks of x, then those of y;
+// blockIdx.y: the part.
 __global__ void __launch_bounds__(256) crt_split(const SplitOperand x, const SplitOperand y, int64_t xblocks) {
   const int64_t b = blockIdx.x;
-  if (b < xblocks) crt_split_block(x, b);
-  else crt_split_block(y, b - xblocks);
+  if (b < xblocks) crt_split_block(x, b, blockIdx.y, gridDim.y);
+  else crt_split_block(y, b - xblocks, blockIdx.y, gridDim.y);
 }
 
 // One INT8 GEMM per modulus: residue planes of X (rows padded to 256) and Y
@@ -773,7 +779,7 @@ __global__ void __launch_bounds__(256) crt_split_grouped(const SplitOperand* ite
   const int64_t b = blockIdx.x;
   const int i = find_item(prefix, count, b);
   const SplitOperand a = items[i];
-  crt_split_block(a, b - prefix[i]);
+  crt_split_block(a, b - prefix[i], blockIdx.y, gridDim.y);
 }
 
 // The tables are read through the constant address space, so that the search
@@ -810,11 +816,22 @@ crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix, int coun
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Parts of a residue launch of `blocks` blocks: the moduli in as many as fill the
+// CUs once, none from 256 blocks on.  One part against the rule, 2 and 8: one call
+// n = 64 (4 blocks) 444 against 346 us, 372, 348; 256 (32) 487 against 393, 440,
+// 393; 300 (60) 544 against 470, 500, 488; 512 (128) 621 against 571, 571, 636;
+// 1024 (512) 1303, 1329, 1663.  Batches, op N T: 1 product of 72 314 against 214,
+// 8 401 against 323, 64 (512 blocks) 744, 756, 945.
+constexpr int kCrtSplitMostParts = 15;
+static unsigned crt_split_parts(int64_t blocks) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kCrtSplitMostParts, 256 / std::max<int64_t>(1, blocks)));
+}
+
 hipError_t launch_crt_split(const SplitOperand& x, const SplitOperand& y, hipStream_t st) {
   const int64_t xb = split_blocks(x), blocks = xb + split_blocks(y);
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff || x.count > kMaxCrtModuli || y.count > kMaxCrtModuli) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_split, dim3((unsigned)blocks), dim3(256), 0, st, x, y, xb);
+  hipLaunchKernelGGL(crt_split, dim3((unsigned)blocks, crt_split_parts(blocks)), dim3(256), 0, st, x, y, xb);
   return hipGetLastError();
 }
 
@@ -891,7 +908,8 @@ hipError_t launch_crt_split_grouped(const SplitOperand* items, const int64_t* pr
                                     hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_split_grouped, dim3((unsigned)blocks), dim3(256), 0, st, items, prefix, count);
+  hipLaunchKernelGGL(crt_split_grouped, dim3((unsigned)blocks, crt_split_parts(blocks)), dim3(256), 0, st, items, prefix,
+                     count);
   return hipGetLastError();
 }
 

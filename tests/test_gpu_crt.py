@@ -423,3 +423,41 @@ def test_chunked_exponents_in_a_captured_graph(bq):
         assert torch.equal(C, eager), scale
         assert oracle.rel_frobenius(C.cpu().numpy(), oracle.gemm(A.cpu().numpy(), B.cpu().numpy())) <= TOL
     del g
+
+
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("N", "T"), ("T", "N")])
+@pytest.mark.parametrize("m,k,n", [(5, 3, 7), (64, 128, 64), (130, 190, 66), (200, 257, 190), (400, 300, 350)])
+@pytest.mark.parametrize("N", [5, 13, 16, 20])
+def test_residues_in_parts(bq, N, m, k, n, opA, opB):
+    """Launches of 4 to 240 blocks form the residues in 15 parts to one, with
+    more, fewer and as many moduli as parts: a real product equals the oracle's
+    in every element."""
+    R = inputs.MASKS["real"]
+    A, B = inputs.pair(m, k, n, "logspread", seed=98 + N, mask_a=R, mask_b=R)
+    if m * n > 20000:
+        A[0, 10:] = np.round(A[0, 10:])  # the rest of the rows is not compared
+    print(f"crt residues in parts {m}x{k}x{n} N={N} {opA}{opB}", flush=True)
+    stored = [np.ascontiguousarray(X.transpose(0, 2, 1)) if op == "T" else X for X, op in ((A, opA), (B, opB))]
+    got = run(bq, *stored, N, mask_a=R, mask_b=R, opA=opA, opB=opB)[0]
+    rows = slice(0, 10) if m * n > 20000 else slice(0, m)
+    assert np.array_equal(got[rows], ozaki2.product(A[0, rows], B[0], N))
+
+
+def test_small_residue_launches_are_short(bq):
+    """The residues of a real product of n = 64 in 15 parts: as long as the
+    exponents before them (6 us between trace events; 10.4 in one part)."""
+    import torch
+
+    A, B = (torch.rand((8, 64, 64), dtype=torch.float64, device="cuda") for _ in range(2))
+    R = inputs.MASKS["real"]
+    for _ in range(3):
+        bq.bq_gemm(A, B, prec=PREC, mask_a=R, mask_b=R)
+    torch.cuda.synchronize()
+    bq.trace_enable(True)
+    for _ in range(20):
+        bq.bq_gemm(A, B, prec=PREC, mask_a=R, mask_b=R)
+    recs = [r for r in bq.trace_read() if r["kernel"] == "split"]
+    bq.trace_enable(False)
+    us = [min(r["ms"] for r in recs[q::2]) * 1e3 for q in (0, 1)]
+    print(f"n = 64: exponents {us[0]:.1f} us, residues {us[1]:.1f} us", flush=True)
+    assert us[1] < 1.35 * us[0]
