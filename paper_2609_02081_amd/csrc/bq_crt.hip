@@ -775,10 +775,18 @@ crt_combine(const CrtCombineArgs g, int nmod) {
 // ---------------------------------------------------------------------------
 // Grouped forms: one launch over the items of many problems.
 // ---------------------------------------------------------------------------
+// VALUES: blockIdx.z is the one of the up to three values that the block forms.
+template <bool VALUES>
 __global__ void __launch_bounds__(256) crt_split_grouped(const SplitOperand* items, const int64_t* prefix, int count) {
   const int64_t b = blockIdx.x;
   const int i = find_item(prefix, count, b);
-  const SplitOperand a = items[i];
+  SplitOperand a = items[i];
+  if constexpr (VALUES) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      if (s != (int)blockIdx.z) a.out[s] = nullptr;
+    if (!a.out[0] && !a.out[1] && !a.out[2]) return;
+  }
   crt_split_block(a, b - prefix[i], blockIdx.y, gridDim.y);
 }
 
@@ -823,6 +831,12 @@ crt_combine_grouped(const CrtCombineArgs* items, const int64_t* prefix, int coun
 // 1024 (512) 1303, 1329, 1663.  Batches, op N T: 1 product of 72 314 against 214,
 // 8 401 against 323, 64 (512 blocks) 744, 756, 945.
 constexpr int kCrtSplitMostParts = 15;
+// A batch's launch of so few blocks has its (up to three) values in blocks of
+// their own as well, the moduli in as many parts as then fill the CUs.  All
+// values in a block against this, whole batches: op N T 1 product of 72 (8
+// blocks) 215 against 206 us, 2 of unequal shapes 244 against 231; N N 1 of 72
+// 221 against 208; 8 of 72 (64 blocks) 328 against 323, within a run's spread.
+constexpr int64_t kCrtSplitValuesMost = 42;
 static unsigned crt_split_parts(int64_t blocks) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kCrtSplitMostParts, 256 / std::max<int64_t>(1, blocks)));
 }
@@ -908,8 +922,12 @@ hipError_t launch_crt_split_grouped(const SplitOperand* items, const int64_t* pr
                                     hipStream_t st) {
   if (count <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(crt_split_grouped, dim3((unsigned)blocks, crt_split_parts(blocks)), dim3(256), 0, st, items, prefix,
-                     count);
+  if (blocks <= kCrtSplitValuesMost)
+    hipLaunchKernelGGL(crt_split_grouped<true>, dim3((unsigned)blocks, crt_split_parts(3 * blocks), 3), dim3(256), 0, st,
+                       items, prefix, count);
+  else
+    hipLaunchKernelGGL(crt_split_grouped<false>, dim3((unsigned)blocks, crt_split_parts(blocks)), dim3(256), 0, st, items,
+                       prefix, count);
   return hipGetLastError();
 }
 

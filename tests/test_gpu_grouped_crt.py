@@ -182,3 +182,15 @@ def test_tall_tiles_of_a_batch(bq):
     rng = np.random.default_rng(94)
     sizes = [(256, 256, 256)] * 6 + [(250, 64, 300), (512, 130, 129), (500, 1030, 260), (100, 40, 70)]
     _check(bq, [_problem(rng, *s) for s in sizes], oracle_check=False).close()
+
+
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("N", "T"), ("H", "C")])
+@pytest.mark.parametrize("count", [1, 4, 21, 22])
+def test_values_of_small_launches_in_blocks_of_their_own(bq, count, opA, opB):
+    """Two residue blocks a product, up to 42 a launch with each value in a
+    block of its own and 44 without, masks that want fewer values among them:
+    equal to the single calls bit for bit."""
+    rng = np.random.default_rng(88)
+    masks = [(0xFF, 0xFF), (0x0F, 0x0F), (0x01, 0xFF), (0xF0, 0x11)]
+    probs = [_problem(rng, 64 - i, 64 - 2 * i, 1 + 3 * i, opA, opB, *masks[i % 4]) for i in range(count)]
+    _check(bq, probs).close()
